@@ -277,8 +277,9 @@ int ddamg_apply_dirac(ddamg_ctx* ctx, const void* in, void* out, int sign, int p
  * in and out hold the fields one after the other (spinor layout above, each
  * field V*12 complex128); the kernel reads the links and the clover term once
  * for all fields, as the lock-step outer solve does.  Same arithmetic per
- * field as ddamg_apply_dirac (bit-identical results); the library stages the
- * fields in device memory of its own for the call.  INVALID_ARG for NULL
+ * field as ddamg_apply_dirac (bit-identical results); host fields, and device
+ * fields of which in and out overlap, are staged in device memory of the
+ * library's own for the call.  INVALID_ARG for NULL
  * fields, nfields out of range or an unknown precision; BAD_STATE without a
  * gauge field. */
 int ddamg_apply_dirac_multi(ddamg_ctx* ctx, int nfields, const void* in, void* out, int sign, int precision,
@@ -287,15 +288,15 @@ int ddamg_apply_dirac_multi(ddamg_ctx* ctx, int nfields, const void* in, void* o
  * allocate device memory (code under HIP graph capture, serving loops,
  * harnesses that forbid hipMalloc).  Same operator and kernels as
  * ddamg_apply_dirac with precision DDAMG_FP64; in and out are device arrays
- * (spinor layout above, complex128, caller-owned, may not alias).  The two
- * block-layout fields it needs live in a scratch array of the library that
- * every device it runs on holds for the life of the process (48 MiB: two
- * fields of at most 131072 sites); lattices with more sites return
- * INVALID_ARG.  The call only enqueues its kernels on the context's stream and
- * returns: out is ready when that stream reaches them.  Every call on one
- * device shares the one scratch array, so calls that can overlap on one GPU
- * (contexts on different streams) race; the array needs no clearing, since
- * each call writes every entry it reads.  sign must be +1 or -1; BAD_STATE
+ * (spinor layout above, complex128, caller-owned).  One kernel reads in and
+ * writes out; an input that overlaps the output is first copied to a scratch
+ * array of the library that every device it runs on holds for the life of the
+ * process (24 MiB: one field of at most 131072 sites).  Lattices with more
+ * sites return INVALID_ARG.  The call only enqueues its kernels on the
+ * context's stream and returns: out is ready when that stream reaches them.
+ * Calls with overlapping fields on one device share the scratch array, so two
+ * of them that can overlap on one GPU (contexts on different streams) race;
+ * the array needs no clearing, since each call writes every entry it reads.  sign must be +1 or -1; BAD_STATE
  * without a gauge field. */
 int ddamg_apply_dirac_noalloc(ddamg_ctx* ctx, const void* in, void* out, int sign);
 /* iters SAP iterations on D x = b starting from x (updated in place): the

@@ -152,6 +152,28 @@ void load_links(Ctx& c, const void* links, int on_device) {
   c.have_gauge = true;
 }
 
+// D(tw) on K caller fields: device fields are read and written in place by one
+// launch; host fields, and device fields that overlap (which the launch cannot
+// take), go through the staging buffers
+void apply_dirac_fields(Ctx& c, const void* in, void* out, int K, Twist tw, int precision, int on_device,
+                        DevBuf& stage_in, DevBuf& stage_out, bool transient) {
+  const size_t bytes = sizeof(cx<double>) * (size_t)c.fine_len() * K;
+  const cx<double>* src = (const cx<double>*)in;
+  cx<double>* dst = (cx<double>*)out;
+  if (!on_device || overlap(in, out, bytes)) {
+    stage_in.ensure(bytes, transient);
+    HIP_CHECK(hipMemcpyAsync(stage_in.p, in, bytes, on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, c.st));
+    src = stage_in.as<cx<double>>();
+  }
+  if (!on_device) {
+    stage_out.ensure(bytes, transient);
+    dst = stage_out.as<cx<double>>();
+  }
+  c.dirac_lex(src, dst, K, tw, precision);
+  if (!on_device) HIP_CHECK(hipMemcpyAsync(out, dst, bytes, hipMemcpyDeviceToHost, c.st));
+  c.sync();
+}
+
 }  // namespace
 
 extern "C" {
@@ -661,33 +683,8 @@ int ddamg_apply_dirac(ddamg_ctx* ctx, const void* in, void* out, int sign, int p
     Ctx& c = ctx->c;
     need_gauge(c);
     if (!in || !out) throw Error(INVALID_ARG, "NULL field");
-    const Twist tw = c.twist(sign);
-    long N = c.fine_len();
-    c.upload_fine(in, on_device, c.f64a.as<cx<double>>());
-    if (precision == DDAMG_FP64) {
-      c.dirac64(c.f64a.as<cx<double>>(), c.f64b.as<cx<double>>(), tw);
-    } else {
-      c.ensure_32();
-      c.f32a.ensure(sizeof(cx<float>) * N);
-      c.f32b.ensure(sizeof(cx<float>) * N);
-      launch_copy_cvt<double, float>(c.f64a.as<cx<double>>(), c.f32a.as<cx<float>>(), N, c.st);
-      if (precision == DDAMG_FP32)
-        launch_dirac<float, float>(c.g, c.U32.p, c.H32.as<float>(), tw, c.f32a.as<cx<float>>(),
-                                   c.f32b.as<cx<float>>(), c.st);
-      else if (precision == DDAMG_FP16 || precision == DDAMG_BF16) {
-        c.ensure_16(precision);
-        if (precision == DDAMG_FP16)
-          launch_dirac<float, f16>(c.g, c.U16.p, c.H32.as<float>(), tw, c.f32a.as<cx<float>>(),
-                                   c.f32b.as<cx<float>>(), c.st);
-        else
-          launch_dirac<float, bf16>(c.g, c.U16.p, c.H32.as<float>(), tw, c.f32a.as<cx<float>>(),
-                                    c.f32b.as<cx<float>>(), c.st);
-      } else
-        throw Error(INVALID_ARG, "unknown precision");
-      launch_copy_cvt<float, double>(c.f32b.as<cx<float>>(), c.f64b.as<cx<double>>(), N, c.st);
-    }
-    c.download_fine(c.f64b.as<cx<double>>(), out, on_device);
-    c.sync();
+    if (precision < DDAMG_FP64 || precision > DDAMG_BF16) throw Error(INVALID_ARG, "unknown precision");
+    apply_dirac_fields(c, in, out, 1, c.twist(sign), precision, on_device, c.lex, c.f64b, false);
     return DDAMG_OK;
   });
 }
@@ -701,39 +698,8 @@ int ddamg_apply_dirac_multi(ddamg_ctx* ctx, int nfields, const void* in, void* o
     if (!in || !out) throw Error(INVALID_ARG, "NULL field");
     if (nfields < 1 || nfields > 16) throw Error(INVALID_ARG, "nfields must be in [1, 16]");
     if (precision < DDAMG_FP64 || precision > DDAMG_BF16) throw Error(INVALID_ARG, "unknown precision");
-    const Twist tw = c.twist(sign);
-    const long N = c.fine_len();
-    const size_t fb = sizeof(cx<double>) * (size_t)N;
     DevBuf a64, b64;
-    a64.alloc(fb * nfields, true);
-    b64.alloc(fb * nfields, true);
-    for (int k = 0; k < nfields; ++k)
-      c.upload_fine((const char*)in + fb * k, on_device, a64.as<cx<double>>() + (long)k * N);
-    if (precision == DDAMG_FP64) {
-      c.dirac64_multi(a64.as<cx<double>>(), b64.as<cx<double>>(), nfields, N, tw);
-    } else {
-      c.ensure_32();
-      DevBuf a32, b32;
-      a32.alloc(sizeof(cx<float>) * (size_t)N * nfields, true);
-      b32.alloc(sizeof(cx<float>) * (size_t)N * nfields, true);
-      launch_copy_cvt<double, float>(a64.as<cx<double>>(), a32.as<cx<float>>(), N * nfields, c.st);
-      if (precision == DDAMG_FP32) {
-        launch_dirac_multi<float, float>(c.g, c.U32.p, c.H32.as<float>(), tw, nfields, N, a32.as<cx<float>>(),
-                                         b32.as<cx<float>>(), c.st);
-      } else {
-        c.ensure_16(precision);
-        if (precision == DDAMG_FP16)
-          launch_dirac_multi<float, f16>(c.g, c.U16.p, c.H32.as<float>(), tw, nfields, N, a32.as<cx<float>>(),
-                                         b32.as<cx<float>>(), c.st);
-        else
-          launch_dirac_multi<float, bf16>(c.g, c.U16.p, c.H32.as<float>(), tw, nfields, N, a32.as<cx<float>>(),
-                                          b32.as<cx<float>>(), c.st);
-      }
-      launch_copy_cvt<float, double>(b32.as<cx<float>>(), b64.as<cx<double>>(), N * nfields, c.st);
-    }
-    for (int k = 0; k < nfields; ++k)
-      c.download_fine(b64.as<cx<double>>() + (long)k * N, (char*)out + fb * k, on_device);
-    c.sync();
+    apply_dirac_fields(c, in, out, nfields, c.twist(sign), precision, on_device, a64, b64, true);
     return DDAMG_OK;
   });
 }

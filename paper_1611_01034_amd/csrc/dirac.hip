@@ -67,4 +67,130 @@ DIRAC_INST(float, f16)
 DIRAC_INST(float, bf16)
 #undef DIRAC_INST
 
+// ---------------------------------------------------------------------------
+// The same operator between fields in the caller's layout (lexicographic
+// [V][4][3] complex128), arithmetic in R: out = D(tw) in for K fields at a
+// stride of ld complex, in one pass.  What bounds it is memory: the spinors
+// are read and written once where a conversion to the block layout and back
+// took two more passes each.  A block's sites are read as whole runs along X
+// (consecutive threads read consecutive components) into LDS, rounded to R;
+// in LDS a site's components lie together, padded to 13, so that both the
+// staging writes and the per-site reads are free of bank conflicts.  A
+// neighbour outside the block is read from the caller's field, where its 12
+// components are contiguous (the block layout's X faces use two of every
+// eight sites of a line).  The result goes back through the same LDS so that
+// it too is written in whole runs.  The order of every sum is that of k_dirac.
+constexpr int LEX_LS = 13;
+
+template <class R>
+__device__ __forceinline__ void load_nbr_lex(const cx<double>* in, const cx<R>* lds, int B, int Bn, int sn, int ln,
+                                             cx<R> p[12]) {
+  if (Bn == B) {
+#pragma unroll
+    for (int c = 0; c < 12; ++c) p[c] = lds[sn * LEX_LS + c];
+  } else {
+    const cx<double>* q = in + (long)ln * 12;
+#pragma unroll
+    for (int c = 0; c < 12; ++c) p[c] = mk<R>((R)q[c].re, (R)q[c].im);
+  }
+}
+
+template <int MU, class R, class S>
+__device__ __forceinline__ void hop_lex_dir(const typename store_traits<S>::elem* U, const cx<double>* in,
+                                            const cx<R>* lds, const Geom& g, int B, int s, const SiteNbr& me, int lex,
+                                            cx<R> out[12]) {
+  cx<R> psi[12], u[9];
+  int Bn, sn;
+  int str = 1;  // lexicographic stride of direction MU
+#pragma unroll
+  for (int d = MU + 1; d < 4; ++d) str *= g.L[d];
+  const int wrap = (g.L[MU] - 1) * str;
+  nbr_of(g, me, MU, +1, Bn, sn);
+  const bool hi = me.l[MU] == g.b[MU] - 1 && me.bc[MU] == g.nb[MU] - 1;
+  load_nbr_lex(in, lds, B, Bn, sn, hi ? lex - wrap : lex + str, psi);
+  load_link<R, S>(U, g, B, s, MU, u);
+  hop_accum_t<0, MU>(psi, u, out);
+  nbr_of(g, me, MU, -1, Bn, sn);
+  const bool lo = me.l[MU] == 0 && me.bc[MU] == 0;
+  load_nbr_lex(in, lds, B, Bn, sn, lo ? lex + wrap : lex - str, psi);
+  load_link<R, S>(U, g, Bn, sn, MU, u);
+  hop_accum_t<1, MU>(psi, u, out);
+}
+
+template <class R, class S>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(R) == 8 ? 2 : 3, 8)))
+k_dirac_lex(Geom g, int gm, const typename store_traits<S>::elem* __restrict__ U, const R* __restrict__ H,
+            TwistR<R> tw, int K, long ld, const cx<double>* __restrict__ in, cx<double>* __restrict__ out) {
+  typedef double v2d __attribute__((ext_vector_type(2)));
+  extern __shared__ char smem_raw[];
+  cx<R>* lds = reinterpret_cast<cx<R>*>(smem_raw);  // bs x LEX_LS
+  __shared__ int xof[256], sof[256];                // lexicographic site and slot of the block's j-th site
+  const int w = gm > 0 ? group_remap(blockIdx.x, gm * K) : xcd_remap(blockIdx.x, gridDim.x), s = threadIdx.x;
+  const int B = w / K, col = w - B * K;
+  in += (long)col * ld;
+  out += (long)col * ld;
+  SiteNbr me;
+  me_of(g, B, s, me);
+  int lex;
+  {
+    int x[4];
+    for (int d = 0; d < 4; ++d) x[d] = me.bc[d] * g.b[d] + me.l[d];
+    lex = (int)lex_index(g, x);
+    const int j = ((me.l[0] * g.b[1] + me.l[1]) * g.b[2] + me.l[2]) * g.b[3] + me.l[3];
+    xof[j] = lex;
+    sof[j] = s;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 12; ++i) {
+    const int e = i * g.bs + s, j = e / 12, c = e - 12 * j;
+    const cx<double> v = in[(long)xof[j] * 12 + c];
+    lds[sof[j] * LEX_LS + c] = mk<R>((R)v.re, (R)v.im);
+  }
+  __syncthreads();
+  cx<R> psi[12], acc[12];
+#pragma unroll
+  for (int c = 0; c < 12; ++c) psi[c] = lds[s * LEX_LS + c];
+  site_term(H, g, B, s, tw, psi, acc);
+#pragma unroll 1
+  for (int mu = 0; mu < g.ndir; ++mu) {
+    switch (mu) {
+      case 0: hop_lex_dir<0, R, S>(U, in, lds, g, B, s, me, lex, acc); break;
+      case 1: hop_lex_dir<1, R, S>(U, in, lds, g, B, s, me, lex, acc); break;
+      case 2: hop_lex_dir<2, R, S>(U, in, lds, g, B, s, me, lex, acc); break;
+      default: hop_lex_dir<3, R, S>(U, in, lds, g, B, s, me, lex, acc); break;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < 12; ++c) lds[s * LEX_LS + c] = acc[c];
+  __syncthreads();
+  // streaming stores, as in k_dirac
+#pragma unroll
+  for (int i = 0; i < 12; ++i) {
+    const int e = i * g.bs + s, j = e / 12, c = e - 12 * j;
+    const cx<R> v = lds[sof[j] * LEX_LS + c];
+    __builtin_nontemporal_store(v2d{(double)v.re, (double)v.im},
+                                reinterpret_cast<v2d*>(out + (long)xof[j] * 12 + c));
+  }
+}
+
+template <class R, class S>
+void launch_dirac_lex(const Geom& g, const void* U, const R* H, Twist tw, int K, long ld, const cx<double>* in,
+                      cx<double>* out, hipStream_t st) {
+  if (g.V > 0x7fffffffL) throw Error(INVALID_ARG, "lattice of 2^31 sites or more");
+  const size_t sm = (size_t)LEX_LS * g.bs * sizeof(cx<R>);
+  const int gm = g.nblocks % (16 * g.nb[3]) == 0 ? 2 * g.nb[3] : 0;
+  hipLaunchKernelGGL((k_dirac_lex<R, S>), dim3(g.nblocks * K), dim3(g.bs), sm, st, g, gm,
+                     (const typename store_traits<S>::elem*)U, H, TwistR<R>(tw), K, ld, in, out);
+}
+#define LEX_INST(R, S)                                                                                            \
+  template void launch_dirac_lex<R, S>(const Geom&, const void*, const R*, Twist, int, long, const cx<double>*, \
+                                       cx<double>*, hipStream_t);
+LEX_INST(double, double)
+LEX_INST(float, float)
+LEX_INST(float, f16)
+LEX_INST(float, bf16)
+#undef LEX_INST
+
 }  // namespace ddamg

@@ -58,6 +58,10 @@ void launch_dirac(const Geom& g, const void* U, const R* H, Twist tw, const cx<R
 template <class R, class S>
 void launch_dirac_multi(const Geom& g, const void* U, const R* H, Twist tw, int K, long ld, const cx<R>* in,
                         cx<R>* out, hipStream_t st);
+// the same between lexicographic complex128 fields (in and out must not overlap)
+template <class R, class S>
+void launch_dirac_lex(const Geom& g, const void* U, const R* H, Twist tw, int K, long ld, const cx<double>* in,
+                      cx<double>* out, hipStream_t st);
 template <class R, class S>
 void launch_sap(const Geom& g, int colour, const void* U, const R* H, const R* Minv, Twist tw, const cx<R>* b,
                 cx<R>* x, int n_mr, hipStream_t st);

@@ -1,8 +1,8 @@
 // ddamg_apply_dirac_noalloc: the fine operator D(+-mu) = D_W +- i Gamma5 mu
 // (Sec. 1) on device fields, for callers that cannot allocate device memory.
-// It runs the kernels of ddamg_apply_dirac in FP64 (lexicographic -> block
-// layout, D, block layout -> lexicographic); the two block-layout fields live
-// in the file-scope array below instead of the context's buffers.
+// It runs the kernel of ddamg_apply_dirac in FP64, which reads and writes the
+// caller's fields in place; only an input that overlaps the output is copied
+// first, to the file-scope array below instead of the context's buffers.
 #include <mutex>
 
 #include "solver.hpp"
@@ -13,13 +13,13 @@ struct ddamg_ctx {
 
 namespace ddamg {
 
-// Largest lattice the scratch serves: 131072 sites (16^3 x 32).  Two FP64
-// spinor fields in block layout, 2 * 131072 * 12 * 16 bytes = 48 MiB, held by
-// every device the library runs on until the process ends.  Host code never
+// Largest lattice the scratch serves: 131072 sites (16^3 x 32).  One FP64
+// spinor field, 131072 * 12 * 16 bytes = 24 MiB, held by every device the
+// library runs on until the process ends.  Host code never
 // passes the array's name to a kernel or a copy: it uses the address that
 // hipGetSymbolAddress returns on each device.
 constexpr long kNoAllocMaxSites = 131072;
-constexpr size_t kScratchBytes = 2 * (size_t)kNoAllocMaxSites * 12 * sizeof(cx<double>);
+constexpr size_t kScratchBytes = (size_t)kNoAllocMaxSites * 12 * sizeof(cx<double>);
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 namespace {
@@ -61,13 +61,14 @@ extern "C" int ddamg_apply_dirac_noalloc(ddamg_ctx* ctx, const void* in, void* o
     if (c.g.V > kNoAllocMaxSites)
       throw Error(INVALID_ARG, "lattice of " + std::to_string(c.g.V) +
                                    " sites exceeds the no-allocation scratch (at most 131072 sites)");
-    cx<double>* a = (cx<double>*)scratch_of(c.dev);
-    if (!a) throw Error(BAD_STATE, "scratch array not set up on the context's device");
-    cx<double>* b = a + kNoAllocMaxSites * 12;
-    // every entry of the first V*12 of each half is written before it is read
-    launch_from_lex<double>(c.g, (const cx<double>*)in, a, 12, c.st);
-    launch_dirac<double, double>(c.g, c.U64.p, c.H64.as<double>(), c.twist(sign), a, b, c.st);
-    launch_to_lex<double>(c.g, b, (cx<double>*)out, 12, c.st);
+    const cx<double>* src = (const cx<double>*)in;
+    if (overlap(in, out, sizeof(cx<double>) * (size_t)c.fine_len())) {
+      cx<double>* a = (cx<double>*)scratch_of(c.dev);
+      if (!a) throw Error(BAD_STATE, "scratch array not set up on the context's device");
+      launch_copy_cvt<double, double>(src, a, c.fine_len(), c.st);
+      src = a;
+    }
+    launch_dirac_lex<double, double>(c.g, c.U64.p, c.H64.as<double>(), c.twist(sign), 1, 0, src, (cx<double>*)out, c.st);
     HIP_CHECK(hipGetLastError());
     return DDAMG_OK;
   } catch (const Error& e) {

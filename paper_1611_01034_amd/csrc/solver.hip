@@ -736,6 +736,22 @@ void Ctx::dirac64_multi(const cx<double>* in, cx<double>* out, int K, long ld, T
   TimeScope ts(timer, 0, (1152.0 + 384.0 * K) * (double)g.V);
   launch_dirac_multi<double, double>(g, U64.p, H64.as<double>(), tw, K, ld, in, out, st);
 }
+void Ctx::dirac_lex(const cx<double>* in, cx<double>* out, int K, Twist tw, int precision) {
+  const long N = fine_len();
+  if (precision == DDAMG_FP64) {
+    TimeScope ts(timer, 0, (1152.0 + 384.0 * K) * (double)g.V);
+    launch_dirac_lex<double, double>(g, U64.p, H64.as<double>(), tw, K, N, in, out, st);
+    return;
+  }
+  ensure_32();
+  if (precision == DDAMG_FP32) {
+    launch_dirac_lex<float, float>(g, U32.p, H32.as<float>(), tw, K, N, in, out, st);
+    return;
+  }
+  ensure_16(precision);
+  if (precision == DDAMG_FP16) launch_dirac_lex<float, f16>(g, U16.p, H32.as<float>(), tw, K, N, in, out, st);
+  else launch_dirac_lex<float, bf16>(g, U16.p, H32.as<float>(), tw, K, N, in, out, st);
+}
 void Ctx::upload_fine(const void* src, int on_device, cx<double>* dst64) {
   const cx<double>* s = (const cx<double>*)src;
   if (!on_device) {

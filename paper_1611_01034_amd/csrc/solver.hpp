@@ -331,10 +331,19 @@ struct Ctx {
   void dirac64(const cx<double>* in, cx<double>* out, Twist tw);
   // K fields at a stride of ld complex in one launch
   void dirac64_multi(const cx<double>* in, cx<double>* out, int K, long ld, Twist tw);
+  // D(tw) on K lexicographic complex128 fields on the device, arithmetic and
+  // link storage of `precision`; in and out must not overlap
+  void dirac_lex(const cx<double>* in, cx<double>* out, int K, Twist tw, int precision);
   // host/device lex FP64 field -> block layout
   void upload_fine(const void* src, int on_device, cx<double>* dst64);
   void download_fine(const cx<double>* src64, void* dst, int on_device);
 };
+
+// whether two buffers of n bytes share a byte
+inline bool overlap(const void* a, const void* b, size_t n) {
+  const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;
+  return x < y + n && y < x + n;
+}
 
 std::unique_ptr<MGBase> make_mg(Ctx& c);
 

@@ -1,0 +1,105 @@
+"""Kernels that read and write the caller's lexicographic fields, on the GPU
+against the oracle (FP64, Sec. 1 D(mu)): blocks and extents that are no powers
+of two, both block orders of the launch, several fields, every precision, and
+fields that overlap.
+
+Tolerances, fixed before the first run: FP64 1e-12 of the result (the FP64
+operator bar); FP32 arithmetic 2e-6 (eight hops of 3-term complex sums and a
+6-term site term, each rounded once to 2^-24, on results of order 10 times an
+entry); FP16 / BF16 links the same against the oracle on links rounded the
+same way."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+pytestmark = pytest.mark.gpu
+
+KAPPA, CSW, MU = 0.13729, 1.57551, 0.0009
+
+
+@pytest.fixture(scope="module")
+def dd():
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    from paper_1611_01034_amd import ddamg
+    return ddamg
+
+
+def _case(dd, dims, block, seed, mu_odd=None):
+    from oracle import dirac
+    from paper_1611_01034_amd import synth
+    U = synth.gauge_field(dims, 0.3, seed)
+    ctx = dd.DDAMG(dims, block, KAPPA, CSW, MU, stream=torch.cuda.current_stream().cuda_stream)
+    ctx.set_gauge(U)
+    return ctx, U, dirac.WilsonClover(U, KAPPA, CSW, MU)
+
+
+def _round_links(U, prec):
+    """Links rounded once to nearest even (no intermediate FP32)."""
+    if prec == "fp16":
+        f = lambda v: v.astype(np.float16).astype(np.float64)
+    else:
+        def f(v):
+            m, e = np.frexp(v)
+            return np.ldexp(np.round(m * 256.0) / 256.0, e)
+    return f(U.real) + 1j * f(U.imag)
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "fp16", "bf16"])
+@pytest.mark.parametrize("dims,block", [((4, 4, 4, 4), (2, 2, 2, 2)),      # 16 sites a block, one row of two blocks
+                                        ((4, 12, 4, 12), (2, 6, 2, 6)),    # 144 sites, two wavefronts and a quarter
+                                        ((8, 4, 12, 8), (4, 2, 6, 4)),     # 192 sites
+                                        ((8, 8, 8, 16), (4, 4, 4, 4))])    # 256 sites, the other block order
+def test_dirac_on_caller_fields(dd, dims, block, prec):
+    from oracle import dirac
+    from paper_1611_01034_amd import synth
+    ctx, U, op = _case(dd, dims, block, 8101)
+    try:
+        print(f"D(mu) on caller fields: {dims} {block} {prec}", flush=True)
+        K = 3
+        psi = synth.spinor(dims, 8102, nvec=K)
+        dev = torch.from_numpy(psi).cuda()
+        one = [ctx.apply_dirac(dev[k].clone(), precision=prec) for k in range(K)]
+        many = ctx.apply_dirac_multi(dev, sign=+1, precision=prec)
+        host = ctx.apply_dirac(psi[1], precision=prec)
+        ref_op = op
+        if prec in ("fp16", "bf16"):
+            ref_op = dirac.WilsonClover(_round_links(U, prec), KAPPA, CSW, MU, clover=dirac.clover_blocks(op.A))
+        tol = 1e-12 if prec == "fp64" else 2e-6
+        for k in range(K):
+            ref = ref_op.apply(psi[k])
+            got = one[k].cpu().numpy()
+            assert np.linalg.norm(got - ref) <= tol * np.linalg.norm(ref)
+            assert torch.equal(one[k], many[k])
+        assert np.array_equal(host, one[1].cpu().numpy())
+    finally:
+        ctx.close()
+
+
+@pytest.mark.parametrize("shift", [0, 1, 12])
+def test_dirac_with_overlapping_fields(dd, shift):
+    """out over in (shifted by `shift` complex entries): as on separate fields."""
+    import ctypes
+    from paper_1611_01034_amd import synth
+    dims, block = (8, 4, 12, 8), (4, 2, 6, 4)
+    ctx, _, _ = _case(dd, dims, block, 8201)
+    try:
+        n = int(np.prod(dims)) * 12
+        psi = torch.from_numpy(synth.spinor(dims, 8202)).cuda()
+        ref = ctx.apply_dirac(psi)
+        for entry in ("apply_dirac", "noalloc"):
+            print(f"overlapping fields: shift {shift}, {entry}", flush=True)
+            buf = torch.zeros(n + shift, dtype=torch.complex128, device="cuda")
+            buf[:n] = psi.reshape(-1)
+            pi = ctypes.c_void_p(buf.data_ptr())
+            po = ctypes.c_void_p(buf.data_ptr() + 16 * shift)
+            torch.cuda.synchronize()
+            if entry == "noalloc":
+                ctx._check(dd._lib.ddamg_apply_dirac_noalloc(ctx._h, pi, po, 1))
+            else:
+                ctx._check(dd._lib.ddamg_apply_dirac(ctx._h, pi, po, 1, dd.FP64, 1))
+            torch.cuda.synchronize()
+            assert torch.equal(buf[shift:].reshape(ref.shape), ref)
+    finally:
+        ctx.close()
