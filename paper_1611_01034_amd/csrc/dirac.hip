@@ -80,6 +80,8 @@ DIRAC_INST(float, bf16)
 // components are contiguous (the block layout's X faces use two of every
 // eight sites of a line).  The result goes back through the same LDS so that
 // it too is written in whole runs.  The order of every sum is that of k_dirac.
+// 64x32x32x32 FP64: 668 us (4.8 TB/s of 1536 B per site; conversions and
+// k_dirac 338 + 738 + 390 us); six fields at 48x24x24x24: 893 us (2390).
 constexpr int LEX_LS = 13;
 
 template <class R>
