@@ -465,18 +465,16 @@ int ddamg_setup_prec(ddamg_ctx* ctx, const ddamg_params* p, const void* const* i
     c.mg.reset();
     c.p = *p;
     c.mg = make_mg(c);
-    c.lex.ensure(sizeof(cx<double>) * fl);
     c.f64b.ensure(sizeof(cx<double>) * fl);
     c.f32a.ensure(sizeof(cx<float>) * fl);
     for (int i = 0; i < p->nvec[0]; ++i) {
-      // complex64 lexicographic -> FP64 lexicographic staging -> FP32 block layout
+      // complex64 lexicographic -> FP32 block layout
       const cx<float>* src = (const cx<float>*)init_vectors[0] + (long)i * fl;
       if (!on_device) {
         HIP_CHECK(hipMemcpyAsync(c.f64b.p, src, sizeof(cx<float>) * fl, hipMemcpyHostToDevice, c.st));
         src = c.f64b.as<cx<float>>();
       }
-      launch_copy_cvt<float, double>(src, c.lex.as<cx<double>>(), fl, c.st);
-      launch_from_lex<float>(c.g, c.lex.as<cx<double>>(), c.f32a.as<cx<float>>(), 12, c.st);
+      launch_from_lex<float, float>(c.g, src, fl, c.f32a.as<cx<float>>(), fl, 1, c.st);
       c.mg->load_fine_vec(i, c.f32a.as<cx<float>>());
     }
     const void* vecs[3] = {nullptr, init_vectors[1], nullptr};
@@ -532,16 +530,12 @@ int ddamg_solve(ddamg_ctx* ctx, const void* b, void* x, int nrhs, double tol, dd
       double worst = 0;
       for (int r0 = 0; r0 < nrhs; r0 += Kb) {
         const int k = std::min(Kb, nrhs - r0);
-        for (int q = 0; q < k; ++q) {
-          const char* bs = (const char*)b + sizeof(cx<double>) * (size_t)N * (r0 + q);
-          c.upload_fine(bs, on_device, bK.as<cx<double>>() + (long)q * N);
-          check_finite(c, (const double*)(bK.as<cx<double>>() + (long)q * N), 2 * N);
-        }
+        c.upload_fields((const cx<double>*)b + (long)r0 * N, on_device, bK.as<cx<double>>(), k);
+        check_finite(c, (const double*)bK.p, 2 * N * k);
         KrylovResultM km = fgmres_multi<double>(c, ws, k, N, AK, zf ? nullptr : &MK, bK.as<cx<double>>(),
                                                 xK.as<cx<double>>(), tol, c.p.max_iter, false, true, zf ? &MKf : nullptr);
+        c.download_fields(xK.as<cx<double>>(), (cx<double>*)x + (long)r0 * N, on_device, k);
         for (int q = 0; q < k; ++q) {
-          char* xs = (char*)x + sizeof(cx<double>) * (size_t)N * (r0 + q);
-          c.download_fine(xK.as<cx<double>>() + (long)q * N, xs, on_device);
           total_it += km.iters[q];
           it_min = std::min(it_min, km.iters[q]);
           it_max = std::max(it_max, km.iters[q]);
@@ -716,19 +710,18 @@ int ddamg_sap_multi(ddamg_ctx* ctx, int nfields, const void* b, void* x, int ite
     const long N = c.fine_len();
     const int K = nfields;
     const size_t fb = sizeof(cx<double>) * (size_t)N;
-    // K fields in block layout, stride N: FP64 staging, then the working precision
-    DevBuf b64, x64;
-    b64.alloc(fb * K);
-    x64.alloc(fb * K);
-    for (int k = 0; k < K; ++k) {
-      c.upload_fine((const char*)b + fb * k, on_device, b64.as<cx<double>>() + (long)k * N);
-      c.upload_fine((const char*)x + fb * k, on_device, x64.as<cx<double>>() + (long)k * N);
-    }
+    // K fields in block layout, stride N, in the working precision
     if (precision == DDAMG_FP64) {
+      DevBuf b64, x64;
+      b64.alloc(fb * K);
+      x64.alloc(fb * K);
+      c.upload_fields(b, on_device, b64.as<cx<double>>(), K);
+      c.upload_fields(x, on_device, x64.as<cx<double>>(), K);
       for (int it = 0; it < iters; ++it)
         for (int col = 0; col < 2; ++col)
           launch_sap_multi<double, double>(c.g, col, c.U64.p, c.H64.as<double>(), c.M64.as<double>(), c.twist(),
                                            b64.as<cx<double>>(), x64.as<cx<double>>(), mr_steps, K, N, c.st);
+      c.download_fields(x64.as<cx<double>>(), x, on_device, K);
     } else {
       c.ensure_32();
       const void* U = c.U32.p;
@@ -739,8 +732,8 @@ int ddamg_sap_multi(ddamg_ctx* ctx, int nfields, const void* b, void* x, int ite
       DevBuf b32, x32;
       b32.alloc(sizeof(cx<float>) * (size_t)N * K);
       x32.alloc(sizeof(cx<float>) * (size_t)N * K);
-      launch_copy_cvt<double, float>(b64.as<cx<double>>(), b32.as<cx<float>>(), N * K, c.st);
-      launch_copy_cvt<double, float>(x64.as<cx<double>>(), x32.as<cx<float>>(), N * K, c.st);
+      c.upload_fields(b, on_device, b32.as<cx<float>>(), K);
+      c.upload_fields(x, on_device, x32.as<cx<float>>(), K);
       for (int it = 0; it < iters; ++it)
         for (int col = 0; col < 2; ++col) {
           if (precision == DDAMG_FP32)
@@ -753,9 +746,8 @@ int ddamg_sap_multi(ddamg_ctx* ctx, int nfields, const void* b, void* x, int ite
             launch_sap_multi<float, bf16>(c.g, col, U, c.H32.as<float>(), c.M32.as<float>(), c.twist(),
                                           b32.as<cx<float>>(), x32.as<cx<float>>(), mr_steps, K, N, c.st);
         }
-      launch_copy_cvt<float, double>(x32.as<cx<float>>(), x64.as<cx<double>>(), N * K, c.st);
+      c.download_fields(x32.as<cx<float>>(), x, on_device, K);
     }
-    for (int k = 0; k < K; ++k) c.download_fine(x64.as<cx<double>>() + (long)k * N, (char*)x + fb * k, on_device);
     c.sync();
     return DDAMG_OK;
   });
@@ -1094,12 +1086,7 @@ void net_buffers(Ctx& c) {
 
 // C fields in the host layout (FP64, contiguous) -> C-channel block-layout FP32 field
 void net_upload(Ctx& c, const void* src, int on_device, cx<float>* dst) {
-  long fl = c.fine_len();
-  for (int ch = 0; ch < c.net.C; ++ch) {
-    const char* s = (const char*)src + sizeof(cx<double>) * (size_t)fl * ch;
-    c.upload_fine(s, on_device, c.f64a.as<cx<double>>());
-    launch_copy_cvt<double, float>(c.f64a.as<cx<double>>(), dst + (long)ch * fl, fl, c.st);
-  }
+  c.upload_fields(src, on_device, dst, c.net.C);
 }
 
 void net_forward(Ctx& c) {
@@ -1207,21 +1194,18 @@ int ddamg_setup_learned(ddamg_ctx* ctx, const ddamg_params* p, const void* noise
     DevBuf A, B;
     A.alloc(sizeof(cx<float>) * f, true);
     B.alloc(sizeof(cx<float>) * f, true);
-    c.lex.ensure(sizeof(cx<double>) * fl);
     for (int ch = 0; ch < c.net.C; ++ch) {
       cx<float>* dst = A.as<cx<float>>() + (long)ch * fl;
       if (noise_precision == DDAMG_FP64) {
-        c.upload_fine((const char*)noise + sizeof(cx<double>) * (size_t)fl * ch, on_device, c.f64a.as<cx<double>>());
-        launch_copy_cvt<double, float>(c.f64a.as<cx<double>>(), dst, fl, c.st);
+        c.upload_fields((const char*)noise + sizeof(cx<double>) * (size_t)fl * ch, on_device, dst, 1);
       } else {
-        // complex64 lexicographic -> FP64 lexicographic staging -> block layout FP32
+        // complex64 lexicographic -> block layout FP32
         const cx<float>* src = (const cx<float>*)noise + (long)ch * fl;
         if (!on_device) {
           HIP_CHECK(hipMemcpyAsync(c.f64b.p, src, sizeof(cx<float>) * fl, hipMemcpyHostToDevice, c.st));
           src = c.f64b.as<cx<float>>();
         }
-        launch_copy_cvt<float, double>(src, c.lex.as<cx<double>>(), fl, c.st);
-        launch_from_lex<float>(c.g, c.lex.as<cx<double>>(), dst, 12, c.st);
+        launch_from_lex<float, float>(c.g, src, fl, dst, fl, 1, c.st);
       }
     }
     cx<float>* out = net_infer(c, A.as<cx<float>>(), B.as<cx<float>>());
@@ -1311,14 +1295,9 @@ int ddamg_net_forward(ddamg_ctx* ctx, const void* noise, void* out, int on_devic
     c.ensure_32();
     net_buffers(c);
     NetState& n = c.net;
-    long fl = c.fine_len();
     net_upload(c, noise, on_device, n.act.as<cx<float>>());
     const cx<float>* y = net_infer(c, n.act.as<cx<float>>(), n.zb.as<cx<float>>());
-    for (int ch = 0; ch < n.C; ++ch) {
-      launch_copy_cvt<float, double>(y + (long)ch * fl, c.f64b.as<cx<double>>(), fl, c.st);
-      char* dst = (char*)out + sizeof(cx<double>) * (size_t)fl * ch;
-      c.download_fine(c.f64b.as<cx<double>>(), dst, on_device);
-    }
+    c.download_fields(y, out, on_device, n.C);
     c.sync();
     return DDAMG_OK;
   });

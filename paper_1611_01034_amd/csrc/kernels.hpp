@@ -68,10 +68,11 @@ void launch_sap(const Geom& g, int colour, const void* U, const R* H, const R* M
 template <class R, class S>
 void launch_sap_multi(const Geom& g, int colour, const void* U, const R* H, const R* Minv, Twist tw, const cx<R>* b,
                       cx<R>* x, int n_mr, int K, long ld, hipStream_t st);
+// K spinor fields, lexicographic (stride ldl) <-> block layout (stride ldb)
+template <class L, class R>
+void launch_from_lex(const Geom& g, const cx<L>* lex, long ldl, cx<R>* out, long ldb, int K, hipStream_t st);
 template <class R>
-void launch_from_lex(const Geom& g, const cx<double>* lex, cx<R>* out, int ncomp, hipStream_t st);
-template <class R>
-void launch_to_lex(const Geom& g, const cx<R>* in, cx<double>* lex, int ncomp, hipStream_t st);
+void launch_to_lex(const Geom& g, const cx<R>* in, long ldb, cx<double>* lex, long ldl, int K, hipStream_t st);
 void set_sigma_table(const double* tab);
 void launch_clover(const Geom& g, const cx<double>* U, double csw, double diag, double* H, hipStream_t st);
 void launch_clover_from_lex(const Geom& g, const cx<double>* lex, double diag, double* H, hipStream_t st);

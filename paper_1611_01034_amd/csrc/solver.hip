@@ -752,25 +752,38 @@ void Ctx::dirac_lex(const cx<double>* in, cx<double>* out, int K, Twist tw, int 
   if (precision == DDAMG_FP16) launch_dirac_lex<float, f16>(g, U16.p, H32.as<float>(), tw, K, N, in, out, st);
   else launch_dirac_lex<float, bf16>(g, U16.p, H32.as<float>(), tw, K, N, in, out, st);
 }
-void Ctx::upload_fine(const void* src, int on_device, cx<double>* dst64) {
-  const cx<double>* s = (const cx<double>*)src;
-  if (!on_device) {
-    lex.ensure(sizeof(cx<double>) * fine_len());
-    HIP_CHECK(hipMemcpyAsync(lex.p, src, sizeof(cx<double>) * fine_len(), hipMemcpyHostToDevice, st));
-    s = lex.as<cx<double>>();
-  }
-  launch_from_lex<double>(g, s, dst64, 12, st);
-}
-void Ctx::download_fine(const cx<double>* src64, void* dst, int on_device) {
+template <class R>
+void Ctx::upload_fields(const void* src, int on_device, cx<R>* dst, int K) {
+  const long N = fine_len();
   if (on_device) {
-    launch_to_lex<double>(g, src64, (cx<double>*)dst, 12, st);
+    launch_from_lex<double, R>(g, (const cx<double>*)src, N, dst, N, K, st);
     return;
   }
-  lex.ensure(sizeof(cx<double>) * fine_len());
-  launch_to_lex<double>(g, src64, lex.as<cx<double>>(), 12, st);
-  HIP_CHECK(hipMemcpyAsync(dst, lex.p, sizeof(cx<double>) * fine_len(), hipMemcpyDeviceToHost, st));
-  HIP_CHECK(hipStreamSynchronize(st));
+  lex.ensure(sizeof(cx<double>) * N);
+  for (int k = 0; k < K; ++k) {
+    HIP_CHECK(hipMemcpyAsync(lex.p, (const cx<double>*)src + (long)k * N, sizeof(cx<double>) * N,
+                             hipMemcpyHostToDevice, st));
+    launch_from_lex<double, R>(g, lex.as<cx<double>>(), N, dst + (long)k * N, N, 1, st);
+  }
 }
+template <class R>
+void Ctx::download_fields(const cx<R>* src, void* dst, int on_device, int K) {
+  const long N = fine_len();
+  if (on_device) {
+    launch_to_lex<R>(g, src, N, (cx<double>*)dst, N, K, st);
+    return;
+  }
+  lex.ensure(sizeof(cx<double>) * N);
+  for (int k = 0; k < K; ++k) {
+    launch_to_lex<R>(g, src + (long)k * N, N, lex.as<cx<double>>(), N, 1, st);
+    HIP_CHECK(hipMemcpyAsync((cx<double>*)dst + (long)k * N, lex.p, sizeof(cx<double>) * N, hipMemcpyDeviceToHost, st));
+    HIP_CHECK(hipStreamSynchronize(st));
+  }
+}
+template void Ctx::upload_fields<double>(const void*, int, cx<double>*, int);
+template void Ctx::upload_fields<float>(const void*, int, cx<float>*, int);
+template void Ctx::download_fields<double>(const cx<double>*, void*, int, int);
+template void Ctx::download_fields<float>(const cx<float>*, void*, int, int);
 
 // ---------------------------------------------------------------------------
 static void lex_coords(const int L[4], int s, int x[4]) {

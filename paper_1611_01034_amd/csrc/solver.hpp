@@ -334,9 +334,13 @@ struct Ctx {
   // D(tw) on K lexicographic complex128 fields on the device, arithmetic and
   // link storage of `precision`; in and out must not overlap
   void dirac_lex(const cx<double>* in, cx<double>* out, int K, Twist tw, int precision);
-  // host/device lex FP64 field -> block layout
-  void upload_fine(const void* src, int on_device, cx<double>* dst64);
-  void download_fine(const cx<double>* src64, void* dst, int on_device);
+  // K host/device lex FP64 fields <-> block layout fields in R, both contiguous
+  template <class R>
+  void upload_fields(const void* src, int on_device, cx<R>* dst, int K);
+  template <class R>
+  void download_fields(const cx<R>* src, void* dst, int on_device, int K);
+  void upload_fine(const void* src, int on_device, cx<double>* dst64) { upload_fields(src, on_device, dst64, 1); }
+  void download_fine(const cx<double>* src64, void* dst, int on_device) { download_fields(src64, dst, on_device, 1); }
 };
 
 // whether two buffers of n bytes share a byte

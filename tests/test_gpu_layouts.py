@@ -128,3 +128,37 @@ def test_new_field_on_ragged_blocks(dd, dims, block):
         assert np.linalg.norm(got.reshape(want.shape) - want) <= 1e-11 * np.linalg.norm(want)
     finally:
         ctx.close()
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "bf16"])
+@pytest.mark.parametrize("dims,block", [((4, 4, 4, 4), (2, 2, 2, 2)), ((4, 12, 4, 12), (2, 6, 2, 6)),
+                                        ((8, 4, 12, 8), (4, 2, 6, 4))])
+def test_layout_conversions_of_several_fields(dd, dims, block, prec):
+    """Device fields (all of them converted by one launch) against host fields
+    (one at a time): zero SAP iterations give x back, rounded once to the
+    arithmetic; two iterations the same bits; FP64 within 1e-11 of the oracle."""
+    import ctypes
+    from oracle import sap, stencil
+    from paper_1611_01034_amd import synth
+    ctx, U, op = _case(dd, dims, block, 8401)
+    try:
+        print(f"layout conversions: {dims} {block} {prec}", flush=True)
+        K = 3
+        b, x0 = synth.spinor(dims, 8402, nvec=K), synth.spinor(dims, 8403, nvec=K)
+        db = torch.from_numpy(b).cuda()
+        for iters in (0, 2):
+            x = torch.from_numpy(x0).cuda()
+            ctx._check(dd._lib.ddamg_sap_multi(ctx._h, K, ctypes.c_void_p(db.data_ptr()),
+                                               ctypes.c_void_p(x.data_ptr()), iters, 3, dd.PRECISIONS[prec], 1))
+            host = ctx.sap_multi(b, x0, iters, 3, prec)
+            assert np.array_equal(x.cpu().numpy(), host)
+            if iters == 0:
+                want = x0 if prec == "fp64" else x0.astype(np.complex64).astype(np.complex128)
+                assert np.array_equal(host, want)
+            elif prec == "fp64":
+                fl = stencil.FineLevel(op)
+                for k in range(K):
+                    want = sap.sap(fl, b[k].reshape(dims + (12,)), x0[k].reshape(dims + (12,)), block, 3, 2)
+                    assert np.linalg.norm(host[k].reshape(want.shape) - want) <= 1e-11 * np.linalg.norm(want)
+    finally:
+        ctx.close()
