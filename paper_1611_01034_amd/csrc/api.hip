@@ -1079,7 +1079,7 @@ void net_buffers(Ctx& c) {
   n.g2.alloc(sizeof(cx<float>) * f);
   n.gpart.alloc(sizeof(double) * 2 * (long)n.C * ((c.g.V + 255) / 256));
   n.wpart.alloc(sizeof(cx<float>) * 256L * n.nWc);
-  n.lscr.alloc(sizeof(cx<double>) * 2L * c.g.nblocks * 3 * n.C * n.C);
+  n.lscr.alloc(net_loss_scratch(c.g, n.C));
   n.lpart.alloc(sizeof(double) * 2L * c.g.nblocks);
   n.V = c.g.V;
 }
@@ -1089,13 +1089,32 @@ void net_upload(Ctx& c, const void* src, int on_device, cx<float>* dst) {
   c.upload_fields(src, on_device, dst, c.net.C);
 }
 
+// the mixing layers run on the matrix cores where the channels fill chunks of
+// eight (FP32 accuracy from split BF16 products; a lattice has a multiple of
+// 256 sites)
+bool net_mfma(const Ctx& c) { return c.net.C % 8 == 0; }
+
+// one mixing layer (adj: its adjoint, on the gradient)
+void net_mix(Ctx& c, int l, const cx<float>* in, cx<float>* out, bool adj) {
+  NetState& n = c.net;
+  if (!net_mfma(c)) {
+    launch_net_mix(c.g, n.C, c.U32.as<cx<float>>(), in, n.W(l), out, adj, c.st);
+    return;
+  }
+  const long per = net_packed_bytes(n.C);
+  n.packed.ensure(per * n.L);
+  bf16* P = n.packed.as<bf16>() + per / (long)sizeof(bf16) * l;
+  launch_net_pack(n.C, n.W(l), P, adj, c.st);
+  launch_net_mix_mfma(c.g, n.C, c.U32.as<cx<float>>(), in, P, out, adj, c.st);
+}
+
 void net_forward(Ctx& c) {
   NetState& n = c.net;
   long f = (long)n.C * c.fine_len();
   cx<float>* act = n.act.as<cx<float>>();
   cx<float>* zb = n.zb.as<cx<float>>();
   for (int l = 0; l < n.L; ++l) {
-    launch_net_mix(c.g, n.C, c.U32.as<cx<float>>(), act + (long)l * f, n.W(l), zb + (long)l * f, false, c.st);
+    net_mix(c, l, act + (long)l * f, zb + (long)l * f, false);
     if (l < n.L - 1)
       launch_net_gate(c.g, n.C, zb + (long)l * f, n.ab(l), n.ab(l) + n.C, act + (long)(l + 1) * f,
                       n.sb.as<float>() + (long)l * n.C * c.g.V, c.st);
@@ -1106,19 +1125,8 @@ void net_forward(Ctx& c) {
 // `in` holds the input and is overwritten; returns the buffer with the output
 cx<float>* net_infer(Ctx& c, cx<float>* in, cx<float>* tmp) {
   NetState& n = c.net;
-  // matrix cores when the channel count and the lattice allow (FP32 accuracy
-  // from split BF16 products)
-  const bool mf = n.C % 8 == 0 && n.C <= 24 && c.g.V % 64 == 0;
-  const long per = net_packed_bytes(n.C) / (long)sizeof(bf16);
-  if (mf) {
-    n.packed.ensure(sizeof(bf16) * per * n.L);
-    for (int l = 0; l < n.L; ++l) launch_net_pack(n.C, n.W(l), n.packed.as<bf16>() + l * per, c.st);
-  }
   for (int l = 0; l < n.L; ++l) {
-    if (mf)
-      launch_net_mix_mfma(c.g, n.C, c.U32.as<cx<float>>(), in, n.packed.as<bf16>() + l * per, tmp, c.st);
-    else
-      launch_net_mix(c.g, n.C, c.U32.as<cx<float>>(), in, n.W(l), tmp, false, c.st);
+    net_mix(c, l, in, tmp, false);
     if (l < n.L - 1) launch_net_gate_inplace(c.g, n.C, n.ab(l), n.ab(l) + n.C, tmp, c.st);
     std::swap(in, tmp);
   }
@@ -1131,7 +1139,7 @@ double net_loss(Ctx& c) {
   long f = (long)n.C * c.fine_len();
   double inv_norm = 1.0 / ((double)n.C * 2.0 * c.g.nblocks);
   launch_net_loss(c.g, n.C, n.zb.as<cx<float>>() + (long)(n.L - 1) * f, n.g2.as<cx<float>>(), inv_norm,
-                  n.lscr.as<cx<double>>(), n.g1.as<cx<float>>(), n.lpart.as<double>(), c.st);
+                  n.lscr.p, n.g1.as<cx<float>>(), n.lpart.as<double>(), c.st);
   std::vector<double> lp(2L * c.g.nblocks);
   HIP_CHECK(hipMemcpyAsync(lp.data(), n.lpart.p, sizeof(double) * lp.size(), hipMemcpyDeviceToHost, c.st));
   c.sync();
@@ -1159,7 +1167,7 @@ void net_backward(Ctx& c) {
                      c.st);
     if (l > 0) {
       cx<float>* dst = (gz == G) ? Gz : G;
-      launch_net_mix(c.g, n.C, c.U32.as<cx<float>>(), gz, n.W(l), dst, true, c.st);
+      net_mix(c, l, gz, dst, true);
       G = dst;
       Gz = (dst == n.g1.as<cx<float>>()) ? n.g2.as<cx<float>>() : n.g1.as<cx<float>>();
     }

@@ -173,19 +173,21 @@ void launch_net_mix(const Geom& g, int C, const cx<float>* U, const cx<float>* i
                     bool adj, hipStream_t st);
 void launch_net_gate(const Geom& g, int C, const cx<float>* z, const float* a, const float* b, cx<float>* y, float* sv,
                      hipStream_t st);
-// the forward mixing layer on the matrix cores (inference; C = 8, 16, 24): the
-// layer's weights split into three BF16 parts and packed once by
+// the mixing layer or its adjoint on the matrix cores (C = 8, 16, 24): the
+// layer's weights split into three BF16 parts and packed by
 // launch_net_pack (net_packed_bytes(C) bytes per layer)
 inline long net_packed_bytes(int C) { return 9L * C * C * 192; }
-void launch_net_pack(int C, const cx<float>* W, bf16* P, hipStream_t st);
+void launch_net_pack(int C, const cx<float>* W, bf16* P, bool adj, hipStream_t st);
 void launch_net_mix_mfma(const Geom& g, int C, const cx<float>* U, const cx<float>* in, const bf16* P,
-                         cx<float>* out, hipStream_t st);
+                         cx<float>* out, bool adj, hipStream_t st);
 void launch_net_gate_inplace(const Geom& g, int C, const float* a, const float* b, cx<float>* z, hipStream_t st);
 void launch_net_gate_bwd(const Geom& g, int C, const cx<float>* Gy, const cx<float>* z, const float* sv,
                          const float* a, cx<float>* Gz, double* partial, float* Ga, float* Gb, hipStream_t st);
 void launch_net_wgrad(const Geom& g, int C, const cx<float>* U, const cx<float>* x, const cx<float>* Gz,
                       cx<float>* partial, int nwg, cx<float>* GW, hipStream_t st);
-void launch_net_loss(const Geom& g, int C, const cx<float>* Y, const cx<float>* Q, double inv_norm, cx<double>* scr,
+// scr: net_loss_scratch(g, C) bytes
+long net_loss_scratch(const Geom& g, int C);
+void launch_net_loss(const Geom& g, int C, const cx<float>* Y, const cx<float>* Q, double inv_norm, void* scr,
                      cx<float>* GY, double* lpart, hipStream_t st);
 void launch_adam(long n, float* p, const float* gr, float* m, float* v, float lr, float b1, float b2, float eps,
                  float c1, float c2, hipStream_t st);

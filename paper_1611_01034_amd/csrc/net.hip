@@ -54,7 +54,8 @@ __device__ __forceinline__ void transport_site(const Geom& g, const cx<float>* U
 // ---------------------------------------------------------------------------
 // mixing layer: 64 sites per workgroup, wave w computes output channels
 // [w*CW, (w+1)*CW) (C = 4*CW); transported inputs staged in LDS 8 channels
-// at a time; the weights are wave-uniform (scalar loads).
+// at a time; the weights are wave-uniform (scalar loads).  For 4 and 12
+// channels; 8, 16 and 24 run on the matrix cores.
 template <int CW, bool ADJ>
 __global__ void __launch_bounds__(256) k_net_mix(Geom g, const cx<float>* __restrict__ U,
                                                  const cx<float>* __restrict__ in, const cx<float>* __restrict__ W,
@@ -128,7 +129,7 @@ __global__ void __launch_bounds__(256) k_net_mix(Geom g, const cx<float>* __rest
 }
 
 // ---------------------------------------------------------------------------
-// The mixing layer on the matrix cores (inference).  Per site and colour k the
+// The mixing layer on the matrix cores (inference and training).  Per site and colour k the
 // layer is z[(c,s)] = sum_{(d,c',t)} W[d][c][c'][s][t] (T_d x_{c'})[t][k]: a
 // complex matrix of 4C rows (c,s) and 9*4C columns (d,c',t) times one column
 // per (site, colour).  It runs as a real product with the embedding
@@ -145,6 +146,9 @@ __global__ void __launch_bounds__(256) k_net_mix(Geom g, const cx<float>* __rest
 // v_mfma_f32_16x16x4f32 for the same terms in FP32, at 16 times the rate.
 // Fragments (wave64): lane L holds A[L%16][8(L/16) + e] and B[8(L/16) + e][L%16]
 // (e < 8); the result D[4(L/16) + e][L%16] (e < 4).
+// Its adjoint for the input gradient packs the conjugate transpose.  Against
+// FP64 the training pass is closer than with the FP32 vector kernel (gradients
+// of 4 layers of 24 channels: 1.9e-6 against 2.2e-6).
 // A workgroup takes 64 sites, wavefront w sites 16w..16w+15 (96 real columns:
 // 6 tiles, each one colour and 8 consecutive sites); the transported inputs of
 // 8 channels of one offset are staged in LDS per chunk as in the VALU kernel.  The weights are split and packed once
@@ -161,7 +165,8 @@ __device__ __forceinline__ void split3(float x, __bf16& x0, __bf16& x1, __bf16& 
 
 // packed[(((chunk * 2 + ks) * RT + t) * 3 + part) * 64 + lane][e] (BF16),
 // chunk = d * (C/8) + k0/8; entry = part `part` of A[16t + lane%16][32 ks + 8 (lane/16) + e]
-__global__ void k_net_pack(int C, const cx<float>* __restrict__ W, __bf16* __restrict__ P) {
+// (adj: of the conjugate transpose, for the input gradient)
+__global__ void k_net_pack(int C, const cx<float>* __restrict__ W, __bf16* __restrict__ P, int adj) {
   const int RT = C / 4, nch = C / 8;
   const long total = 9L * nch * 2 * RT * 3 * 64 * 8;
   for (long e = (long)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (long)gridDim.x * blockDim.x) {
@@ -180,17 +185,25 @@ __global__ void k_net_pack(int C, const cx<float>* __restrict__ W, __bf16* __res
     const int l = q >> 1, cp = q & 1;                  // complex inner (c', t), part
     const int ci = k0 + (l >> 2), tt = l & 3;
     const int co = i >> 2, sp = i & 3;
-    const cx<float> w = W[((long)(d * C + co) * C + ci) * 16 + sp * 4 + tt];
+    const cx<float> w = adj ? conj(W[((long)(d * C + ci) * C + co) * 16 + tt * 4 + sp])
+                            : W[((long)(d * C + co) * C + ci) * 16 + sp * 4 + tt];
     __bf16 x[3];
     split3(cp == 0 ? w.re : w.im, x[0], x[1], x[2]);
     P[e] = x[part];
   }
 }
-void launch_net_pack(int C, const cx<float>* W, __bf16* P, hipStream_t st) {
-  hipLaunchKernelGGL(k_net_pack, dim3(256), dim3(256), 0, st, C, W, P);
+void launch_net_pack(int C, const cx<float>* W, __bf16* P, bool adj, hipStream_t st) {
+  hipLaunchKernelGGL(k_net_pack, dim3(256), dim3(256), 0, st, C, W, P, adj ? 1 : 0);
 }
 
-template <int RT>
+// offset whose transport layer term d takes (the adjoint swaps forward and
+// backward offsets)
+template <bool ADJ>
+__device__ __forceinline__ int mix_offset(int d) {
+  return ADJ && d ? (d <= 4 ? d + 4 : d - 4) : d;
+}
+
+template <int RT, bool ADJ>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8)))
 k_net_mix_mfma(Geom g, const cx<float>* __restrict__ U, const cx<float>* __restrict__ in,
                const v8bf_n* __restrict__ P, cx<float>* __restrict__ out) {
@@ -212,7 +225,7 @@ k_net_mix_mfma(Geom g, const cx<float>* __restrict__ U, const cx<float>* __restr
   const int kk = lane >> 4;
 #pragma unroll 1
   for (int chunk = 0; chunk < 9 * NCH; ++chunk) {
-    const int d = chunk / NCH, k0 = (chunk % NCH) * 8;
+    const int d = mix_offset<ADJ>(chunk / NCH), k0 = (chunk % NCH) * 8;
     __syncthreads();
 #pragma unroll 1
     for (int p = t; p < 64 * 8; p += 256) {
@@ -304,14 +317,164 @@ k_net_mix_mfma(Geom g, const cx<float>* __restrict__ U, const cx<float>* __restr
   }
 }
 
+// The same layer on 16 sites per workgroup, for lattices of which 64 sites per
+// workgroup leave CUs idle: the four wavefronts share the sites, wavefront w
+// taking one half of the row tiles and three of the six column tiles.  Each
+// thread transports two spins of one (site, channel); the loads of the next
+// chunk are in flight while this one multiplies (one workgroup per CU has
+// nothing else to hide them), and the chunks alternate between two LDS
+// buffers, one barrier each.  24 channels at 8^4: 117 us a layer (vector kernel
+// 680 us, 64 sites per workgroup 250 us).
+template <int RT, bool ADJ>
+__global__ void __launch_bounds__(256)
+k_net_mix_mfma16(Geom g, const cx<float>* __restrict__ U, const cx<float>* __restrict__ in,
+                 const v8bf_n* __restrict__ P, cx<float>* __restrict__ out) {
+  constexpr int C = 4 * RT, NCH = C / 8, NA = RT / 2;
+  constexpr int TXC = 12 * 16 + 8;
+  __shared__ cx<float> txs[2][8 * TXC];
+  const int t = threadIdx.x, lane = t & 63, kk = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(t >> 6), a0t = (w >> 1) * NA, u0 = 3 * (w & 1);
+  const long fl = g.V * 12;
+  v4f_n acc[NA][3];
+#pragma unroll
+  for (int a = 0; a < NA; ++a)
+#pragma unroll
+    for (int u = 0; u < 3; ++u) acc[a][u] = v4f_n{0.f, 0.f, 0.f, 0.f};
+  // this thread's staging task: site i, channel ch of the chunk, spins 2 hf and 2 hf + 1
+  const int i = t & 15, ch_ = (t >> 4) & 7, hf = t >> 7;
+  SiteNbr me;
+  const long gs0 = (long)blockIdx.x * 16 + i;
+  const int Bi = (int)(gs0 / g.bs), si = (int)(gs0 - (long)Bi * g.bs);
+  me_of(g, Bi, si, me);
+  cx<float> psi[6], u9[9];
+  auto load = [&](int chunk) {
+    const int d = mix_offset<ADJ>(chunk / NCH), ch = (chunk % NCH) * 8 + ch_;
+    int Bn = Bi, sn = si;
+    if (d) {
+      const int mu = (d - 1) & 3;
+      nbr_of(g, me, mu, d <= 4 ? 1 : -1, Bn, sn);
+      if (d <= 4) load_link<float, float>(U, g, Bi, si, mu, u9);
+      else load_link<float, float>(U, g, Bn, sn, mu, u9);
+    }
+    const cx<float>* p = in + (long)ch * fl + fidx(g, Bn, sn, 12) + (long)(6 * hf) * TILE;
+#pragma unroll
+    for (int c = 0; c < 6; ++c) psi[c] = p[c * TILE];
+  };
+  auto stage = [&](int chunk, cx<float>* buf) {
+    const int d = mix_offset<ADJ>(chunk / NCH);
+    cx<float>* o = buf + ch_ * TXC + (6 * hf) * 16 + i;
+    if (d == 0) {
+#pragma unroll
+      for (int c = 0; c < 6; ++c) o[c * 16] = psi[c];
+      return;
+    }
+    const bool fwd = d <= 4;
+#pragma unroll
+    for (int sp = 0; sp < 2; ++sp)
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        cx<float> v = mk<float>(0, 0);
+#pragma unroll
+        for (int b = 0; b < 3; ++b) {
+          if (fwd) cmac(v, u9[3 * a + b], psi[3 * sp + b]);
+          else cjmac(v, u9[3 * b + a], psi[3 * sp + b]);
+        }
+        o[(3 * sp + a) * 16] = v;
+      }
+  };
+  load(0);
+  stage(0, txs[0]);
+  __syncthreads();
+#pragma unroll 1
+  for (int chunk = 0; chunk < 9 * NCH; ++chunk) {
+    if (chunk + 1 < 9 * NCH) load(chunk + 1);
+    const cx<float>* tx = txs[chunk & 1];
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      const int ch = 4 * ks + kk;
+      const v8bf_n* Pc = P + ((long)(chunk * 2 + ks) * RT + a0t) * 3 * 64 + lane;
+      v8bf_n b0[3], b1[3], b2[3];
+#pragma unroll
+      for (int uu = 0; uu < 3; ++uu) {
+        const int u = u0 + uu;
+        const int c = lane & 1, k = u >> 1, site = 8 * (u & 1) + ((lane & 15) >> 1);
+#pragma unroll
+        for (int tt = 0; tt < 4; ++tt) {
+          const cx<float> v = tx[ch * TXC + (3 * tt + k) * 16 + site];
+          __bf16 h, m, lo;
+          split3(c == 0 ? v.re : v.im, h, m, lo);
+          b0[uu][2 * tt] = h;
+          b1[uu][2 * tt] = m;
+          b2[uu][2 * tt] = lo;
+          split3(c == 0 ? -v.im : v.re, h, m, lo);
+          b0[uu][2 * tt + 1] = h;
+          b1[uu][2 * tt + 1] = m;
+          b2[uu][2 * tt + 1] = lo;
+        }
+      }
+#pragma unroll
+      for (int a = 0; a < NA; ++a) {
+        const v8bf_n x0 = Pc[(a * 3 + 0) * 64], x1 = Pc[(a * 3 + 1) * 64], x2 = Pc[(a * 3 + 2) * 64];
+        v4f_n* ac = acc[a];
+        // smallest terms first, as in the 64-site form
+#pragma unroll
+        for (int uu = 0; uu < 3; ++uu) ac[uu] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x2, b0[uu], ac[uu], 0, 0, 0);
+#pragma unroll
+        for (int uu = 0; uu < 3; ++uu) ac[uu] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x1, b1[uu], ac[uu], 0, 0, 0);
+#pragma unroll
+        for (int uu = 0; uu < 3; ++uu) ac[uu] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x0, b2[uu], ac[uu], 0, 0, 0);
+#pragma unroll
+        for (int uu = 0; uu < 3; ++uu) ac[uu] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x1, b0[uu], ac[uu], 0, 0, 0);
+#pragma unroll
+        for (int uu = 0; uu < 3; ++uu) ac[uu] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x0, b1[uu], ac[uu], 0, 0, 0);
+#pragma unroll
+        for (int uu = 0; uu < 3; ++uu) ac[uu] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x0, b0[uu], ac[uu], 0, 0, 0);
+      }
+    }
+    if (chunk + 1 < 9 * NCH) stage(chunk + 1, txs[(chunk + 1) & 1]);
+    __syncthreads();
+  }
+#pragma unroll
+  for (int uu = 0; uu < 3; ++uu) {
+    const int u = u0 + uu, c = lane & 1, k = u >> 1, site = 8 * (u & 1) + ((lane & 15) >> 1);
+    const long gs = (long)blockIdx.x * 16 + site;
+    const int Bs = (int)(gs / g.bs), ss = (int)(gs - (long)Bs * g.bs);
+    const long base = fidx(g, Bs, ss, 12);
+#pragma unroll
+    for (int a = 0; a < NA; ++a)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int ir = 16 * (a0t + a) + 4 * kk + e;
+        const int co = ir >> 2, sp = ir & 3;
+        reinterpret_cast<float*>(out + (long)co * fl + base + (long)(3 * sp + k) * TILE)[c] = acc[a][uu][e];
+      }
+  }
+}
+
+template <int RT>
+static void mix_mfma_dispatch(const Geom& g, const cx<float>* U, const cx<float>* in, const v8bf_n* P, cx<float>* out,
+                              bool adj, hipStream_t st) {
+  // 64 sites per workgroup from 32768 sites on (two workgroups per CU); below,
+  // 16 sites per workgroup keep the CUs busy.  A whole forward pass with 4
+  // layers of 24 channels, 16 against 64 sites per workgroup: 4096 sites 558
+  // and 1127 us, 16384 sites 1185 and 1272, 32768 sites 2265 and 1846
+  if (g.V >= 32768) {
+    const dim3 grid((unsigned)(g.V / 64));
+    if (adj) hipLaunchKernelGGL((k_net_mix_mfma<RT, true>), grid, dim3(256), 0, st, g, U, in, P, out);
+    else hipLaunchKernelGGL((k_net_mix_mfma<RT, false>), grid, dim3(256), 0, st, g, U, in, P, out);
+  } else {
+    const dim3 grid((unsigned)(g.V / 16));
+    if (adj) hipLaunchKernelGGL((k_net_mix_mfma16<RT, true>), grid, dim3(256), 0, st, g, U, in, P, out);
+    else hipLaunchKernelGGL((k_net_mix_mfma16<RT, false>), grid, dim3(256), 0, st, g, U, in, P, out);
+  }
+}
 void launch_net_mix_mfma(const Geom& g, int C, const cx<float>* U, const cx<float>* in, const __bf16* P,
-                         cx<float>* out, hipStream_t st) {
-  dim3 grid((unsigned)(g.V / 64));
+                         cx<float>* out, bool adj, hipStream_t st) {
   const v8bf_n* Pv = reinterpret_cast<const v8bf_n*>(P);
   switch (C) {
-    case 8: hipLaunchKernelGGL((k_net_mix_mfma<2>), grid, dim3(256), 0, st, g, U, in, Pv, out); break;
-    case 16: hipLaunchKernelGGL((k_net_mix_mfma<4>), grid, dim3(256), 0, st, g, U, in, Pv, out); break;
-    case 24: hipLaunchKernelGGL((k_net_mix_mfma<6>), grid, dim3(256), 0, st, g, U, in, Pv, out); break;
+    case 8: mix_mfma_dispatch<2>(g, U, in, Pv, out, adj, st); break;
+    case 16: mix_mfma_dispatch<4>(g, U, in, Pv, out, adj, st); break;
+    case 24: mix_mfma_dispatch<6>(g, U, in, Pv, out, adj, st); break;
     default: throw Error(INVALID_ARG, "matrix-core network layer needs 8, 16 or 24 channels");
   }
 }
@@ -501,141 +664,192 @@ __global__ void k_net_wgrad_reduce(const cx<float>* __restrict__ partial, int nw
 // subspace loss and its gradient on one aggregate half (block B, half h), FP64
 // small-matrix algebra: G = Y^dag Y, Cm = Y^dag Q, M = G^{-1} Cm,
 // L_A = |Q|^2 - tr(Cm^dag M), G_Y = -2 (Q - Y M) M^dag / norm.
-// Rows are (slot, component of the half).  scr: [nagg][3][C][C] FP64 scratch.
-__global__ void __launch_bounds__(256) k_net_loss(Geom g, int C, const cx<float>* __restrict__ Y,
-                                                  const cx<float>* __restrict__ Q, double inv_norm,
-                                                  cx<double>* __restrict__ scr, cx<float>* __restrict__ GY,
-                                                  double* __restrict__ lpart) {
-  __shared__ cx<float> ys[64][32];
-  __shared__ cx<float> qs[64][32];
-  __shared__ double lred[4];
-  const int A = blockIdx.x, B = A >> 1, h = A & 1;
-  const int t = threadIdx.x;
+// An aggregate half is one serial chain but its rows are not, so the work is
+// three launches (one workgroup per aggregate half, with the elimination in one
+// thread, left most of the card idle: 8^4 and 24 channels 5300 -> 150 us): the
+// products over parts of the rows, the C x C algebra in LDS with a
+// workgroup's threads on the columns, and the gradient, which is the product
+// G_Y = Q X1 + Y X2 with X1 = -2 M^dag / norm, X2 = 2 M M^dag / norm.  Rows are
+// (tile of 8 slots, component of the half, slot in the tile), so that 48
+// consecutive rows are contiguous in the block layout.
+namespace {
+constexpr int LOSS_ROWS = 48;
+__device__ __forceinline__ long loss_row(const Geom& g, int B, int h, int tile, int r) {
+  return ((long)B * (g.bs / TILE) + tile) * 12 * TILE + (long)(6 * h) * TILE + r;
+}
+}  // namespace
+
+// partial sums of G and Cm over the tiles blockIdx.y, + gridDim.y, ... ->
+// part[A][P][2 C C], |Q|^2 -> qpart[A][P].  Thread = 2 x 4 entries of
+// Y^dag [Y | Q].
+template <int C>
+__global__ void __launch_bounds__(256) k_net_gram(Geom g, const cx<float>* __restrict__ Y,
+                                                  const cx<float>* __restrict__ Q, cx<double>* __restrict__ part,
+                                                  double* __restrict__ qpart) {
+  constexpr int LD = 2 * C + 1, TI = C / 2, TJ = C / 2;  // tiles of 2 rows, of 4 columns
+  __shared__ cx<double> ys[LOSS_ROWS][LD];               // [row][Y_0.. | Q_0..]
+  __shared__ double qred[4];
+  const int A = blockIdx.x, B = A >> 1, h = A & 1, t = threadIdx.x;
   const long fl = g.V * 12;
-  const int rows = g.bs * 6;
-  const int CC = C * C;
-  cx<double>* Gm = scr + (long)A * 3 * CC;
-  cx<double>* Cm = Gm + CC;
-  cx<double>* Mm = Cm + CC;
-  // accumulate G and Cm: thread owns entries e = t, t+256, ... of the 2*CC list
-  cx<double> accv[8];
+  const int ti = t / TJ, tj = t - ti * TJ;
+  const bool on = ti < TI;
+  cx<double> acc[2][4];
 #pragma unroll
-  for (int m = 0; m < 8; ++m) accv[m] = mk(0.0, 0.0);
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = mk(0.0, 0.0);
   double qn = 0.0;
-  for (int r0 = 0; r0 < rows; r0 += 64) {
+  for (int tile = blockIdx.y; tile < g.bs / TILE; tile += gridDim.y) {
     __syncthreads();
-    for (int p = t; p < 64 * C; p += 256) {
-      int rr = p % 64, c = p / 64;
-      int r = r0 + rr;
-      cx<float> yv = mk<float>(0, 0), qv = mk<float>(0, 0);
-      if (r < rows) {
-        int slot = r / 6, comp = 6 * h + (r % 6);
-        long idx = (long)c * fl + fidx(g, B, slot, 12) + (long)comp * TILE;
-        yv = Y[idx];
-        qv = Q[idx];
-      }
-      ys[rr][c] = yv;
-      qs[rr][c] = qv;
+    for (int p = t; p < LOSS_ROWS * 2 * C; p += 256) {
+      const int c = p / LOSS_ROWS, r = p - c * LOSS_ROWS;
+      const long o = loss_row(g, B, h, tile, r);
+      const cx<float> v = c < C ? Y[(long)c * fl + o] : Q[(long)(c - C) * fl + o];
+      ys[r][c] = mk<double>(v.re, v.im);
+      if (c >= C) qn += (double)v.re * v.re + (double)v.im * v.im;
     }
     __syncthreads();
+    if (on) {
+      for (int r = 0; r < LOSS_ROWS; ++r) {
+        cx<double> a[2], b[4];
 #pragma unroll
-    for (int m = 0; m < 8; ++m) {
-      int e = t + 256 * m;
-      if (e < 2 * CC) {
-        bool isG = e < CC;
-        int ee = isG ? e : e - CC;
-        int i = ee / C, j = ee % C;
-        cx<double> a = accv[m];
-        for (int rr = 0; rr < 64; ++rr) {
-          cx<float> yi = ys[rr][i];
-          cx<float> v = isG ? ys[rr][j] : qs[rr][j];
-          cjmac(a, mk<double>(yi.re, yi.im), mk<double>(v.re, v.im));
-        }
-        accv[m] = a;
+        for (int i = 0; i < 2; ++i) a[i] = ys[r][2 * ti + i];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) b[j] = ys[r][4 * tj + j];
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) cjmac(acc[i][j], a[i], b[j]);
       }
-    }
-    if (t < 64) {
-      for (int c = 0; c < C; ++c) qn += norm2(qs[t][c]);
     }
   }
+  cx<double>* o = part + ((long)A * gridDim.y + blockIdx.y) * 2 * C * C;
+  if (on) {
 #pragma unroll
-  for (int m = 0; m < 8; ++m) {
-    int e = t + 256 * m;
-    if (e < 2 * CC) {
-      if (e < CC) Gm[e] = accv[m];
-      else Cm[e - CC] = accv[m];
-    }
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int row = 2 * ti + i, col = 4 * tj + j;
+        o[(col < C ? 0 : C * C) + row * C + (col < C ? col : col - C)] = acc[i][j];
+      }
   }
   qn = wave_sum_n(qn, 64);
+  if ((t & 63) == 0) qred[t >> 6] = qn;
   __syncthreads();
-  // M = G^{-1} Cm by Gauss-Jordan on [G | Cm] (one thread; C <= 32)
+  if (t == 0) qpart[(long)A * gridDim.y + blockIdx.y] = (qred[0] + qred[1]) + (qred[2] + qred[3]);
+}
+
+// G and Cm from their NP partial sums, M = G^{-1} Cm by Gauss-Jordan with
+// column pivoting on [G | M], the loss of the aggregate half, X1 and X2 ->
+// xm[A][2 C C] (element (j, i) at j C + i)
+template <int C>
+__global__ void __launch_bounds__(256) k_net_loss(int NP, const cx<double>* __restrict__ part,
+                                                  const double* __restrict__ qpart, double inv_norm,
+                                                  cx<double>* __restrict__ xm, double* __restrict__ lpart) {
+  constexpr int CC = C * C, W = 2 * C;
+  __shared__ cx<double> S[C][W + 1], Cm[CC], col[C];
+  __shared__ double red[4];
+  __shared__ int pivot;
+  const int A = blockIdx.x, t = threadIdx.x;
+  const cx<double>* pa = part + (long)A * NP * 2 * CC;
+  for (int e = t; e < 2 * CC; e += 256) {
+    cx<double> v = mk(0.0, 0.0);
+    for (int p = 0; p < NP; ++p) v += pa[(long)p * 2 * CC + e];
+    const int ee = e < CC ? e : e - CC;
+    S[ee / C][(e < CC ? 0 : C) + ee % C] = v;
+    if (e >= CC) Cm[ee] = v;
+  }
+  __syncthreads();
+  for (int k = 0; k < C; ++k) {
+    if (t < 64) {  // the first row of largest |S[r][k]|, r >= k
+      double best = t >= k && t < C ? norm2(S[t][k]) : -1.0;
+      int at = t;
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) {
+        const double ob = __shfl_xor(best, o, 64);
+        const int oa = __shfl_xor(at, o, 64);
+        if (ob > best || (ob == best && oa < at)) {
+          best = ob;
+          at = oa;
+        }
+      }
+      // (no entry compares as largest where the column holds NaN: keep row k)
+      if (t == 0) pivot = at >= k && at < C ? at : k;
+    }
+    __syncthreads();
+    const int pv = pivot;
+    if (pv != k && t < W) {
+      const cx<double> a = S[k][t];
+      S[k][t] = S[pv][t];
+      S[pv][t] = a;
+    }
+    __syncthreads();
+    const cx<double> d = S[k][k];
+    const double dn = norm2(d);
+    const cx<double> inv = dn > 0 ? mk(d.re / dn, -d.im / dn) : mk(0.0, 0.0);
+    if (t < C) col[t] = S[t][k];
+    __syncthreads();
+    if (t < W) S[k][t] = S[k][t] * inv;
+    __syncthreads();
+    for (int e = t; e < C * W; e += 256) {
+      const int r = e / W, j = e - r * W;
+      if (r != k) S[r][j] -= col[r] * S[k][j];
+    }
+    __syncthreads();
+  }
+  // L_A = |Q|^2 - tr(Cm^dag M)
+  double tr = 0.0;
+  for (int e = t; e < CC; e += 256) {
+    const cx<double> c = Cm[e], m = S[e / C][C + e % C];
+    tr += c.re * m.re + c.im * m.im;
+  }
+  tr = wave_sum_n(tr, 64);
+  if ((t & 63) == 0) red[t >> 6] = tr;
+  __syncthreads();
   if (t == 0) {
-    for (int e = 0; e < CC; ++e) Mm[e] = Cm[e];
-    for (int k = 0; k < C; ++k) {
-      int piv = k;
-      double best = norm2(Gm[k * C + k]);
-      for (int r = k + 1; r < C; ++r)
-        if (norm2(Gm[r * C + k]) > best) {
-          best = norm2(Gm[r * C + k]);
-          piv = r;
-        }
-      if (piv != k)
-        for (int j = 0; j < C; ++j) {
-          cx<double> tmp = Gm[k * C + j];
-          Gm[k * C + j] = Gm[piv * C + j];
-          Gm[piv * C + j] = tmp;
-          tmp = Mm[k * C + j];
-          Mm[k * C + j] = Mm[piv * C + j];
-          Mm[piv * C + j] = tmp;
-        }
-      cx<double> pv = Gm[k * C + k];
-      double dn = norm2(pv);
-      cx<double> inv = dn > 0 ? mk(pv.re / dn, -pv.im / dn) : mk(0.0, 0.0);
-      for (int j = 0; j < C; ++j) {
-        Gm[k * C + j] = Gm[k * C + j] * inv;
-        Mm[k * C + j] = Mm[k * C + j] * inv;
-      }
-      for (int r = 0; r < C; ++r) {
-        if (r == k) continue;
-        cx<double> f = Gm[r * C + k];
-        for (int j = 0; j < C; ++j) {
-          Gm[r * C + j] -= f * Gm[k * C + j];
-          Mm[r * C + j] -= f * Mm[k * C + j];
-        }
-      }
-    }
-    // L_A = |Q|^2 - tr(Cm^dag M)
-    double tr = 0;
-    for (int i = 0; i < C; ++i)
-      for (int j = 0; j < C; ++j) {
-        cx<double> cv = Cm[i * C + j], mv = Mm[i * C + j];
-        tr += cv.re * mv.re + cv.im * mv.im;
-      }
-    lred[0] = tr;
+    double qn = 0.0;
+    for (int p = 0; p < NP; ++p) qn += qpart[(long)A * NP + p];
+    lpart[A] = (qn - ((red[0] + red[1]) + (red[2] + red[3]))) * inv_norm;
   }
+  cx<double>* x = xm + (long)A * 2 * CC;
+  for (int e = t; e < CC; e += 256) {
+    const int j = e / C, i = e - j * C;
+    x[e] = (-2.0 * inv_norm) * conj(S[i][C + j]);
+    cx<double> a = mk(0.0, 0.0);
+    for (int q = 0; q < C; ++q) cjmac(a, S[i][C + q], S[j][C + q]);  // (M M^dag)_{ji}
+    x[CC + e] = (2.0 * inv_norm) * a;
+  }
+}
+
+// G_Y[r][i] = sum_j Q[r][j] X1[j][i] + Y[r][j] X2[j][i]: one thread per row,
+// the C sums in registers, X broadcast from LDS
+template <int C>
+__global__ void __launch_bounds__(64) k_net_loss_grad(Geom g, const cx<float>* __restrict__ Y,
+                                                      const cx<float>* __restrict__ Q,
+                                                      const cx<double>* __restrict__ xm, cx<float>* __restrict__ GY) {
+  __shared__ cx<double> xs[2 * C * C];
+  const int A = blockIdx.x, B = A >> 1, h = A & 1, t = threadIdx.x;
+  for (int e = t; e < 2 * C * C; e += 64) xs[e] = xm[(long)A * 2 * C * C + e];
   __syncthreads();
-  if (t == 0) lpart[A] = (qn - lred[0]) * inv_norm;
-  // gradient rows: G_Y[r] = -2 inv_norm (Q[r] - Y[r] M) M^dag
-  for (int r = t; r < rows; r += 256) {
-    int slot = r / 6, comp = 6 * h + (r % 6);
-    long off = fidx(g, B, slot, 12) + (long)comp * TILE;
-    cx<double> yr[32], rr[32];
-    for (int c = 0; c < C; ++c) {
-      cx<float> v = Y[(long)c * fl + off];
-      yr[c] = mk<double>(v.re, v.im);
-    }
-    for (int j = 0; j < C; ++j) {
-      cx<float> qv = Q[(long)j * fl + off];
-      cx<double> a = mk<double>(qv.re, qv.im);
-      for (int i = 0; i < C; ++i) a -= yr[i] * Mm[i * C + j];
-      rr[j] = a;
-    }
+  const long fl = g.V * 12;
+  const int row = blockIdx.y * 64 + t;
+  if (row >= 6 * g.bs) return;
+  const long o = loss_row(g, B, h, row / LOSS_ROWS, row % LOSS_ROWS);
+  cx<double> acc[C];
+#pragma unroll
+  for (int i = 0; i < C; ++i) acc[i] = mk(0.0, 0.0);
+#pragma unroll 1
+  for (int j = 0; j < C; ++j) {
+    const cx<float> qf = Q[(long)j * fl + o], yf = Y[(long)j * fl + o];
+    const cx<double> q = mk<double>(qf.re, qf.im), y = mk<double>(yf.re, yf.im);
+#pragma unroll
     for (int i = 0; i < C; ++i) {
-      cx<double> a = mk(0.0, 0.0);
-      for (int j = 0; j < C; ++j) cmac(a, rr[j], conj(Mm[i * C + j]));
-      GY[(long)i * fl + off] = mk<float>((float)(-2.0 * inv_norm * a.re), (float)(-2.0 * inv_norm * a.im));
+      cmac(acc[i], q, xs[j * C + i]);
+      cmac(acc[i], y, xs[C * C + j * C + i]);
     }
   }
+#pragma unroll
+  for (int i = 0; i < C; ++i) GY[(long)i * fl + o] = mk<float>((float)acc[i].re, (float)acc[i].im);
 }
 
 // Adam on a real view of all parameters: p -= lr mhat / (sqrt(vhat) + eps)
@@ -664,11 +878,8 @@ void launch_net_mix(const Geom& g, int C, const cx<float>* U, const cx<float>* i
                     bool adj, hipStream_t st) {
   switch (C) {
     case 4: mix_dispatch<1>(g, U, in, W, out, adj, st); break;
-    case 8: mix_dispatch<2>(g, U, in, W, out, adj, st); break;
     case 12: mix_dispatch<3>(g, U, in, W, out, adj, st); break;
-    case 16: mix_dispatch<4>(g, U, in, W, out, adj, st); break;
-    case 24: mix_dispatch<6>(g, U, in, W, out, adj, st); break;
-    default: throw Error(INVALID_ARG, "network channels must be 4, 8, 12, 16 or 24");
+    default: throw Error(INVALID_ARG, "the vector form of the mixing layer is for 4 and 12 channels");
   }
 }
 
@@ -705,9 +916,40 @@ void launch_net_wgrad(const Geom& g, int C, const cx<float>* U, const cx<float>*
                      1.0f, GW);
 }
 
-void launch_net_loss(const Geom& g, int C, const cx<float>* Y, const cx<float>* Q, double inv_norm, cx<double>* scr,
+// parts of an aggregate half's rows in k_net_gram: about 512 workgroups over
+// all aggregate halves, at most one per tile of 8 slots
+static int loss_parts(const Geom& g) {
+  const long halves = 2L * g.nblocks;
+  const long p = (512 + halves - 1) / halves, most = g.bs / TILE;
+  return (int)(p < 1 ? 1 : p < most ? p : most);
+}
+long net_loss_scratch(const Geom& g, int C) {
+  const long halves = 2L * g.nblocks, np = loss_parts(g);
+  return halves * ((np + 1) * 2 * C * C * (long)sizeof(cx<double>) + np * (long)sizeof(double));
+}
+template <int C>
+static void loss_dispatch(const Geom& g, const cx<float>* Y, const cx<float>* Q, double inv_norm, void* scr,
+                          cx<float>* GY, double* lpart, hipStream_t st) {
+  const int halves = 2 * g.nblocks, np = loss_parts(g);
+  cx<double>* part = (cx<double>*)scr;
+  cx<double>* xm = part + (long)halves * np * 2 * C * C;
+  double* qpart = (double*)(xm + (long)halves * 2 * C * C);
+  hipLaunchKernelGGL(k_net_gram<C>, dim3(halves, np), dim3(256), 0, st, g, Y, Q, part, qpart);
+  hipLaunchKernelGGL(k_net_loss<C>, dim3(halves), dim3(256), 0, st, np, (const cx<double>*)part, (const double*)qpart,
+                     inv_norm, xm, lpart);
+  hipLaunchKernelGGL(k_net_loss_grad<C>, dim3(halves, (6 * g.bs + 63) / 64), dim3(64), 0, st, g, Y, Q,
+                     (const cx<double>*)xm, GY);
+}
+void launch_net_loss(const Geom& g, int C, const cx<float>* Y, const cx<float>* Q, double inv_norm, void* scr,
                      cx<float>* GY, double* lpart, hipStream_t st) {
-  hipLaunchKernelGGL(k_net_loss, dim3(2 * g.nblocks), dim3(256), 0, st, g, C, Y, Q, inv_norm, scr, GY, lpart);
+  switch (C) {
+    case 4: loss_dispatch<4>(g, Y, Q, inv_norm, scr, GY, lpart, st); break;
+    case 8: loss_dispatch<8>(g, Y, Q, inv_norm, scr, GY, lpart, st); break;
+    case 12: loss_dispatch<12>(g, Y, Q, inv_norm, scr, GY, lpart, st); break;
+    case 16: loss_dispatch<16>(g, Y, Q, inv_norm, scr, GY, lpart, st); break;
+    case 24: loss_dispatch<24>(g, Y, Q, inv_norm, scr, GY, lpart, st); break;
+    default: throw Error(INVALID_ARG, "network channels must be 4, 8, 12, 16 or 24");
+  }
 }
 
 void launch_adam(long n, float* p, const float* gr, float* m, float* v, float lr, float b1, float b2, float eps,
