@@ -338,6 +338,162 @@ __global__ void __launch_bounds__(256) k_coarse_hop_inv_odd_mrhs(CGeom cg,
   }
 }
 
+// ---------------------------------------------------------------------------
+// The same kernels for K <= 8 columns.  With one wavefront per 16 output rows, a
+// site is a chain of eight or nine blocks (loads, products) and, on odd sites,
+// the inverse: latency, not bytes, when there are few sites.
+// Here four groups of n/16 wavefronts share a site: group gb takes the forward
+// and the backward block of direction gb (and, of the self block, k-step gb),
+// so that every load of the site is in flight at once; their FP32 partial sums
+// meet in LDS in fixed order
+// (launches and sizes measured: split_sites).  The inverse is spread over 4 n threads, each with
+// n/16 of the inner terms of one row, loaded before the hops.
+constexpr int SPLIT_G = 4;
+constexpr int SPLIT_LD = 20;  // floats per output row of a partial sum (16 used; conflict-free)
+
+// part[gb][row][column] of the hops of xh (scaled by hs) and the self block on
+// xs (or null); wavefront (gb, t)
+template <class S, int RT>
+__device__ __forceinline__ void stencil_split(const CGeom& cg, const typename store_traits<S>::elem* D, int site,
+                                              int gb, int t, const cx<float>* xs, const cx<float>* xh, float hs, int K,
+                                              long ldv, int lane, float* part) {
+  constexpr int n = 16 * RT, h = n / 2;
+  constexpr long nn = (long)n * n;
+  const int row = lane & 15, grp = lane >> 4, i = 16 * t + row;
+  const int cf = cg.nbr[site * 8 + gb], cb = cg.nbr[site * 8 + 4 + gb];
+  const typename store_traits<S>::elem* bf_ = D + ((long)site * 5 + 1 + gb) * nn;
+  const typename store_traits<S>::elem* bb_ = D + ((long)cb * 5 + 1 + gb) * nn;
+  typename mm16<S>::frag af[2 * RT + 1], bf[2 * RT + 1];
+#pragma unroll
+  for (int s = 0; s < RT; ++s) {
+    const int lc = 16 * s + 4 * grp;
+    af[s] = a_frag_col<S>(bf_, n, i, lc);
+    af[RT + s] = a_frag_bwd<S>(bb_, n, i, lc, i < h);
+    bf[s] = b_frag<S>(xh + (long)cf * n, ldv, K, row, lc, hs);
+    bf[RT + s] = b_frag<S>(xh + (long)cb * n, ldv, K, row, lc, lc < h ? -hs : hs);
+  }
+  const bool self = xs && gb < RT;
+  if (self) {
+    const int lc = 16 * gb + 4 * grp;
+    af[2 * RT] = a_frag_col<S>(D + (long)site * 5 * nn, n, i, lc);
+    bf[2 * RT] = b_frag<S>(xs + (long)site * n, ldv, K, row, lc, 1.0f);
+  }
+  v4f acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int s = 0; s < 2 * RT; ++s) acc = mm16<S>::mma(af[s], bf[s], acc);
+  if (self) acc = mm16<S>::mma(af[2 * RT], bf[2 * RT], acc);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) part[(gb * n + 16 * t + 4 * grp + e) * SPLIT_LD + row] = acc[e];
+}
+// entry (row i, column r) of the sum of the four groups
+template <int RT>
+__device__ __forceinline__ cx<float> split_sum(const float* part, int i, int r) {
+  constexpr int n = 16 * RT;
+  cx<float> v = mk<float>(0.f, 0.f);
+#pragma unroll
+  for (int g = 0; g < SPLIT_G; ++g) v += *reinterpret_cast<const cx<float>*>(part + (g * n + i) * SPLIT_LD + 2 * r);
+  return v;
+}
+
+// y_r = D x_r, or b_r - D x_r, on every site or on the sites of a list
+template <class S, int RT>
+__global__ void __launch_bounds__(256 * RT) k_coarse_apply_split(CGeom cg,
+                                                                 const typename store_traits<S>::elem* __restrict__ D,
+                                                                 float tw, int K, long ldv,
+                                                                 const cx<float>* __restrict__ x,
+                                                                 const cx<float>* __restrict__ b,
+                                                                 cx<float>* __restrict__ y,
+                                                                 const int* __restrict__ sites) {
+  constexpr int n = 16 * RT;
+  __shared__ float part[SPLIT_G * n * SPLIT_LD];
+  const int site = sites ? sites[blockIdx.x] : cg.lexord[xcd_remap(blockIdx.x, gridDim.x)];
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  stencil_split<S, RT>(cg, D, site, w / RT, w % RT, x, x, 1.0f, K, ldv, threadIdx.x & 63, part);
+  __syncthreads();
+  for (int e = threadIdx.x; e < n * K; e += 256 * RT) {
+    const int r = e / n, i = e - r * n;
+    const long o = (long)r * ldv + (long)site * n + i;
+    cx<float> q = split_sum<RT>(part, i, r);
+    const cx<float> xv = x[o];
+    const float g = i < n / 2 ? -tw : tw;
+    q.re += -g * xv.im;
+    q.im += g * xv.re;
+    y[o] = b ? b[o] - q : q;
+  }
+}
+
+template <class S, int RT>
+__global__ void __launch_bounds__(256 * RT) k_coarse_schur_even_split(CGeom cg,
+                                                                      const typename store_traits<S>::elem* __restrict__ D,
+                                                                      float tw, int K, long ldv,
+                                                                      const cx<float>* __restrict__ v,
+                                                                      const cx<float>* __restrict__ t,
+                                                                      cx<float>* __restrict__ y, int mode) {
+  constexpr int n = 16 * RT;
+  __shared__ float part[SPLIT_G * n * SPLIT_LD];
+  const int site = blockIdx.x, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  stencil_split<S, RT>(cg, D, site, w / RT, w % RT, mode == 0 ? v : nullptr, t, -1.0f, K, ldv, threadIdx.x & 63, part);
+  __syncthreads();
+  for (int e = threadIdx.x; e < n * K; e += 256 * RT) {
+    const int r = e / n, i = e - r * n;
+    const long o = (long)r * ldv + (long)site * n + i;
+    cx<float> q = split_sum<RT>(part, i, r);
+    const cx<float> x = v[o];
+    if (mode == 0) {
+      const float g = i < n / 2 ? -tw : tw;
+      q.re += -g * x.im;
+      q.im += g * x.re;
+    } else {
+      q = x + q;
+    }
+    y[o] = q;
+  }
+}
+
+template <class S, int RT>
+__global__ void __launch_bounds__(256 * RT) k_coarse_hop_inv_odd_split(CGeom cg,
+                                                                       const typename store_traits<S>::elem* __restrict__ D,
+                                                                       const cx<float>* __restrict__ Minv, int K,
+                                                                       long ldv, const cx<float>* __restrict__ x,
+                                                                       const cx<float>* __restrict__ base,
+                                                                       cx<float>* __restrict__ y) {
+  constexpr int n = 16 * RT, NQ = 16;  // NQ parts of the inner index, RT terms each
+  __shared__ float part[SPLIT_G * n * SPLIT_LD];
+  extern __shared__ char smem_raw[];
+  cx<float>* us = reinterpret_cast<cx<float>*>(smem_raw);  // [n][K]
+  cx<float>* ps = us + n * K;                               // [NQ][K][n]
+  const int io = blockIdx.x, site = cg.neven + io;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int i0 = threadIdx.x % n, q = threadIdx.x / n;
+  cx<float> m[RT];
+  const cx<float>* M = Minv + (long)io * n * n;
+#pragma unroll
+  for (int l = 0; l < RT; ++l) m[l] = M[(long)(q * RT + l) * n + i0];
+  stencil_split<S, RT>(cg, D, site, w / RT, w % RT, nullptr, x, 1.0f, K, ldv, threadIdx.x & 63, part);
+  __syncthreads();
+  for (int e = threadIdx.x; e < n * K; e += 256 * RT) {
+    const int r = e / n, i = e - r * n;
+    cx<float> u = split_sum<RT>(part, i, r);
+    if (base) u = base[(long)r * ldv + (long)site * n + i] - u;
+    us[i * K + r] = u;
+  }
+  __syncthreads();
+  for (int r = 0; r < K; ++r) {
+    cx<float> o = mk<float>(0.f, 0.f);
+#pragma unroll
+    for (int l = 0; l < RT; ++l) cmac(o, m[l], us[(q * RT + l) * K + r]);
+    ps[(q * K + r) * n + i0] = o;
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < n * K; e += 256 * RT) {
+    const int r = e / n, i = e - r * n;
+    cx<float> o = mk<float>(0.f, 0.f);
+#pragma unroll
+    for (int p = 0; p < NQ; ++p) o += ps[(p * K + r) * n + i];
+    y[(long)r * ldv + (long)site * n + i] = o;
+  }
+}
+
 // SAP on the blocks of one colour of an intermediate level for K fields in
 // one workgroup per block: n_mr MR steps on the block operator D_B (hops
 // leaving the block dropped).  Wavefront j takes block site j and computes
@@ -510,26 +666,50 @@ __global__ void __launch_bounds__(1024) k_coarse_sap_mrhs(CGeom cg,
 static inline int nt_of(int K) { return K <= 8 ? 1 : 2; }
 
 // instantiate KERNEL<S, NT, RT> for NT = nt_of(K), RT = n / 16
-#define MRHS_DISPATCH(KERNEL, ...)                                                   \
-  do {                                                                               \
-    const int nt = nt_of(K), rt = cg.n / 16;                                         \
-    if (cg.n % 16 || rt < 1 || rt > 4) throw Error(INVALID_ARG, "coarse n must be 16, 32, 48 or 64"); \
-    if (nt == 1) {                                                                   \
-      switch (rt) {                                                                  \
-        case 1: hipLaunchKernelGGL((KERNEL<S, 1, 1>), __VA_ARGS__); break;           \
-        case 2: hipLaunchKernelGGL((KERNEL<S, 1, 2>), __VA_ARGS__); break;           \
-        case 3: hipLaunchKernelGGL((KERNEL<S, 1, 3>), __VA_ARGS__); break;           \
-        default: hipLaunchKernelGGL((KERNEL<S, 1, 4>), __VA_ARGS__); break;          \
-      }                                                                              \
-    } else {                                                                         \
-      switch (rt) {                                                                  \
-        case 1: hipLaunchKernelGGL((KERNEL<S, 2, 1>), __VA_ARGS__); break;           \
-        case 2: hipLaunchKernelGGL((KERNEL<S, 2, 2>), __VA_ARGS__); break;           \
-        case 3: hipLaunchKernelGGL((KERNEL<S, 2, 3>), __VA_ARGS__); break;           \
-        default: hipLaunchKernelGGL((KERNEL<S, 2, 4>), __VA_ARGS__); break;          \
-      }                                                                              \
-    }                                                                                \
+#define MRHS_NT(KERNEL, NT, ...)                                                          \
+  switch (cg.n) {                                                                         \
+    case 16: hipLaunchKernelGGL((KERNEL<S, NT, 1>), __VA_ARGS__); break;                  \
+    case 32: hipLaunchKernelGGL((KERNEL<S, NT, 2>), __VA_ARGS__); break;                  \
+    case 48: hipLaunchKernelGGL((KERNEL<S, NT, 3>), __VA_ARGS__); break;                  \
+    case 64: hipLaunchKernelGGL((KERNEL<S, NT, 4>), __VA_ARGS__); break;                  \
+    default: throw Error(INVALID_ARG, "coarse n must be 16, 32, 48 or 64");               \
+  }
+#define MRHS_DISPATCH(KERNEL, ...)                                                        \
+  do {                                                                                    \
+    if (nt_of(K) == 1) {                                                                  \
+      MRHS_NT(KERNEL, 1, __VA_ARGS__)                                                     \
+    } else {                                                                              \
+      MRHS_NT(KERNEL, 2, __VA_ARGS__)                                                     \
+    }                                                                                     \
   } while (0)
+// the stencil kernels that split_sites leaves: one column tile at n = 64 only
+#define MRHS_DISPATCH_BIG(KERNEL, ...)                                                    \
+  do {                                                                                    \
+    if (nt_of(K) == 1) hipLaunchKernelGGL((KERNEL<S, 1, 4>), __VA_ARGS__);                \
+    else {                                                                                \
+      MRHS_NT(KERNEL, 2, __VA_ARGS__)                                                     \
+    }                                                                                     \
+  } while (0)
+
+// instantiate KERNEL<S, RT> for RT = n / 16
+#define SPLIT_DISPATCH(KERNEL, ...)                                                                  \
+  do {                                                                                               \
+    switch (cg.n) {                                                                                  \
+      case 16: hipLaunchKernelGGL((KERNEL<S, 1>), __VA_ARGS__); break;                               \
+      case 32: hipLaunchKernelGGL((KERNEL<S, 2>), __VA_ARGS__); break;                               \
+      case 48: hipLaunchKernelGGL((KERNEL<S, 3>), __VA_ARGS__); break;                               \
+      case 64: hipLaunchKernelGGL((KERNEL<S, 4>), __VA_ARGS__); break;                               \
+      default: throw Error(INVALID_ARG, "coarse n must be 16, 32, 48 or 64");                        \
+    }                                                                                                \
+  } while (0)
+
+// Whether a launch over nsites sites takes the split kernels.  Up to eight
+// columns; at n <= 48 on every size measured (six columns, us per odd-even pair,
+// before and now: 32 sites of n = 32 18.1 and 8.2, 512 sites of n = 48 30.4 and
+// 12.8, 41472 sites of n = 48 867 and 825), at n = 64 while 512 workgroups or
+// fewer leave room (pair on 256 sites 35.4 and 18.6, on 1024 48.7 and 39.1, but
+// on 2048 66.0 and 74.0: 1024 threads a site then keep too few sites in flight).
+static inline bool split_sites(int nsites, int n, int K) { return K <= 8 && (n <= 48 || nsites <= 512); }
 
 template <class S>
 void launch_coarse_apply_mrhs(const CGeom& cg, const void* D, double tw, int K, long ldv, const cx<float>* x,
@@ -537,7 +717,11 @@ void launch_coarse_apply_mrhs(const CGeom& cg, const void* D, double tw, int K, 
   dim3 grid(sites ? nlist : cg.nsites), blk(4 * cg.n);
   if (grid.x == 0) return;
   auto Dp = (const typename store_traits<S>::elem*)D;
-  MRHS_DISPATCH(k_coarse_apply_mrhs, grid, blk, 0, st, cg, Dp, (float)tw, K, ldv, x, b, y, sites);
+  if (split_sites(grid.x, cg.n, K)) {
+    SPLIT_DISPATCH(k_coarse_apply_split, grid, dim3(16 * cg.n), 0, st, cg, Dp, (float)tw, K, ldv, x, b, y, sites);
+    return;
+  }
+  MRHS_DISPATCH_BIG(k_coarse_apply_mrhs, grid, blk, 0, st, cg, Dp, (float)tw, K, ldv, x, b, y, sites);
 }
 
 template <class S>
@@ -545,7 +729,11 @@ void launch_coarse_schur_even_mrhs(const CGeom& cg, const void* D, double tw, in
                                    const cx<float>* t, cx<float>* y, int mode, hipStream_t st) {
   dim3 grid(cg.neven), blk(4 * cg.n);
   auto Dp = (const typename store_traits<S>::elem*)D;
-  MRHS_DISPATCH(k_coarse_schur_even_mrhs, grid, blk, 0, st, cg, Dp, (float)tw, K, ldv, v, t, y, mode);
+  if (split_sites(cg.neven, cg.n, K)) {
+    SPLIT_DISPATCH(k_coarse_schur_even_split, grid, dim3(16 * cg.n), 0, st, cg, Dp, (float)tw, K, ldv, v, t, y, mode);
+    return;
+  }
+  MRHS_DISPATCH_BIG(k_coarse_schur_even_mrhs, grid, blk, 0, st, cg, Dp, (float)tw, K, ldv, v, t, y, mode);
 }
 
 template <class S>
@@ -557,7 +745,12 @@ void launch_coarse_hop_inv_odd_mrhs(const CGeom& cg, const void* D, const cx<flo
   // hop result [n][K], and for K <= 8 the four partial sums [4][n][K]
   const size_t sm = (size_t)(nt_of(K) == 2 ? 1 : 5) * cg.n * K * sizeof(cx<float>);
   auto Dp = (const typename store_traits<S>::elem*)D;
-  MRHS_DISPATCH(k_coarse_hop_inv_odd_mrhs, grid, blk, sm, st, cg, Dp, Minv, K, ldv, x, base, y);
+  if (split_sites(nodd, cg.n, K)) {
+    const size_t ss = (size_t)17 * cg.n * K * sizeof(cx<float>);  // us and the 16 partial sums
+    SPLIT_DISPATCH(k_coarse_hop_inv_odd_split, grid, dim3(16 * cg.n), ss, st, cg, Dp, Minv, K, ldv, x, base, y);
+    return;
+  }
+  MRHS_DISPATCH_BIG(k_coarse_hop_inv_odd_mrhs, grid, blk, sm, st, cg, Dp, Minv, K, ldv, x, base, y);
 }
 
 template <class S>
