@@ -219,17 +219,6 @@ __global__ void k_trisolve(const cx<double>* H, int ldh, const cx<double>* g, cx
     y[i] = dn > 0 ? (1.0 / dn) * (s * conj(d)) : mk(0.0, 0.0);
   }
 }
-void launch_trisolve(const cx<double>* H, int ldh, const cx<double>* g, cx<double>* y, int j, hipStream_t st) {
-  hipLaunchKernelGGL(k_trisolve, dim3(1), dim3(64), 0, st, H, ldh, g, y, j);
-}
-
-__global__ void k_set_scalar(cx<double>* dst, const cx<double>* src) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) dst[0] = src[0];
-}
-void launch_set_scalar(cx<double>* dst, const cx<double>* src, hipStream_t st) {
-  hipLaunchKernelGGL(k_set_scalar, dim3(1), dim3(64), 0, st, dst, src);
-}
-
 #define INST_B(R)                                                                                                \
   template void launch_multidot<R>(const cx<R>*, long, int, const cx<R>*, long, cx<double>*, int, hipStream_t); \
   template void launch_multi_axpy<R>(const cx<R>*, long, int, const cx<double>*, double, cx<R>*, long,          \
@@ -503,17 +492,18 @@ __global__ void k_trisolve_b(const cx<double>* H, int ldh, int m, const cx<doubl
 }
 // the same for m <= 32: one workgroup per column, the triangle staged in LDS
 // with all loads in flight, then column-oriented substitution (after y_k,
-// every row t < k takes s_t -= H[t][k] y_k in parallel)
+// every row t < k takes s_t -= H[t][k] y_k in parallel); without jd every
+// column has jall steps
 __global__ void __launch_bounds__(64) k_trisolve_lds_b(const cx<double>* __restrict__ H, int ldh, int m,
                                                        const cx<double>* __restrict__ g, cx<double>* __restrict__ y,
-                                                       const int* __restrict__ jd) {
+                                                       const int* __restrict__ jd, int jall) {
   __shared__ cx<double> Hs[32][33];  // Hs[k][i] = H[i][k] (column k of the triangle)
   __shared__ cx<double> sv[32], yv[32];
   const int r = blockIdx.x, t = threadIdx.x;
   const cx<double>* Hr = H + (long)r * ldh * m;
   const cx<double>* gr = g + (long)r * ldh;
   cx<double>* yr = y + (long)r * ldh;
-  const int j = jd[r];
+  const int j = jd ? jd[r] : jall;
   for (int q = t; q < j * 32; q += 64) {
     const int k = q >> 5, i = q & 31;
     if (i <= k) Hs[k][i] = Hr[(long)k * ldh + i];
@@ -535,9 +525,16 @@ __global__ void __launch_bounds__(64) k_trisolve_lds_b(const cx<double>* __restr
 void launch_trisolve_b(const cx<double>* H, int ldh, int m, const cx<double>* g, cx<double>* y, const int* jd, int K,
                        hipStream_t st) {
   if (m <= 32)
-    hipLaunchKernelGGL(k_trisolve_lds_b, dim3(K), dim3(64), 0, st, H, ldh, m, g, y, jd);
+    hipLaunchKernelGGL(k_trisolve_lds_b, dim3(K), dim3(64), 0, st, H, ldh, m, g, y, jd, 0);
   else
     hipLaunchKernelGGL(k_trisolve_b, dim3(1), dim3(64), 0, st, H, ldh, m, g, y, jd, K);
+}
+
+void launch_trisolve(const cx<double>* H, int ldh, int m, const cx<double>* g, cx<double>* y, int j, hipStream_t st) {
+  if (m <= 32)
+    hipLaunchKernelGGL(k_trisolve_lds_b, dim3(1), dim3(64), 0, st, H, ldh, m, g, y, (const int*)nullptr, j);
+  else
+    hipLaunchKernelGGL(k_trisolve, dim3(1), dim3(64), 0, st, H, ldh, g, y, j);
 }
 
 // g_r = 0 except g_r[0] = s_r  (start of a cycle)
@@ -612,11 +609,11 @@ __device__ __forceinline__ void reduce_partials(const double* partd, int nval, i
 }
 }  // namespace
 
-// Per-thread sums and the updates w -= sum_i c_i V_i are in R (FP32 for FP32
-// vectors; the coefficients are rounded to R), every sum across threads in FP64
-// from the wavefront totals on.
+// Per-thread sums and the updates w -= sum_i c_i V_i are in A (lock-step columns
+// in FP32: FP32 with the coefficients rounded to it; one column: FP64), every
+// sum across threads in FP64 from the wavefront totals on.
 // pa_r: partials of V_{r,i}^H w_r  (i < k)
-template <class R, int KM, int BS>
+template <class R, class A, int KM, int BS>
 __global__ void __launch_bounds__(BS) k_cgs_dot(const cx<R>* __restrict__ V, long ldv, long csV, int k,
                                                 const cx<R>* __restrict__ w, long csw, long N, double* pa,
                                                 long pcs, const int* act) {
@@ -626,17 +623,17 @@ __global__ void __launch_bounds__(BS) k_cgs_dot(const cx<R>* __restrict__ V, lon
   w += r * csw;
   // sums for KM vectors, padded to a power of two for the wavefront reduction
   constexpr int KP = cgs_pow2(KM);
-  R acc[2 * KP];
+  A acc[2 * KP];
 #pragma unroll
-  for (int q = 0; q < 2 * KP; ++q) acc[q] = R(0);
+  for (int q = 0; q < 2 * KP; ++q) acc[q] = A(0);
   const long stride = (long)gridDim.x * BS;
   for (long e = (long)blockIdx.x * BS + threadIdx.x; e < N; e += stride) {
     const cx<R> x = w[e];
 #pragma unroll
     for (int i = 0; i < KM; ++i) {  // every load issued (index clamped); sums past k unused
       const cx<R> v = V[(long)min(i, k - 1) * ldv + e];
-      acc[2 * i] += v.re * x.re + v.im * x.im;
-      acc[2 * i + 1] += v.re * x.im - v.im * x.re;
+      acc[2 * i] += (A)v.re * x.re + (A)v.im * x.im;
+      acc[2 * i + 1] += (A)v.re * x.im - (A)v.im * x.re;
     }
   }
   store_partials<KP, BS / 64>(acc, 2 * k, pa + 2 * r * pcs);
@@ -644,7 +641,7 @@ __global__ void __launch_bounds__(BS) k_cgs_dot(const cx<R>* __restrict__ V, lon
 
 // h_r = sum of pa_r (workgroup 0 stores it in hcol_r);  w_r -= sum_i h_r[i] V_{r,i};
 // pb_r: partials of V_{r,i}^H w_r
-template <class R, int KM, int BS>
+template <class R, class A, int KM, int BS>
 __global__ void __launch_bounds__(BS) k_cgs_axpy_dot(const cx<R>* __restrict__ V, long ldv, long csV, int k,
                                                      cx<R>* w, long csw, long N, const double* pa, double* pb,
                                                      long pcs, cx<double>* hcol, long hcs, const int* act) {
@@ -653,34 +650,34 @@ __global__ void __launch_bounds__(BS) k_cgs_axpy_dot(const cx<R>* __restrict__ V
   V += r * csV;
   w += r * csw;
   __shared__ double cf[2 * KM];
-  __shared__ cx<R> cfr[KM];
+  __shared__ cx<A> cfr[KM];
   reduce_partials(pa + 2 * r * pcs, 2 * k, 2 * KM, gridDim.x, cf);
   if (blockIdx.x == 0 && threadIdx.x < 2 * k) reinterpret_cast<double*>(hcol + r * hcs)[threadIdx.x] = cf[threadIdx.x];
-  if (threadIdx.x < KM) cfr[threadIdx.x] = mk<R>((R)cf[2 * threadIdx.x], (R)cf[2 * threadIdx.x + 1]);
+  if (threadIdx.x < KM) cfr[threadIdx.x] = mk<A>((A)cf[2 * threadIdx.x], (A)cf[2 * threadIdx.x + 1]);
   __syncthreads();
   // sums for KM vectors, padded to a power of two for the wavefront reduction
   constexpr int KP = cgs_pow2(KM);
-  R acc[2 * KP];
+  A acc[2 * KP];
 #pragma unroll
-  for (int q = 0; q < 2 * KP; ++q) acc[q] = R(0);
+  for (int q = 0; q < 2 * KP; ++q) acc[q] = A(0);
   const long stride = (long)gridDim.x * BS;
   for (long e = (long)blockIdx.x * BS + threadIdx.x; e < N; e += stride) {
     const cx<R> x0 = w[e];
-    cx<R> s = mk<R>(0, 0);
+    cx<A> s = mk<A>(0, 0);
 #pragma unroll
     for (int i = 0; i < KM; ++i) {  // coefficients past k are zero
       const cx<R> v = V[(long)min(i, k - 1) * ldv + e];
-      cmac(s, cfr[i], v);
+      cmac(s, cfr[i], mk<A>(v.re, v.im));
     }
-    const cx<R> x = mk<R>(x0.re - s.re, x0.im - s.im);
+    const cx<R> x = mk<R>((R)(x0.re - s.re), (R)(x0.im - s.im));
     w[e] = x;
     // reload the basis entries (cache hits) rather than hold KM of them in registers
     asm volatile("" ::: "memory");
 #pragma unroll
     for (int i = 0; i < KM; ++i) {
       const cx<R> v = V[(long)min(i, k - 1) * ldv + e];
-      acc[2 * i] += v.re * x.re + v.im * x.im;
-      acc[2 * i + 1] += v.re * x.im - v.im * x.re;
+      acc[2 * i] += (A)v.re * x.re + (A)v.im * x.im;
+      acc[2 * i + 1] += (A)v.re * x.im - (A)v.im * x.re;
     }
   }
   store_partials<KP, BS / 64>(acc, 2 * k, pb + 2 * r * pcs);
@@ -688,7 +685,7 @@ __global__ void __launch_bounds__(BS) k_cgs_axpy_dot(const cx<R>* __restrict__ V
 
 // c_r = sum of pb_r (workgroup 0: hcol_r += c_r, or hcol_r = c_r when this is
 // the only pass);  w_r -= sum_i c_r[i] V_{r,i};  pa_r: partials of ||w_r||^2
-template <class R, int KM, int BS, bool FIRST = false>
+template <class R, class A, int KM, int BS, bool FIRST = false>
 __global__ void __launch_bounds__(BS) k_cgs_axpy_norm(const cx<R>* __restrict__ V, long ldv, long csV, int k,
                                                       cx<R>* w, long csw, long N, const double* pb, double* pa,
                                                       long pcs, cx<double>* hcol, long hcs, const int* act) {
@@ -697,27 +694,27 @@ __global__ void __launch_bounds__(BS) k_cgs_axpy_norm(const cx<R>* __restrict__ 
   V += r * csV;
   w += r * csw;
   __shared__ double cf[2 * KM];
-  __shared__ cx<R> cfr[KM];
+  __shared__ cx<A> cfr[KM];
   reduce_partials(pb + 2 * r * pcs, 2 * k, 2 * KM, gridDim.x, cf);
   if (blockIdx.x == 0 && threadIdx.x < 2 * k) {
     double& hv = reinterpret_cast<double*>(hcol + r * hcs)[threadIdx.x];
     hv = FIRST ? cf[threadIdx.x] : hv + cf[threadIdx.x];
   }
-  if (threadIdx.x < KM) cfr[threadIdx.x] = mk<R>((R)cf[2 * threadIdx.x], (R)cf[2 * threadIdx.x + 1]);
+  if (threadIdx.x < KM) cfr[threadIdx.x] = mk<A>((A)cf[2 * threadIdx.x], (A)cf[2 * threadIdx.x + 1]);
   __syncthreads();
-  R acc[2] = {R(0), R(0)};
+  A acc[2] = {A(0), A(0)};
   const long stride = (long)gridDim.x * BS;
   for (long e = (long)blockIdx.x * BS + threadIdx.x; e < N; e += stride) {
     const cx<R> x0 = w[e];
-    cx<R> s = mk<R>(0, 0);
+    cx<A> s = mk<A>(0, 0);
 #pragma unroll
     for (int i = 0; i < KM; ++i) {  // coefficients past k are zero
       const cx<R> v = V[(long)min(i, k - 1) * ldv + e];
-      cmac(s, cfr[i], v);
+      cmac(s, cfr[i], mk<A>(v.re, v.im));
     }
-    const cx<R> x = mk<R>(x0.re - s.re, x0.im - s.im);
+    const cx<R> x = mk<R>((R)(x0.re - s.re), (R)(x0.im - s.im));
     w[e] = x;
-    acc[0] += x.re * x.re + x.im * x.im;
+    acc[0] += (A)x.re * x.re + (A)x.im * x.im;
   }
   store_partials<1, BS / 64>(acc, 1, pa + 2 * r * pcs);
 }
@@ -777,7 +774,7 @@ __global__ void __launch_bounds__(BS) k_cgs_scale_givens(cx<R>* w, long csw, lon
   }
 }
 
-template <class R, int BS>
+template <class R, class A, int BS>
 static void cgs_step_bs(const cx<R>* V, long ldv, long csV, int k, cx<R>* w, long csw, long N, double* a, double* b,
                         long pcs, int nwg, cx<double>* hcol, long hcs, cx<double>* H, int ldh, int m, double* cs,
                         cx<double>* sn, cx<double>* g, int j, double* resid, double* resid_host, int K, const int* act,
@@ -789,15 +786,15 @@ static void cgs_step_bs(const cx<R>* V, long ldv, long csV, int k, cx<R>* w, lon
 #define CGS_LAUNCH(KM)                                                                                                 \
   {                                                                                                                    \
     constexpr int BA = (BS == 1024 && KM >= 16) ? 512 : BS;                                                            \
-    hipLaunchKernelGGL((k_cgs_dot<R, KM, BS>), grid, blk, 0, st, V, ldv, csV, k, (const cx<R>*)w, csw, N, a, pcs,     \
+    hipLaunchKernelGGL((k_cgs_dot<R, A, KM, BS>), grid, blk, 0, st, V, ldv, csV, k, (const cx<R>*)w, csw, N, a, pcs,     \
                        act);                                                                                           \
     if (two_pass) {                                                                                                    \
-      hipLaunchKernelGGL((k_cgs_axpy_dot<R, KM, BA>), grid, dim3(BA), 0, st, V, ldv, csV, k, w, csw, N,               \
+      hipLaunchKernelGGL((k_cgs_axpy_dot<R, A, KM, BA>), grid, dim3(BA), 0, st, V, ldv, csV, k, w, csw, N,               \
                          (const double*)a, b, pcs, hcol, hcs, act);                                                    \
-      hipLaunchKernelGGL((k_cgs_axpy_norm<R, KM, BA>), grid, dim3(BA), 0, st, V, ldv, csV, k, w, csw, N,              \
+      hipLaunchKernelGGL((k_cgs_axpy_norm<R, A, KM, BA>), grid, dim3(BA), 0, st, V, ldv, csV, k, w, csw, N,              \
                          (const double*)b, a, pcs, hcol, hcs, act);                                                    \
     } else {                                                                                                           \
-      hipLaunchKernelGGL((k_cgs_axpy_norm<R, KM, BA, true>), grid, dim3(BA), 0, st, V, ldv, csV, k, w, csw, N,        \
+      hipLaunchKernelGGL((k_cgs_axpy_norm<R, A, KM, BA, true>), grid, dim3(BA), 0, st, V, ldv, csV, k, w, csw, N,        \
                          (const double*)a, b, pcs, hcol, hcs, act);                                                    \
     }                                                                                                                  \
   }
@@ -839,19 +836,20 @@ template <class R>
 void launch_cgs_step(const cx<R>* V, long ldv, long csV, int k, cx<R>* w, long csw, long N, cx<double>* pa,
                      cx<double>* pb, long pcs, int nwg, cx<double>* hcol, long hcs, cx<double>* H, int ldh, int m,
                      double* cs, cx<double>* sn, cx<double>* g, int j, double* resid, double* resid_host, int K,
-                     const int* act, hipStream_t st) {
+                     const int* act, bool sums64, hipStream_t st) {
   double* a = reinterpret_cast<double*>(pa);
   double* b = reinterpret_cast<double*>(pb);
-  if constexpr (sizeof(R) == 4)
-    cgs_step_bs<R, 512>(V, ldv, csV, k, w, csw, N, a, b, pcs, nwg, hcol, hcs, H, ldh, m, cs, sn, g, j, resid, resid_host, K, act, st);
-  else
-    cgs_step_bs<R, 256>(V, ldv, csV, k, w, csw, N, a, b, pcs, nwg, hcol, hcs, H, ldh, m, cs, sn, g, j, resid, resid_host, K, act, st);
+#define CGS_ARGS V, ldv, csV, k, w, csw, N, a, b, pcs, nwg, hcol, hcs, H, ldh, m, cs, sn, g, j, resid, resid_host, K, act, st
+  if constexpr (sizeof(R) == 8) cgs_step_bs<R, double, 256>(CGS_ARGS);
+  else if (sums64) cgs_step_bs<R, double, 512>(CGS_ARGS);
+  else cgs_step_bs<R, R, 512>(CGS_ARGS);
+#undef CGS_ARGS
 }
 #define INST_CGS(R)                                                                                             \
   template int cgs_block_size<R>();                                                                               \
   template void launch_cgs_step<R>(const cx<R>*, long, long, int, cx<R>*, long, long, cx<double>*, cx<double>*,   \
                                    long, int, cx<double>*, long, cx<double>*, int, int, double*, cx<double>*,     \
-                                   cx<double>*, int, double*, double*, int, const int*, hipStream_t);
+                                   cx<double>*, int, double*, double*, int, const int*, bool, hipStream_t);
 INST_CGS(double)
 INST_CGS(float)
 

@@ -72,6 +72,177 @@ __device__ __forceinline__ cx<R> hop_row(const CGeom& cg, const typename store_t
   return acc;
 }
 
+// ---------------------------------------------------------------------------
+// One site per workgroup of eight wavefronts, for grids whose sites do not fill
+// the card at one wavefront each: wavefront w takes one of the eight hops (and
+// an eighth of the self block's columns), so that the site's blocks are loaded
+// together instead of one after the other.  Lanes hold rows; with n <= 32 the
+// lanes left over split the inner index P ways.  Sums are in R as in the
+// one-wavefront form, the 8 P partial sums of a row added in fixed order.
+namespace {
+constexpr int SITE_W = 8;
+constexpr int SITE_T = 64 * SITE_W;
+// inner-index parts per wavefront
+__device__ __forceinline__ int site_parts(int n) { return n > 32 ? 1 : n > 16 ? 2 : n > 8 ? 4 : 8; }
+
+// sum over l = l0 + part, l0 + part + P, ... < l1 of D[l * n + k] y[l]
+template <class R, class S>
+__device__ __forceinline__ cx<R> col_sum(const typename store_traits<S>::elem* D, int n, int k, int l0, int l1, int P,
+                                         const cx<R>* y) {
+  constexpr int U = sizeof(R) == 8 ? 8 : 16;  // entries in flight
+  cx<R> acc = mk<R>(0, 0);
+  for (int l = l0; l < l1; l += U * P) {
+    cx<R> d[U];
+#pragma unroll
+    for (int q = 0; q < U; ++q) d[q] = ld<R, S>(D, (long)min(l + q * P, l1 - 1) * n + k);
+#pragma unroll
+    for (int q = 0; q < U; ++q)
+      if (l + q * P < l1) cmac(acc, d[q], y[l + q * P]);
+  }
+  return acc;
+}
+// sum over the l of this part of conj(D[k * n + l]) y[l]: a lane reads its row
+// VE entries (16 bytes) at a time where n allows
+template <class R, class S>
+__device__ __forceinline__ cx<R> row_sum(const typename store_traits<S>::elem* D, int n, int k, int part, int P,
+                                         const cx<R>* y) {
+  using E = typename store_traits<S>::elem;
+  constexpr int VE = 16 / sizeof(E), U = sizeof(R) == 8 ? 8 : 4;
+  struct alignas(16) V {
+    E e[VE];
+  };
+  cx<R> acc = mk<R>(0, 0);
+  if (n % VE == 0) {
+    const V* p = reinterpret_cast<const V*>(D + (long)k * n);
+    const int nv = n / VE;
+    for (int c = part; c < nv; c += U * P) {
+      V v[U];
+#pragma unroll
+      for (int q = 0; q < U; ++q) v[q] = p[min(c + q * P, nv - 1)];
+#pragma unroll
+      for (int q = 0; q < U; ++q)
+        if (c + q * P < nv) {
+#pragma unroll
+          for (int e = 0; e < VE; ++e) cjmac(acc, ld<R, S>(v[q].e, e), y[(c + q * P) * VE + e]);
+        }
+    }
+  } else {
+    for (int l = part; l < n; l += P) cjmac(acc, ld<R, S>(D, (long)k * n + l), y[l]);
+  }
+  return acc;
+}
+
+// partial sums ps[(w P + part) * n + row] of hs * (hops of xh) + S xs at `site`
+// (xs null: hops only); ys: 9 * 64 complex of LDS.  Ends with a barrier.
+template <class R, class S>
+__device__ __forceinline__ void site_partials(const CGeom& cg, const typename store_traits<S>::elem* D, int site,
+                                              const cx<R>* xs, const cx<R>* xh, R hs, cx<R>* ys, cx<R>* ps) {
+  const int n = cg.n, h = n >> 1, P = site_parts(n), rows = 64 / P;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const long nn = (long)n * n;
+  const int row = lane & (rows - 1), part = lane / rows, nb = cg.nbr[site * 8 + w];
+  // the wavefront's hop input (the backward one with its Gamma5 sign) and an
+  // eighth of the self input
+  if (lane < n) {
+    const cx<R> v = xh[(long)nb * n + lane];
+    const R f = w >= 4 && lane < h ? -hs : hs;
+    ys[w * 64 + lane] = mk<R>(f * v.re, f * v.im);
+  }
+  const int l0 = w * n / SITE_W, l1 = (w + 1) * n / SITE_W;
+  if (xs && lane >= l0 && lane < l1) ys[8 * 64 + lane] = xs[(long)site * n + lane];
+  __syncthreads();
+  if (row < n) {
+    cx<R> acc;
+    if (w < 4) {
+      acc = col_sum<R, S>(D + ((long)site * 5 + 1 + w) * nn, n, row, part, n, P, ys + w * 64);
+    } else {
+      acc = row_sum<R, S>(D + ((long)nb * 5 + 1 + (w - 4)) * nn, n, row, part, P, ys + w * 64);
+      if (row < h) acc = -acc;
+    }
+    if (xs) acc += col_sum<R, S>(D + (long)site * 5 * nn, n, row, l0 + part, l1, P, ys + 8 * 64);
+    ps[(w * P + part) * n + row] = acc;
+  }
+  __syncthreads();
+}
+template <class R>
+__device__ __forceinline__ cx<R> site_sum(const CGeom& cg, const cx<R>* ps, int k) {
+  const int q = SITE_W * site_parts(cg.n);
+  cx<R> v = mk<R>(0, 0);
+  for (int p = 0; p < q; ++p) v += ps[p * cg.n + k];
+  return v;
+}
+}  // namespace
+
+// out = D y, or b - D y
+template <class R, class S>
+__global__ void __launch_bounds__(SITE_T) k_coarse_apply_site(CGeom cg,
+                                                              const typename store_traits<S>::elem* __restrict__ D, R tw,
+                                                              const cx<R>* __restrict__ in, const cx<R>* __restrict__ b,
+                                                              cx<R>* __restrict__ out) {
+  __shared__ cx<R> ys[9 * 64], ps[SITE_T];
+  // each XCD takes a contiguous range of sites in lexicographic order: a
+  // forward block is still in its L2 when the neighbours' backward hops read it
+  const int site = cg.lexord[xcd_remap(blockIdx.x, gridDim.x)], k = threadIdx.x, n = cg.n;
+  site_partials<R, S>(cg, D, site, in, in, R(1), ys, ps);
+  if (k >= n) return;
+  const long o = (long)site * n + k;
+  const cx<R> acc = site_sum(cg, ps, k) + (R)(tw * g5(k, n)) * times_i(in[o]);
+  out[o] = b ? b[o] - acc : acc;
+}
+
+// even sites: mode 0: out = (S + i tw G5) v - hop(t);  mode 1: out = v - hop(t)
+template <class R, class S>
+__global__ void __launch_bounds__(SITE_T) k_coarse_schur_even_site(CGeom cg,
+                                                                   const typename store_traits<S>::elem* __restrict__ D,
+                                                                   R tw, const cx<R>* __restrict__ v,
+                                                                   const cx<R>* __restrict__ tv, cx<R>* __restrict__ out,
+                                                                   int mode) {
+  __shared__ cx<R> ys[9 * 64], ps[SITE_T];
+  const int site = blockIdx.x, k = threadIdx.x, n = cg.n;
+  site_partials<R, S>(cg, D, site, mode == 0 ? v : nullptr, tv, R(-1), ys, ps);
+  if (k >= n) return;
+  const long o = (long)site * n + k;
+  const cx<R> acc = site_sum(cg, ps, k), x = v[o];
+  out[o] = mode == 0 ? acc + (R)(tw * g5(k, n)) * times_i(x) : x + acc;
+}
+
+// odd sites: out = M (base - hop(in)) if base, else out = M hop(in)
+template <class R, class S>
+__global__ void __launch_bounds__(SITE_T) k_coarse_hop_inv_odd_site(CGeom cg,
+                                                                    const typename store_traits<S>::elem* __restrict__ D,
+                                                                    const cx<R>* __restrict__ Minv,
+                                                                    const cx<R>* __restrict__ in,
+                                                                    const cx<R>* __restrict__ base,
+                                                                    cx<R>* __restrict__ out) {
+  __shared__ cx<R> ys[9 * 64], ps[SITE_T];
+  const int n = cg.n, io = blockIdx.x, site = cg.neven + io, t = threadIdx.x;
+  // this thread's entries of the inverse (row, l = q, q + 8 P, ...: at most 8),
+  // loaded before the hops
+  const int P = site_parts(n), rows = 64 / P, Q = SITE_W * P, row = t & (rows - 1), q = t / rows;
+  const cx<R>* M = Minv + (long)io * n * n;
+  cx<R> m[8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) m[j] = M[(long)min(q + j * Q, n - 1) * n + min(row, n - 1)];
+  site_partials<R, S>(cg, D, site, nullptr, in, R(1), ys, ps);
+  if (t < n) {
+    cx<R> u = site_sum(cg, ps, t);
+    if (base) u = base[(long)site * n + t] - u;
+    ys[t] = u;
+  }
+  __syncthreads();
+  cx<R> acc = mk<R>(0, 0);
+#pragma unroll
+  for (int j = 0; j < 8; ++j)
+    if (q + j * Q < n) cmac(acc, m[j], ys[q + j * Q]);
+  if (row < n) ps[q * n + row] = acc;
+  __syncthreads();
+  if (t < n) {
+    cx<R> o = mk<R>(0, 0);
+    for (int p = 0; p < Q; ++p) o += ps[p * n + t];
+    out[(long)site * n + t] = o;
+  }
+}
+
 // out = D y   (or out = b - D y when b != nullptr)
 template <class R, class S>
 __global__ void __launch_bounds__(256) k_coarse_apply(CGeom cg, const typename store_traits<S>::elem* __restrict__ D,
@@ -90,16 +261,31 @@ __global__ void __launch_bounds__(256) k_coarse_apply(CGeom cg, const typename s
   }
 }
 
+// Whether a launch over nsites sites takes one workgroup per site.  From n = 26
+// on it is as fast or faster on every size measured (us, before and now; apply:
+// FP64 n = 48 on 32 sites 31 and 11, on 2048 116 and 115, on 8192 620 and 452;
+// FP32 n = 64 on 512 55 and 27; odd-even pair: 16-bit n = 52 on 1024 94 and 30).
+// Smaller sites give eight wavefronts too little work once the grid fills the
+// card (FP32 n = 16: pair on 512 sites 23 and 11, apply on 1024 10.5 and 11.9,
+// on 8192 45 and 82).
+static inline bool one_site(int nsites, int n) { return n > 24 || nsites <= 512; }
+template <class R, class S>
+static void coarse_apply(const CGeom& cg, const void* D, double tw, const cx<R>* in, const cx<R>* b, cx<R>* out,
+                         hipStream_t st) {
+  auto Dp = (const typename store_traits<S>::elem*)D;
+  if (one_site(cg.nsites, cg.n))
+    hipLaunchKernelGGL((k_coarse_apply_site<R, S>), dim3(cg.nsites), dim3(SITE_T), 0, st, cg, Dp, (R)tw, in, b, out);
+  else
+    hipLaunchKernelGGL((k_coarse_apply<R, S>), dim3((cg.nsites + 3) / 4), dim3(256), 0, st, cg, Dp, (R)tw, in, b, out);
+}
 template <class R, class S>
 void launch_coarse_apply(const CGeom& cg, const void* D, double tw, const cx<R>* in, cx<R>* out, hipStream_t st) {
-  hipLaunchKernelGGL((k_coarse_apply<R, S>), dim3((cg.nsites + 3) / 4), dim3(256), 0, st, cg,
-                     (const typename store_traits<S>::elem*)D, (R)tw, in, (const cx<R>*)nullptr, out);
+  coarse_apply<R, S>(cg, D, tw, in, nullptr, out, st);
 }
 template <class R, class S>
 void launch_coarse_residual(const CGeom& cg, const void* D, double tw, const cx<R>* b, const cx<R>* x, cx<R>* r,
                             hipStream_t st) {
-  hipLaunchKernelGGL((k_coarse_apply<R, S>), dim3((cg.nsites + 3) / 4), dim3(256), 0, st, cg,
-                     (const typename store_traits<S>::elem*)D, (R)tw, x, b, r);
+  coarse_apply<R, S>(cg, D, tw, x, b, r, st);
 }
 
 // ---------------------------------------------------------------------------
@@ -707,19 +893,15 @@ __global__ void __launch_bounds__(256) k_coarse_hop_inv_odd(CGeom cg,
   }
 }
 template <class R, class S>
-void launch_coarse_hop_inv_odd(const CGeom& cg, const void* D, const cx<R>* Minv, const cx<R>* in, cx<R>* out,
-                               int subtract_from, hipStream_t st) {
-  (void)subtract_from;
-  int nodd = cg.nsites - cg.neven;
-  hipLaunchKernelGGL((k_coarse_hop_inv_odd<R, S>), dim3((nodd + 3) / 4), dim3(256), 0, st, cg,
-                     (const typename store_traits<S>::elem*)D, Minv, in, (const cx<R>*)nullptr, out);
-}
-template <class R, class S>
-void launch_coarse_hop_inv_odd_base(const CGeom& cg, const void* D, const cx<R>* Minv, const cx<R>* in,
-                                    const cx<R>* base, cx<R>* out, hipStream_t st) {
-  int nodd = cg.nsites - cg.neven;
-  hipLaunchKernelGGL((k_coarse_hop_inv_odd<R, S>), dim3((nodd + 3) / 4), dim3(256), 0, st, cg,
-                     (const typename store_traits<S>::elem*)D, Minv, in, base, out);
+void launch_coarse_hop_inv_odd(const CGeom& cg, const void* D, const cx<R>* Minv, const cx<R>* in, const cx<R>* base,
+                               cx<R>* out, hipStream_t st) {
+  const int nodd = cg.nsites - cg.neven;
+  auto Dp = (const typename store_traits<S>::elem*)D;
+  if (one_site(nodd, cg.n))
+    hipLaunchKernelGGL((k_coarse_hop_inv_odd_site<R, S>), dim3(nodd), dim3(SITE_T), 0, st, cg, Dp, Minv, in, base, out);
+  else
+    hipLaunchKernelGGL((k_coarse_hop_inv_odd<R, S>), dim3((nodd + 3) / 4), dim3(256), 0, st, cg, Dp, Minv, in, base,
+                       out);
 }
 
 // even sites: mode 0: out = (S + i tw G5) v - hop(t);  mode 1: out = v - hop(t)
@@ -746,8 +928,13 @@ __global__ void __launch_bounds__(256) k_coarse_schur_even(CGeom cg,
 template <class R, class S>
 void launch_coarse_schur_even(const CGeom& cg, const void* D, double tw, const cx<R>* v, const cx<R>* t, cx<R>* out,
                               int mode, hipStream_t st) {
-  hipLaunchKernelGGL((k_coarse_schur_even<R, S>), dim3((cg.neven + 3) / 4), dim3(256), 0, st, cg,
-                     (const typename store_traits<S>::elem*)D, (R)tw, v, t, out, mode);
+  auto Dp = (const typename store_traits<S>::elem*)D;
+  if (one_site(cg.neven, cg.n))
+    hipLaunchKernelGGL((k_coarse_schur_even_site<R, S>), dim3(cg.neven), dim3(SITE_T), 0, st, cg, Dp, (R)tw, v, t, out,
+                       mode);
+  else
+    hipLaunchKernelGGL((k_coarse_schur_even<R, S>), dim3((cg.neven + 3) / 4), dim3(256), 0, st, cg, Dp, (R)tw, v, t,
+                       out, mode);
 }
 
 // ---------------------------------------------------------------------------
@@ -759,10 +946,8 @@ void launch_coarse_schur_even(const CGeom& cg, const void* D, double tw, const c
                                         const cx<R>*, cx<R>*, int, hipStream_t);                                  \
   template void launch_coarse_sap_multi<R, S>(const CGeom&, const void*, double, int, int, const int*,            \
                                               const int*, const cx<R>*, cx<R>*, int, int, long, hipStream_t);     \
-  template void launch_coarse_hop_inv_odd<R, S>(const CGeom&, const void*, const cx<R>*, const cx<R>*, cx<R>*,    \
-                                                int, hipStream_t);                                                \
-  template void launch_coarse_hop_inv_odd_base<R, S>(const CGeom&, const void*, const cx<R>*, const cx<R>*,       \
-                                                     const cx<R>*, cx<R>*, hipStream_t);                          \
+  template void launch_coarse_hop_inv_odd<R, S>(const CGeom&, const void*, const cx<R>*, const cx<R>*,            \
+                                                const cx<R>*, cx<R>*, hipStream_t);                               \
   template void launch_coarse_schur_even<R, S>(const CGeom&, const void*, double, const cx<R>*, const cx<R>*,     \
                                                cx<R>*, int, hipStream_t);
 INST_RS(double, double)

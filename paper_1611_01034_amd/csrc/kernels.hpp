@@ -159,11 +159,8 @@ void launch_coarse_odd_inverse(const CGeom& cg, const cx<double>* D, double tw, 
                                hipStream_t st);
 // odd-even Schur pieces on the coarsest level
 template <class R, class S>
-void launch_coarse_hop_inv_odd(const CGeom& cg, const void* D, const cx<R>* Minv, const cx<R>* in, cx<R>* out,
-                               int unused, hipStream_t st);
-template <class R, class S>
-void launch_coarse_hop_inv_odd_base(const CGeom& cg, const void* D, const cx<R>* Minv, const cx<R>* in,
-                                    const cx<R>* base, cx<R>* out, hipStream_t st);
+void launch_coarse_hop_inv_odd(const CGeom& cg, const void* D, const cx<R>* Minv, const cx<R>* in, const cx<R>* base,
+                               cx<R>* out, hipStream_t st);
 template <class R, class S>
 void launch_coarse_schur_even(const CGeom& cg, const void* D, double tw, const cx<R>* v, const cx<R>* t, cx<R>* out,
                               int mode, hipStream_t st);
@@ -213,8 +210,7 @@ template <class R>
 void launch_zero(long N, cx<R>* x, hipStream_t st);
 void launch_givens(cx<double>* H, int ldh, double* cs, cx<double>* sn, cx<double>* g, int j, double* resid,
                    hipStream_t st);
-void launch_trisolve(const cx<double>* H, int ldh, const cx<double>* g, cx<double>* y, int j, hipStream_t st);
-void launch_set_scalar(cx<double>* dst, const cx<double>* src_norm2_sqrt, hipStream_t st);
+void launch_trisolve(const cx<double>* H, int ldh, int m, const cx<double>* g, cx<double>* y, int j, hipStream_t st);
 
 // column-batched Krylov kernels (K columns, column r = blockIdx.y; act: per-column
 // mask or null; cs*: column strides of vectors and scalar arrays)
@@ -256,11 +252,12 @@ template <class R>
 inline bool cgs_two_pass(int m) {
   return sizeof(R) == 8 && m > 8;
 }
+// sums64: per-thread sums and updates of FP32 vectors in FP64
 template <class R>
 void launch_cgs_step(const cx<R>* V, long ldv, long csV, int k, cx<R>* w, long csw, long N, cx<double>* pa,
                      cx<double>* pb, long pcs, int nwg, cx<double>* hcol, long hcs, cx<double>* H, int ldh, int m,
                      double* cs, cx<double>* sn, cx<double>* g, int j, double* resid, double* resid_host, int K,
-                     const int* act, hipStream_t st);
+                     const int* act, bool sums64, hipStream_t st);
 void launch_givens_b(cx<double>* H, int ldh, int m, double* cs, cx<double>* sn, cx<double>* g, int j, double* resid,
                      int K, const int* act, hipStream_t st);
 void launch_trisolve_b(const cx<double>* H, int ldh, int m, const cx<double>* g, cx<double>* y, const int* jd, int K,

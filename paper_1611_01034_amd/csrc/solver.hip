@@ -270,6 +270,16 @@ static double sap_sweep_bytes(const Geom& g, int K) {
 }
 
 // ---------------------------------------------------------------------------
+// workgroups per column of the fused Arnoldi step: about one element per
+// thread of an FP32 vector (at most 128 workgroups, so every workgroup's
+// prologue sums few partials), four per thread of an FP64 one (at most 1024)
+template <class R>
+static int cgs_nwg(long N) {
+  const long per = sizeof(R) == 4 ? cgs_block_size<R>() : 4L * cgs_block_size<R>();
+  const long cap = sizeof(R) == 4 ? 256 : 1024;
+  return (int)std::min<long>(cap, std::max<long>(1, (N + per - 1) / per));
+}
+
 template <class R>
 void KrylovWS<R>::init(int m_, long ld_, long N, bool flex) {
   m = m_;
@@ -284,10 +294,12 @@ void KrylovWS<R>::init(int m_, long ld_, long N, bool flex) {
   g.ensure(sizeof(cx<double>) * (m + 1));
   y.ensure(sizeof(cx<double>) * (m + 1));
   nwg = (int)std::min<long>(1024, std::max<long>(1, (N + 255) / 256));
-  part.ensure(sizeof(cx<double>) * (size_t)nwg * (m + 1));
+  nwgf = cgs_nwg<R>(N);
+  part.ensure(sizeof(cx<double>) * (size_t)std::max(nwg, nwgf) * (m + 1) * 2);  // two halves for the fused step
   scal.ensure(sizeof(cx<double>) * 4);
   resid.ensure(sizeof(double));
-  if (!h_resid) HIP_CHECK(hipHostMalloc((void**)&h_resid, sizeof(double) * 4, hipHostMallocDefault));
+  // coherent: the Arnoldi kernels store residual estimates here directly
+  if (!h_resid) HIP_CHECK(hipHostMalloc((void**)&h_resid, sizeof(double) * 4, hipHostMallocCoherent));
   for (auto& e : ready)
     if (!e) HIP_CHECK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
 }
@@ -307,13 +319,18 @@ KrylovResult fgmres(Ctx& c, KrylovWS<R>& ws, long N, const std::function<void(co
   hipStream_t st = c.st;
   const int m = ws.m;
   const long ld = ws.ld;
-  int nwg = (int)std::min<long>(ws.nwg, std::max<long>(1, (N + 255) / 256));
+  const int ldh = m + 1;
+  const int nwg = (int)std::min<long>(ws.nwg, std::max<long>(1, (N + 255) / 256));
+  const int nwgf = std::min(ws.nwgf, cgs_nwg<R>(N));
+  const long pcs = (long)std::max(ws.nwg, ws.nwgf) * ldh;
   cx<R>* V = ws.V.template as<cx<R>>();
   cx<R>* Z = M ? ws.Z.template as<cx<R>>() : V;
   cx<R>* r = ws.tmp.template as<cx<R>>();
   cx<double>* H = ws.H.template as<cx<double>>();
   cx<double>* scal = ws.scal.template as<cx<double>>();
   cx<double>* part = ws.part.template as<cx<double>>();
+  cx<double>* g = ws.g.template as<cx<double>>();
+  cx<double>* y = ws.y.template as<cx<double>>();
   auto norm_to = [&](const cx<R>* v, cx<double>* dst) {
     launch_multidot<R>(v, 0, 1, v, N, part, nwg, st);
     launch_reduce(part, 1, nwg, dst, 2, st);
@@ -324,30 +341,31 @@ KrylovResult fgmres(Ctx& c, KrylovWS<R>& ws, long N, const std::function<void(co
     return ws.h_resid[0];
   };
   KrylovResult res;
-  norm_to(b, scal);
-  double bnorm = read(scal);
+  norm_to(b, scal + 1);
+  const double bnorm = read(scal + 1);
   if (bnorm == 0.0) {
     launch_zero<R>(N, x, st);
     res.converged = true;
     return res;
   }
+  const cx<R>* r0 = r;  // residual of the cycle to start
+  double beta = bnorm;
   if (x_is_zero) {
     launch_zero<R>(N, x, st);
-    launch_copy_cvt<R, R>(b, r, N, st);
+    r0 = b;
   } else {
     A(x, r);
     launch_sub<R>(N, b, r, r, st);
+    norm_to(r, scal + 1);
+    beta = read(scal + 1);
   }
-  norm_to(r, scal + 1);
-  double beta = read(scal + 1);
   int it = 0;
   while (true) {
     if (!fixed && beta <= tol * bnorm) break;
     if (it >= max_iter) break;
     int mm = fixed ? std::min(m, max_iter - it) : m;
-    launch_scale_by_inv<R>(r, scal + 1, V, N, st);
-    launch_zero<double>(m + 1, ws.g.template as<cx<double>>(), st);
-    launch_set_scalar(ws.g.template as<cx<double>>(), scal + 1, st);
+    launch_scale_by_inv<R>(r0, scal + 1, V, N, st);
+    launch_init_g_b(g, ldh, scal + 1, 1, 1, nullptr, st);
     int jd = 0;
     // Without a preconditioner an iteration is cheap, so the convergence test
     // of iteration j is taken while iteration j+1 is already queued (no idle
@@ -365,25 +383,36 @@ KrylovResult fgmres(Ctx& c, KrylovWS<R>& ws, long N, const std::function<void(co
         (*M)(Vj, z);
       }
       A(z, Vn);
-      cx<double>* hcol = H + (long)j * (m + 1);
-      launch_multidot<R>(V, ld, j + 1, Vn, N, part, nwg, st);
-      launch_reduce(part, j + 1, nwg, hcol, 0, st);
-      launch_multi_axpy<R>(V, ld, j + 1, hcol, -1.0, Vn, N, st);
-      if (cgs_two_pass<R>(m)) {  // second classical Gram-Schmidt pass
+      cx<double>* hcol = H + (long)j * ldh;
+      // where the residual estimate lands on the host (nowhere if nobody reads it)
+      double* host = fixed ? nullptr : lookahead ? ws.h_resid + 2 + (j & 1) : ws.h_resid;
+      if (j + 1 <= 32) {
+        // one column of the lock-step Arnoldi step, its sums in FP64: three or
+        // four launches instead of nine or thirteen, and the estimate goes
+        // straight to its pinned slot
+        launch_cgs_step<R>(V, ld, 0, j + 1, Vn, 0, N, part, part + pcs, pcs, nwgf, hcol, 0, H, ldh, m,
+                           ws.cs.template as<double>(), ws.sn.template as<cx<double>>(), g, j,
+                           ws.resid.template as<double>(), host, 1, nullptr, true, st);
+      } else {
         launch_multidot<R>(V, ld, j + 1, Vn, N, part, nwg, st);
-        launch_reduce(part, j + 1, nwg, ws.y.template as<cx<double>>(), 0, st);
-        launch_reduce(part, j + 1, nwg, hcol, 1, st);
-        launch_multi_axpy<R>(V, ld, j + 1, ws.y.template as<cx<double>>(), -1.0, Vn, N, st);
+        launch_reduce(part, j + 1, nwg, hcol, 0, st);
+        launch_multi_axpy<R>(V, ld, j + 1, hcol, -1.0, Vn, N, st);
+        if (cgs_two_pass<R>(m)) {  // second classical Gram-Schmidt pass
+          launch_multidot<R>(V, ld, j + 1, Vn, N, part, nwg, st);
+          launch_reduce(part, j + 1, nwg, y, 0, st);
+          launch_reduce(part, j + 1, nwg, hcol, 1, st);
+          launch_multi_axpy<R>(V, ld, j + 1, y, -1.0, Vn, N, st);
+        }
+        norm_to(Vn, hcol + j + 1);
+        launch_scale_by_inv<R>(Vn, hcol + j + 1, Vn, N, st);
+        launch_givens(H, ldh, ws.cs.template as<double>(), ws.sn.template as<cx<double>>(), g, j,
+                      ws.resid.template as<double>(), st);
+        if (host) HIP_CHECK(hipMemcpyAsync(host, ws.resid.p, sizeof(double), hipMemcpyDeviceToHost, st));
       }
-      norm_to(Vn, hcol + j + 1);
-      launch_scale_by_inv<R>(Vn, hcol + j + 1, Vn, N, st);
-      launch_givens(H, m + 1, ws.cs.template as<double>(), ws.sn.template as<cx<double>>(), ws.g.template as<cx<double>>(), j,
-                    ws.resid.template as<double>(), st);
       ++it;
       jd = j + 1;
       if (lookahead) {
         const int k = j & 1;
-        HIP_CHECK(hipMemcpyAsync(ws.h_resid + 2 + k, ws.resid.p, sizeof(double), hipMemcpyDeviceToHost, st));
         HIP_CHECK(hipEventRecord(ws.ready[k], st));
         if (pending) {
           HIP_CHECK(hipEventSynchronize(ws.ready[k ^ 1]));
@@ -396,8 +425,8 @@ KrylovResult fgmres(Ctx& c, KrylovWS<R>& ws, long N, const std::function<void(co
         }
         pending = true;
       } else if (!fixed) {
-        double est = read(ws.resid.p);
-        if (est <= tol * bnorm) break;
+        HIP_CHECK(hipStreamSynchronize(st));
+        if (ws.h_resid[0] <= tol * bnorm) break;
       }
       if (it >= max_iter) break;
     }
@@ -405,12 +434,13 @@ KrylovResult fgmres(Ctx& c, KrylovWS<R>& ws, long N, const std::function<void(co
       HIP_CHECK(hipEventSynchronize(ws.ready[(jd - 1) & 1]));
       pending = false;
     }
-    launch_trisolve(H, m + 1, ws.g.template as<cx<double>>(), ws.y.template as<cx<double>>(), jd, st);
-    launch_multi_axpy<R>(Z, ld, jd, ws.y.template as<cx<double>>(), 1.0, x, N, st);
+    launch_trisolve(H, ldh, m, g, y, jd, st);
+    launch_multi_axpy<R>(Z, ld, jd, y, 1.0, x, N, st);
     A(x, r);
     launch_sub<R>(N, b, r, r, st);
     norm_to(r, scal + 1);
     beta = read(scal + 1);
+    r0 = r;
     if (fixed && it >= max_iter) break;
     if (beta == 0.0) break;
   }
@@ -426,16 +456,6 @@ KrylovResult fgmres(Ctx& c, KrylovWS<R>& ws, long N, const std::function<void(co
 // meets its tolerance drops out of the reductions and its next basis vector is
 // zeroed, so nested solves see a zero right-hand side for it.  The iterates are
 // those of K separate solves in exact arithmetic.
-// workgroups per column of the fused Arnoldi step: about one element per
-// thread of an FP32 vector (at most 128 workgroups, so every workgroup's
-// prologue sums few partials), four per thread of an FP64 one (at most 1024)
-template <class R>
-static int cgs_nwg(long N) {
-  const long per = sizeof(R) == 4 ? cgs_block_size<R>() : 4L * cgs_block_size<R>();
-  const long cap = sizeof(R) == 4 ? 256 : 1024;
-  return (int)std::min<long>(cap, std::max<long>(1, (N + per - 1) / per));
-}
-
 template <class R>
 void KrylovWSm<R>::init(int m_, int K_, long ld_, long N, bool flex, bool z_fp32, bool transient) {
   m = m_;
@@ -597,7 +617,7 @@ KrylovResultM fgmres_multi(Ctx& c, KrylovWSm<R>& ws, int K, long N, const OpM<R>
         launch_cgs_step<R>(V, (long)K * ld, ld, j + 1, Vn, ld, N, part, part + (long)K * pcs, pcs, nwgf, hcol, hcs, H,
                            ldh, m, ws.cs.template as<double>(), ws.sn.template as<cx<double>>(), g, j,
                            ws.resid.template as<double>(), lookahead ? ws.h_resid + 32 * (j % NSLOT) : nullptr, K,
-                           act, st);
+                           act, false, st);
       } else {
         launch_multidot_b<R>(V, (long)K * ld, ld, j + 1, Vn, ld, N, part, pcs, nwg, K, act, st);
         launch_reduce_b(part, pcs, j + 1, nwg, hcol, hcs, 0, K, act, st);
@@ -1023,7 +1043,7 @@ struct MG : MGBase {
         cx<R>* t = wk[l][0].template as<cx<R>>();
         Aop[l] = [this, cg, l, t](const cx<R>* in, cx<R>* out) {
           TimeScope ts(c.timer, 5);
-          launch_coarse_hop_inv_odd<R, S>(cg, Dst(l), Minvc.template as<cx<R>>(), in, t, 0, c.st);
+          launch_coarse_hop_inv_odd<R, S>(cg, Dst(l), Minvc.template as<cx<R>>(), in, nullptr, t, c.st);
           launch_coarse_schur_even<R, S>(cg, Dst(l), tw[l], in, t, out, 0, c.st);
         };
       } else {
@@ -1180,7 +1200,7 @@ struct MG : MGBase {
       kr = fgmres<R>(c, kws[l], (long)G.neven * G.n, Aop[l], nullptr, rhs, x, p.coarse_tol, p.coarse_max_iter,
                      p.fixed_iters != 0, true);
       // x_o = D_oo^{-1} (b_o - D_oe x_e)
-      launch_coarse_hop_inv_odd_base<R, S>(cg, Dst(l), Minvc.template as<cx<R>>(), x, b, x, c.st);
+      launch_coarse_hop_inv_odd<R, S>(cg, Dst(l), Minvc.template as<cx<R>>(), x, b, x, c.st);
     } else {
       kr = fgmres<R>(c, kws[l], (long)G.nsites * G.n, Aop[l], &Mop[l], b, x, p.inter_tol, p.inter_max_iter,
                      p.fixed_iters != 0, true);
@@ -1242,8 +1262,8 @@ struct MG : MGBase {
             }
           }
           for (int k = 0; k < K_; ++k) {
-            launch_coarse_hop_inv_odd<R, S>(cg, Dst(l), Minvc.template as<cx<R>>(), in + k * len, t + k * len, 0,
-                                            c.st);
+            launch_coarse_hop_inv_odd<R, S>(cg, Dst(l), Minvc.template as<cx<R>>(), in + k * len, nullptr,
+                                            t + k * len, c.st);
             launch_coarse_schur_even<R, S>(cg, Dst(l), tw[l], in + k * len, t + k * len, out + k * len, 0, c.st);
           }
         };
@@ -1296,7 +1316,7 @@ struct MG : MGBase {
       }
       if (!done)
         for (int k = 0; k < K; ++k)
-          launch_coarse_hop_inv_odd_base<R, S>(cg, Dst(l), Minvc.template as<cx<R>>(), x + k * len, b + k * len,
+          launch_coarse_hop_inv_odd<R, S>(cg, Dst(l), Minvc.template as<cx<R>>(), x + k * len, b + k * len,
                                                x + k * len, c.st);
     } else {
       kr = fgmres_multi<R>(c, kwsm[l], K, len, AopM[l], &MopM[l], b, x, p.inter_tol, p.inter_max_iter,

@@ -138,6 +138,7 @@ struct KrylovWS {
   double* h_resid = nullptr;  // pinned host mirror: [0] blocking reads, [2 + k] look-ahead slot k
   hipEvent_t ready[2] = {nullptr, nullptr};  // look-ahead: residual estimate k has reached h_resid[2 + k]
   int nwg = 0;
+  int nwgf = 0;                  // workgroups of the fused Arnoldi step
   void init(int m_, long ld_, long N, bool flex);
   ~KrylovWS();
 };

@@ -45,3 +45,68 @@ def test_columns_alone_and_among_sixteen(dims, nv, prec):
                 for k in range(K):
                     d = np.linalg.norm(got[k] - many[k]) / np.linalg.norm(many[k])
                     assert d <= tol, (name, K, k, d)
+
+
+def _round(x, prec):
+    """Stored operator entries, rounded once to nearest even."""
+    if prec == "fp64":
+        return x
+    if prec in ("fp32", "fp16"):
+        t = np.float32 if prec == "fp32" else np.float16
+        return x.real.astype(t).astype(np.float64) + 1j * x.imag.astype(t).astype(np.float64)
+
+    def f(v):
+        m, e = np.frexp(v)
+        return np.ldexp(np.round(m * 256.0) / 256.0, e)
+    return f(x.real) + 1j * f(x.imag)
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "fp16", "bf16"])
+@pytest.mark.parametrize("nv", [1, 4, 5, 9, 13, 16, 17, 26, 32])
+def test_single_column_operators_of_any_width(nv, prec):
+    """One workgroup per site (n = 2 .. 64: every split of the inner index, rows
+    that 16-byte loads divide and rows that they do not) and, for n <= 24 on
+    1536 sites, four sites per workgroup: D_c y and the odd-even operator
+    against FP64 sums over the stored blocks.  FP64 1e-12; FP32 arithmetic 1e-5
+    of the norm (9 n products of 2^-24 each; the odd-site inverse is held in
+    FP32 and applied once more).  The odd-even operator of 16-bit storage runs
+    here where n is no multiple of 16."""
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    from paper_1611_01034_amd import ddamg, synth
+    block = (2, 2, 2, 2)
+    for dims in ((8, 8, 4, 4), (8, 8, 16, 24)) if nv <= 9 else ((8, 8, 4, 4),):
+        with ddamg.DDAMG(dims, block, KAPPA, CSW, MU) as ctx:
+            ctx.set_gauge(synth.gauge_field(dims, 0.3, 9301))
+            p = ddamg.default_params(levels=2, block=[block], nvec=[nv], coarse_mu_factor=5.0, precision=prec)
+            ctx.set_test_vectors(p, [synth.spinor(dims, 9302, nvec=nv)])
+            cd, n = ctx.level_info(1)
+            print(f"single column: {dims} n {n} {prec}", flush=True)
+            S, F = (_round(a, prec) for a in ctx.get_coarse_op(1))
+            y = synth.gaussian(cd + (n,), 9303)
+            g = np.where(np.arange(n) < n // 2, -1.0, 1.0)
+            tw = 5.0 * MU
+
+            def hop(v):
+                out = np.zeros_like(v)
+                for mu in range(4):
+                    out += (F[mu] @ np.roll(v, -1, axis=mu)[..., None])[..., 0]
+                    Fb = np.conj(np.swapaxes(np.roll(F[mu], 1, axis=mu), -1, -2))
+                    out += g * (Fb @ (g * np.roll(v, 1, axis=mu))[..., None])[..., 0]
+                return out
+
+            def site(v):
+                return (S @ v[..., None])[..., 0] + 1j * tw * g * v
+
+            tol = 1e-12 if prec == "fp64" else 1e-5
+            want = site(y) + hop(y)
+            got = ctx.apply_coarse(1, y)
+            assert np.linalg.norm(got - want) <= tol * np.linalg.norm(want)
+            if prec in ("fp16", "bf16") and n % 16 == 0:
+                continue  # the K-column kernels, tested above
+            par = np.indices(cd).sum(axis=0)[..., None] % 2
+            Sd, _ = ctx.get_coarse_op(1)  # the inverse is that of the FP64 block
+            u = np.linalg.solve(Sd + 1j * tw * np.diag(g), (par * hop((1 - par) * y))[..., None])[..., 0]
+            want = (1 - par) * (site((1 - par) * y) - hop(u))
+            got = ctx.apply_coarse_schur_multi(1, y[None])[0]
+            assert np.linalg.norm(got - want) <= tol * np.linalg.norm(want)
