@@ -397,16 +397,17 @@ int ddamg_timing_query(ddamg_ctx* ctx, int kind, long* count, double* ms);
 /* Algorithmic bytes of the launches timed so far of a kind, each datum moved
  * once per launch: kind 0, 1536 bytes per site (spinor in and out, links,
  * clover in FP64); kind 1, per site of the swept colour the links (36
- * entries of the storage format), the clover term and the odd-site inverse
- * factors (108 reals on average) once, and per field b, x in, x out and the
- * other colour's x (48 complex); other kinds report 0.  bytes / (ms 1e-3) is
- * the achieved rate. */
+ * entries of the storage format), the clover term and the odd-site inverses
+ * (144 FP32 reals on average, 108 in FP64) once, and per field b, x in, x out
+ * and the other colour's x (48 complex); other kinds report 0.
+ * bytes / (ms 1e-3) is the achieved rate. */
 int ddamg_timing_bytes(ddamg_ctx* ctx, int kind, double* bytes);
 /* Real floating-point operations of the launches timed so far of a kind (a
  * complex multiply-add counts 8): kind 1, per site of the swept colour and
- * field 4932 + 2604 n_MR (the residual, the odd-site solves, the first rho,
+ * field 4452 + 2364 n_MR (the residual, the odd-site solves, the first rho,
  * n_MR MR steps on the even-site Schur complement and the odd-site
- * correction; 15348 at n_MR = 4); other kinds report 0. */
+ * correction; 13908 at n_MR = 4) in FP32, 4932 + 2604 n_MR in FP64, whose
+ * odd-site solves are two Hermitian products; other kinds report 0. */
 int ddamg_timing_flops(ddamg_ctx* ctx, int kind, double* flops);
 
 /* ---- learned setup (not a method of the paper: it replaces the random start

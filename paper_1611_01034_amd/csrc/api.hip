@@ -737,13 +737,13 @@ int ddamg_sap_multi(ddamg_ctx* ctx, int nfields, const void* b, void* x, int ite
       for (int it = 0; it < iters; ++it)
         for (int col = 0; col < 2; ++col) {
           if (precision == DDAMG_FP32)
-            launch_sap_multi<float, float>(c.g, col, U, c.H32.as<float>(), c.M32.as<float>(), c.twist(),
+            launch_sap_multi<float, float>(c.g, col, U, c.H32.as<float>(), c.T32.as<float>(), c.twist(),
                                            b32.as<cx<float>>(), x32.as<cx<float>>(), mr_steps, K, N, c.st);
           else if (precision == DDAMG_FP16)
-            launch_sap_multi<float, f16>(c.g, col, U, c.H32.as<float>(), c.M32.as<float>(), c.twist(),
+            launch_sap_multi<float, f16>(c.g, col, U, c.H32.as<float>(), c.T32.as<float>(), c.twist(),
                                          b32.as<cx<float>>(), x32.as<cx<float>>(), mr_steps, K, N, c.st);
           else
-            launch_sap_multi<float, bf16>(c.g, col, U, c.H32.as<float>(), c.M32.as<float>(), c.twist(),
+            launch_sap_multi<float, bf16>(c.g, col, U, c.H32.as<float>(), c.T32.as<float>(), c.twist(),
                                           b32.as<cx<float>>(), x32.as<cx<float>>(), mr_steps, K, N, c.st);
         }
       c.download_fields(x32.as<cx<float>>(), x, on_device, K);

@@ -110,12 +110,12 @@ __device__ __forceinline__ void hop_lex_dir(const typename store_traits<S>::elem
   nbr_of(g, me, MU, +1, Bn, sn);
   const bool hi = me.l[MU] == g.b[MU] - 1 && me.bc[MU] == g.nb[MU] - 1;
   load_nbr_lex(in, lds, B, Bn, sn, hi ? lex - wrap : lex + str, psi);
-  load_link<R, S>(U, g, B, s, MU, u);
+  load_link_t<MU, R, S>(U, g, B, s, u);
   hop_accum_t<0, MU>(psi, u, out);
   nbr_of(g, me, MU, -1, Bn, sn);
   const bool lo = me.l[MU] == 0 && me.bc[MU] == 0;
   load_nbr_lex(in, lds, B, Bn, sn, lo ? lex + wrap : lex - str, psi);
-  load_link<R, S>(U, g, Bn, sn, MU, u);
+  load_link_t<MU, R, S>(U, g, Bn, sn, u);
   hop_accum_t<1, MU>(psi, u, out);
 }
 

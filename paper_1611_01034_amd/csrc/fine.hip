@@ -62,46 +62,119 @@ __device__ __forceinline__ BlockNbr block_nbrs(const Geom& g, const SiteNbr& me)
   return nb;
 }
 
+// The block solve's fields in LDS: entry idx of component pair p at p * hs + idx,
+// so that a site is six 16-byte (FP32) accesses of consecutive entries.
+template <class R>
+struct alignas(4 * sizeof(R)) cxpair {
+  cx<R> a, b;
+};
+template <class R, bool NEG = false>
+__device__ __forceinline__ void pair_get(const cxpair<R>* f, int hs, int idx, cx<R> v[12]) {
+#pragma unroll
+  for (int p = 0; p < 6; ++p) {
+    const cxpair<R> q = f[p * hs + idx];
+    v[2 * p] = NEG ? -q.a : q.a;
+    v[2 * p + 1] = NEG ? -q.b : q.b;
+  }
+}
+template <class R>
+__device__ __forceinline__ void pair_put(cxpair<R>* f, int hs, int idx, const cx<R> v[12]) {
+#pragma unroll
+  for (int p = 0; p < 6; ++p) f[p * hs + idx] = cxpair<R>{v[2 * p], v[2 * p + 1]};
+}
+
+// the links of direction MU's two in-block hops at a slot; a dropped backward hop
+// reads a link of the block, multiplied by the zero spinor
+template <int MU, class S>
+__device__ __forceinline__ void hop_block_load(const typename store_traits<S>::elem* U, const Geom& g, int B,
+                                               long site_s, BlockNbr nb, int noff, RawLink<S>& cf, RawLink<S>& cb) {
+  const int sb = (nb.w[MU >> 1] >> (16 * (MU & 1) + 8)) & 255;
+  load_raw<S>(U, site_s, MU, cf);
+  load_raw<S>(U, link_site<S>(g, B, min(sb, g.half - 1) + noff), MU, cb);
+}
+template <int MU, class R, class S, bool SUB>
+__device__ __forceinline__ void hop_block_dir(const RawLink<S>& cf, const RawLink<S>& cb, const cxpair<R>* lds,
+                                              int hs, BlockNbr nb, cx<R> out[12]) {
+  const unsigned wd = nb.w[MU >> 1] >> (16 * (MU & 1));
+  const int sf = wd & 255, sb = (wd >> 8) & 255;
+  cx<R> psi[12], u[9];
+  unpack_link<MU, R, S>(cf, u);
+  pair_get<R, SUB>(lds, hs, sf, psi);
+  hop_accum_t<0, MU>(psi, u, out);
+  unpack_link<MU, R, S>(cb, u);
+  pair_get<R, SUB>(lds, hs, sb, psi);
+  hop_accum_t<1, MU>(psi, u, out);
+}
 // out += (or -= with SUB) the in-block hops of slot s, the neighbours' spinors
-// read from lds (12 x hs, component-major, the other parity's half of the
-// block; entry `half` of every component is zero).  noff: slot offset of the
-// neighbours' parity (their links are read for the backward hops).  Both links
-// of a direction are loaded before its arithmetic (one memory latency per
-// direction); a dropped backward hop reads a link of the block, multiplied by
-// the zero spinor.
-template <class R, class S, bool SUB = false>
+// read from lds (the other parity's half of the block; entry `half` of every
+// pair is zero).  noff: slot offset of the neighbours' parity (their links are
+// read for the backward hops).  `last`: loads to issue before the last
+// direction multiplies.
+template <class R, class S, bool SUB = false, class F>
 __device__ __forceinline__ void hop_block_lds(const typename store_traits<S>::elem* U, const Geom& g, int B, int s,
-                                              BlockNbr nb, int noff, const cx<R>* lds, int hs, cx<R> out[12]) {
-  using E = typename store_traits<S>::elem;
+                                              BlockNbr nb, int noff, const cxpair<R>* lds, int hs, cx<R> out[12],
+                                              F last) {
   // opaque per call: nothing derived from the neighbour words or the slot is
   // kept live across the MR steps
   __asm__ volatile("" : "+v"(nb.w[0]), "+v"(nb.w[1]), "+v"(s));
-  const long blk = (long)B * (g.bs / TILE) * 36 * TILE;
-  const long base_s = blk + (long)(s / TILE) * 36 * TILE + (s % TILE);
-#pragma unroll 1
-  for (int mu = 0; mu < 4; ++mu) {
-    const unsigned wd = (mu < 2 ? nb.w[0] : nb.w[1]) >> (16 * (mu & 1));
-    const int sf = wd & 255, sb = (wd >> 8) & 255;
-    const int lb = min(sb, g.half - 1) + noff;
-    const long bf = base_s + (long)mu * 9 * TILE;
-    const long bb = blk + (long)(lb / TILE) * 36 * TILE + (lb % TILE) + (long)mu * 9 * TILE;
-    E cf[9], cb[9];
+  const long site_s = link_site<S>(g, B, s);
+  RawLink<S> cf, cb, nf, nn;
+  hop_block_load<0, S>(U, g, B, site_s, nb, noff, cf, cb);
+  // the links of the next direction are in flight while this one multiplies; the
+  // scheduling barriers keep the later directions' loads from being hoisted
+  hop_block_load<1, S>(U, g, B, site_s, nb, noff, nf, nn);
+  __builtin_amdgcn_sched_barrier(0);
+  hop_block_dir<0, R, S, SUB>(cf, cb, lds, hs, nb, out);
+  __builtin_amdgcn_sched_barrier(0);
+  hop_block_load<2, S>(U, g, B, site_s, nb, noff, cf, cb);
+  __builtin_amdgcn_sched_barrier(0);
+  hop_block_dir<1, R, S, SUB>(nf, nn, lds, hs, nb, out);
+  __builtin_amdgcn_sched_barrier(0);
+  hop_block_load<3, S>(U, g, B, site_s, nb, noff, nf, nn);
+  __builtin_amdgcn_sched_barrier(0);
+  hop_block_dir<2, R, S, SUB>(cf, cb, lds, hs, nb, out);
+  __builtin_amdgcn_sched_barrier(0);
+  last();
+  __builtin_amdgcn_sched_barrier(0);
+  hop_block_dir<3, R, S, SUB>(nf, nn, lds, hs, nb, out);
+}
+template <class R, class S, bool SUB = false>
+__device__ __forceinline__ void hop_block_lds(const typename store_traits<S>::elem* U, const Geom& g, int B, int s,
+                                              BlockNbr nb, int noff, const cxpair<R>* lds, int hs, cx<R> out[12]) {
+  hop_block_lds<R, S, SUB>(U, g, B, s, nb, noff, lds, hs, out, [] {});
+}
+
+// w = T_oo^{-1} (in-block hops of the other parity's field in lds) at odd slot s.
+// FP32: the rows of T_oo^{-1} are loaded three ahead of their products, the first
+// during the last direction of the hops.
+template <class R, class S>
+__device__ __forceinline__ void hop_inv_block(const typename store_traits<S>::elem* U, const R* H, const R* Minv,
+                                              const Geom& g, int B, int s, TwistR<R> tw, BlockNbr nb,
+                                              const cxpair<R>* lds, int hs, cx<R> w[12]) {
+  cx<R> u[12];
 #pragma unroll
-    for (int k = 0; k < 9; ++k) {
-      cf[k] = U[bf + (long)k * TILE];
-      cb[k] = U[bb + (long)k * TILE];
-    }
-    cx<R> psi[12], u[9];
-#pragma unroll
-    for (int k = 0; k < 9; ++k) u[k] = mk<R>((R)cf[k].re, (R)cf[k].im);
-#pragma unroll
-    for (int c = 0; c < 12; ++c) psi[c] = SUB ? -lds[c * hs + sf] : lds[c * hs + sf];
-    hop_accum<0>(mu, psi, u, out);
-#pragma unroll
-    for (int k = 0; k < 9; ++k) u[k] = mk<R>((R)cb[k].re, (R)cb[k].im);
-#pragma unroll
-    for (int c = 0; c < 12; ++c) psi[c] = SUB ? -lds[c * hs + sb] : lds[c * hs + sb];
-    hop_accum<1>(mu, psi, u, out);
+  for (int c = 0; c < 12; ++c) u[c] = mk<R>(0, 0);
+  if constexpr (sizeof(R) == 8) {
+    hop_block_lds<R, S>(U, g, B, s, nb, 0, lds, hs, u);
+    site_inv(H, Minv, g, B, s, tw, u, w);
+  } else {
+    const int io = s - g.half, tl = io % TILE;
+    const long tt = (long)B * (g.half / TILE) + io / TILE;
+    TinvRows a, b;
+    hop_block_lds<R, S>(U, g, B, s, nb, 0, lds, hs, u, [&] { tinv_load(Minv, tt, tl, 0, a); });
+    __builtin_amdgcn_sched_barrier(0);
+    tinv_load(Minv, tt, tl, 1, b);
+    __builtin_amdgcn_sched_barrier(0);
+    tinv_mv(a, 0, u, w);
+    __builtin_amdgcn_sched_barrier(0);
+    tinv_load(Minv, tt, tl, 2, a);
+    __builtin_amdgcn_sched_barrier(0);
+    tinv_mv(b, 1, u, w);
+    __builtin_amdgcn_sched_barrier(0);
+    tinv_load(Minv, tt, tl, 3, b);
+    __builtin_amdgcn_sched_barrier(0);
+    tinv_mv(a, 2, u, w);
+    tinv_mv(b, 3, u, w);
   }
 }
 
@@ -115,6 +188,16 @@ __device__ __forceinline__ void hop_block_lds(const typename store_traits<S>::el
 //   x_o -= T_oo^{-1} D_oe e_e  (together: x_o += T_oo^{-1} (r_o - D_oe e_e)).
 // x of a block is read and written by its own workgroup only: the residual
 // reads the other colour's blocks, which this sweep leaves unchanged.
+// Bound by the vector units (at 48x24^3, six fields, 16-bit links, 4 MR steps
+// they issue in about 85 % of the cycles of two wavefronts per SIMD; the links,
+// clover and inverses of a block come from L2 after the first MR step), so the
+// levers are fewer instructions and no idle issue slots: unrolled directions with
+// compile-time spin projections, T_oo^{-1} as one product, 16-byte loads and LDS
+// accesses, each direction's links and each third of T_oo^{-1}'s rows loaded
+// while the one before multiplies.  1042 -> 769 us a sweep there, 105 -> 84 us
+// with one field and FP32 links at 24x16x16x24, 79 -> 57 us on 8x8x8x16.  All
+// 256 registers are in use: with 168 (three wavefronts per SIMD) the sweeps take
+// 1086 and 129 us, and two threads for each pair of slots spill at any count.
 template <class R, class S>
 __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(sizeof(R) == 8 ? 1 : 2, 8)))
 k_sap(Geom g, int colour, const typename store_traits<S>::elem* __restrict__ U, const R* __restrict__ H,
@@ -122,11 +205,12 @@ k_sap(Geom g, int colour, const typename store_traits<S>::elem* __restrict__ U, 
       long ld) {
   extern __shared__ char smem_raw[];
   // the residual stages x of the block parity-split (24 x half); the block
-  // solve then keeps one field per parity as 12 x hs (hs = half + 1: entry
-  // half of each component is the zero spinor of dropped hops)
+  // solve then keeps one field per parity as 6 pairs x hs (hs = half + 1: entry
+  // half is the zero spinor of dropped hops)
   const int hs = g.half + 1;
-  cx<R>* ev = reinterpret_cast<cx<R>*>(smem_raw);  // 12 x hs, even slots
-  cx<R>* od = ev + 12 * hs;                         // 12 x hs, odd slots
+  cx<R>* xs = reinterpret_cast<cx<R>*>(smem_raw);
+  cxpair<R>* ev = reinterpret_cast<cxpair<R>*>(smem_raw);  // even slots
+  cxpair<R>* od = ev + 6 * hs;                              // odd slots
   __shared__ double red[2][3][2];                    // per-wavefront sums, by MR step parity
   int B;
   {
@@ -155,17 +239,17 @@ k_sap(Geom g, int colour, const typename store_traits<S>::elem* __restrict__ U, 
     cx<R> psi[12], ro[12];
     load_spinor(x, g, B, se, psi);
 #pragma unroll
-    for (int c = 0; c < 12; ++c) *lds_site(ev, g, se, c) = psi[c];
+    for (int c = 0; c < 12; ++c) *lds_site(xs, g, se, c) = psi[c];
     site_term(H, g, B, se, tw, psi, rho);
     __asm__ volatile("" ::: "memory");
     load_spinor(x, g, B, so, psi);
 #pragma unroll
-    for (int c = 0; c < 12; ++c) *lds_site(ev, g, so, c) = psi[c];
+    for (int c = 0; c < 12; ++c) *lds_site(xs, g, so, c) = psi[c];
     site_term(H, g, B, so, tw, psi, ro);
     __syncthreads();
-    hop_staged<R, S>(U, x, ev, g, B, se, me_e, rho);
+    hop_staged<R, S>(U, x, xs, g, B, se, me_e, rho);
     __asm__ volatile("" ::: "memory");
-    hop_staged<R, S>(U, x, ev, g, B, so, me_o, ro);
+    hop_staged<R, S>(U, x, xs, g, B, so, me_o, ro);
     load_spinor(b, g, B, se, psi);
 #pragma unroll
     for (int c = 0; c < 12; ++c) rho[c] = psi[c] - rho[c];
@@ -176,13 +260,11 @@ k_sap(Geom g, int colour, const typename store_traits<S>::elem* __restrict__ U, 
     __asm__ volatile("" ::: "memory");
     site_inv(H, Minv, g, B, so, tw, ro, tmp);
     load_spinor(x, g, B, so, psi);
+    pair_put(od, hs, i, tmp);
 #pragma unroll
-    for (int c = 0; c < 12; ++c) {
-      od[c * hs + i] = tmp[c];
-      psi[c] += tmp[c];
-    }
+    for (int c = 0; c < 12; ++c) psi[c] += tmp[c];
     store_spinor(x, g, B, so, psi);
-    for (int e = i; e < 24; e += g.half) (e < 12 ? ev : od)[(e % 12) * hs + g.half] = mk<R>(0, 0);
+    for (int e = i; e < 12; e += g.half) ev[e * hs + g.half] = cxpair<R>{mk<R>(0, 0), mk<R>(0, 0)};  // od follows ev
   }
   const BlockNbr nb_e = block_nbrs(g, me_e), nb_o = block_nbrs(g, me_o);
   __syncthreads();
@@ -190,28 +272,26 @@ k_sap(Geom g, int colour, const typename store_traits<S>::elem* __restrict__ U, 
 #pragma unroll
   for (int c = 0; c < 12; ++c) ee[c] = mk<R>(0, 0);
   const int nact = min(64, g.half - wv * 64);
+  pair_put(ev, hs, i, rho);
   for (int k = 0; k < n_mr; ++k) {
     // the block operator is re-read in every step: keeping the loop-invariant
-    // links, clover and inverses in registers would exceed the register file
+    // links, clover and inverses in registers would exceed the register file;
+    // rho lives in LDS, where the neighbours read it anyway
     __asm__ volatile("" ::: "memory");
-#pragma unroll
-    for (int c = 0; c < 12; ++c) ev[c * hs + i] = rho[c];
     __syncthreads();
-    {  // w = T_oo^{-1} D_oe rho
-      cx<R> u[12];
-#pragma unroll
-      for (int c = 0; c < 12; ++c) u[c] = mk<R>(0, 0);
-      hop_block_lds<R, S>(U, g, B, so, nb_o, 0, ev, hs, u);
-      site_inv(H, Minv, g, B, so, tw, u, tmp);
-#pragma unroll
-      for (int c = 0; c < 12; ++c) od[c * hs + i] = tmp[c];
-    }
+    // w = T_oo^{-1} D_oe rho
+    hop_inv_block<R, S>(U, H, Minv, g, B, so, tw, nb_o, ev, hs, tmp);
+    pair_put(od, hs, i, tmp);
     __syncthreads();
     __asm__ volatile("" ::: "memory");
     // q = T_ee rho - D_eo w
+    pair_get(ev, hs, i, rho);
     site_term(H, g, B, se, tw, rho, tmp);
+    __asm__ volatile("" ::: "memory");
     hop_block_lds<R, S, true>(U, g, B, se, nb_e, g.half, od, hs, tmp);
     double qr_re = 0, qr_im = 0, qq = 0;
+    __asm__ volatile("" ::: "memory");
+    pair_get(ev, hs, i, rho);
 #pragma unroll
     for (int c = 0; c < 12; ++c) {
       qr_re += (double)tmp[c].re * rho[c].re + (double)tmp[c].im * rho[c].im;
@@ -240,16 +320,13 @@ k_sap(Geom g, int colour, const typename store_traits<S>::elem* __restrict__ U, 
       ee[c] += alpha * rho[c];
       rho[c] -= alpha * tmp[c];
     }
+    pair_put(ev, hs, i, rho);
   }
-#pragma unroll
-  for (int c = 0; c < 12; ++c) ev[c * hs + i] = ee[c];
+  pair_put(ev, hs, i, ee);
   __syncthreads();
   {  // x_o -= T_oo^{-1} D_oe e_e
     cx<R> u[12];
-#pragma unroll
-    for (int c = 0; c < 12; ++c) u[c] = mk<R>(0, 0);
-    hop_block_lds<R, S>(U, g, B, so, nb_o, 0, ev, hs, u);
-    site_inv(H, Minv, g, B, so, tw, u, tmp);
+    hop_inv_block<R, S>(U, H, Minv, g, B, so, tw, nb_o, ev, hs, tmp);
     load_spinor(x, g, B, so, u);
 #pragma unroll
     for (int c = 0; c < 12; ++c) u[c] -= tmp[c];
@@ -1271,12 +1348,69 @@ template void launch_cvt_cx<float>(long, const cx<double>*, void*, hipStream_t);
 template void launch_cvt_cx<f16>(long, const cx<double>*, void*, hipStream_t);
 template void launch_cvt_cx<bf16>(long, const cx<double>*, void*, hipStream_t);
 
-__global__ void k_cvt_real(long n, const double* __restrict__ in, float* __restrict__ out) {
-  long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) out[i] = (float)in[i];
+// FP64 operator fields -> copies in 16-byte chunks: nt tiles of 8 sites, per site
+// 36 complex link entries in 16 bits or (k_chunk_real) 72 reals in FP32
+template <class S>
+__global__ void k_chunk_links(long nt, const cx<double>* __restrict__ in,
+                              typename store_traits<S>::elem* __restrict__ out) {
+  const long gid = (long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (gid >= nt * 36 * TILE) return;
+  const int lane = (int)(gid % TILE), k = (int)(gid / TILE % 36);
+  const long tile = gid / (36 * TILE);
+  out[((tile * LC + (k >> 2)) * TILE + lane) * 4 + (k & 3)] = st_cvt<S, double>(in[gid]);
 }
-void launch_cvt_real(long n, const double* in, float* out, hipStream_t st) {
-  hipLaunchKernelGGL(k_cvt_real, dim3((n + 255) / 256), dim3(256), 0, st, n, in, out);
+template <class S>
+void launch_chunk_links(long nt, const cx<double>* in, void* out, hipStream_t st) {
+  hipLaunchKernelGGL(k_chunk_links<S>, dim3((unsigned)((nt * 36 * TILE + 255) / 256)), dim3(256), 0, st, nt, in,
+                     (typename store_traits<S>::elem*)out);
+}
+template void launch_chunk_links<f16>(long, const cx<double>*, void*, hipStream_t);
+template void launch_chunk_links<bf16>(long, const cx<double>*, void*, hipStream_t);
+
+__global__ void k_chunk_real(long nt, const double* __restrict__ in, float* __restrict__ out) {
+  const long gid = (long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (gid >= nt * 72 * TILE) return;
+  const int lane = (int)(gid % TILE), k = (int)(gid / TILE % 72);
+  const long tile = gid / (72 * TILE);
+  out[((tile * HC + (k >> 2)) * TILE + lane) * 4 + (k & 3)] = (float)in[gid];
+}
+// T^{-1} = (H + i tw) M on chirality 0, (H - i tw) M on chirality 1 of every odd
+// site, from the FP64 H and M; one thread per (odd site, row of 12)
+__global__ void k_chunk_tinv(Geom g, const double* __restrict__ H, const double* __restrict__ M, double tw,
+                             float* __restrict__ out) {
+  const long gid = (long)blockIdx.x * blockDim.x + threadIdx.x;
+  const int lane = (int)(gid % TILE), i12 = (int)(gid / TILE % 12);
+  const long tile = gid / (12 * TILE);  // tile of odd sites
+  if (tile >= (long)g.nblocks * (g.half / TILE)) return;
+  const int b = i12 / 6, i = i12 - 6 * b;
+  const int B = (int)(tile / (g.half / TILE)), io = (int)(tile % (g.half / TILE)) * TILE + lane;
+  const double* h = H + fidx(g, B, g.half + io, 72) + 36L * b * TILE;
+  const double* m = M + oidx(g, B, io, 72) + 36L * b * TILE;
+  auto get = [](const double* p, int r, int c) {
+    if (r == c) return mk(p[(long)r * TILE], 0.0);
+    const int k = 6 + 2 * (r < c ? herm_idx(r, c) : herm_idx(c, r));
+    return mk(p[(long)k * TILE], r < c ? p[(long)(k + 1) * TILE] : -p[(long)(k + 1) * TILE]);
+  };
+  for (int j = 0; j < 6; ++j) {
+    cx<double> acc = mk(0.0, 0.0);
+    for (int k = 0; k < 6; ++k) {
+      cx<double> a = get(h, i, k);
+      if (k == i) a.im += b == 0 ? tw : -tw;
+      cmac(acc, a, get(m, k, j));
+    }
+    const int w = i12 * 12 + 2 * j;  // word of the real part
+    float* o = out + ((tile * TC + (w >> 2)) * TILE + lane) * 4 + (w & 3);
+    o[0] = (float)acc.re;
+    o[1] = (float)acc.im;
+  }
+}
+void launch_chunk_tinv(const Geom& g, const double* H, const double* M, double tw, float* out, hipStream_t st) {
+  const long n = (long)g.nblocks * g.half * 12;
+  hipLaunchKernelGGL(k_chunk_tinv, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, g, H, M, tw, out);
+}
+
+void launch_chunk_real(long nt, const double* in, float* out, hipStream_t st) {
+  hipLaunchKernelGGL(k_chunk_real, dim3((unsigned)((nt * 72 * TILE + 255) / 256)), dim3(256), 0, st, nt, in, out);
 }
 
 // ---------------------------------------------------------------------------

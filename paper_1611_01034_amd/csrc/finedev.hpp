@@ -71,12 +71,60 @@ __device__ __forceinline__ void hop_accum(int mu, const cx<R> psi[12], const cx<
   }
 }
 
+// The 9 entries of one link as loaded, converted later: 16-bit links as the
+// three chunks that hold direction mu's nine words (they begin at word mu of
+// the site's chunk 2 mu), others as the entries themselves.
+template <class S, bool CH = link_in_chunks<S>>
+struct RawLink {
+  typename store_traits<S>::elem c[9];
+};
+template <class S>
+struct RawLink<S, true> {
+  chunk16 c[3];
+};
+// offset of slot s of block B in a link field: chunks, or entries
+template <class S>
+__device__ __forceinline__ long link_site(const Geom& g, int B, int s) {
+  return fidx(g, B, s, link_in_chunks<S> ? LC : 36);
+}
+template <class S>
+__device__ __forceinline__ void load_raw(const typename store_traits<S>::elem* U, long site, int mu, RawLink<S>& r) {
+  if constexpr (link_in_chunks<S>) {
+    const chunk16* p = reinterpret_cast<const chunk16*>(U) + site + (long)(2 * mu) * TILE;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) r.c[k] = p[k * TILE];
+  } else {
+    const typename store_traits<S>::elem* p = U + site + (long)mu * 9 * TILE;
+#pragma unroll
+    for (int k = 0; k < 9; ++k) r.c[k] = p[k * TILE];
+  }
+}
+template <int MU, class R, class S>
+__device__ __forceinline__ void unpack_link(const RawLink<S>& r, cx<R> u[9]) {
+#pragma unroll
+  for (int k = 0; k < 9; ++k) {
+    if constexpr (link_in_chunks<S>) {
+      const auto e = __builtin_bit_cast(typename store_traits<S>::elem, r.c[(MU + k) >> 2].w[(MU + k) & 3]);
+      u[k] = mk<R>((R)e.re, (R)e.im);
+    } else {
+      u[k] = mk<R>((R)r.c[k].re, (R)r.c[k].im);
+    }
+  }
+}
+template <int MU, class R, class S>
+__device__ __forceinline__ void load_link_t(const typename store_traits<S>::elem* U, const Geom& g, int B, int s,
+                                            cx<R> u[9]) {
+  RawLink<S> r;
+  load_raw<S>(U, link_site<S>(g, B, s), MU, r);
+  unpack_link<MU, R, S>(r, u);
+}
 template <class R, class S>
 __device__ __forceinline__ void load_link(const typename store_traits<S>::elem* U, const Geom& g, int B, int s, int mu,
                                           cx<R> u[9]) {
-  long base = fidx(g, B, s, 36) + (long)mu * 9 * TILE;
-#pragma unroll
-  for (int k = 0; k < 9; ++k) u[k] = ld<R, S>(U, base + (long)k * TILE);
+  static_assert(!link_in_chunks<S>, "a chunked link is unpacked for a direction known at compile time");
+  RawLink<S> r;
+  load_raw<S>(U, link_site<S>(g, B, s), mu, r);
+  unpack_link<0, R, S>(r, u);
 }
 
 template <class R>
@@ -114,14 +162,38 @@ __device__ __forceinline__ void herm_mv(const R* hp, long stride, const cx<R> x[
     }
 }
 
+// both chirality blocks of the packed Hermitian matrix of site `lane` of tile
+// `tile`: FP64 in the tiled layout, FP32 in 16-byte chunks (9 per block)
+__device__ __forceinline__ void herm_apply(const double* H, long tile, int lane, const cx<double> x[12],
+                                           cx<double> y[12]) {
+  const double* p = H + tile * 72 * TILE + lane;
+  herm_mv(p, TILE, x, y);
+  herm_mv(p + 36L * TILE, TILE, x + 6, y + 6);
+}
+__device__ __forceinline__ void herm_apply(const float* H, long tile, int lane, const cx<float> x[12],
+                                           cx<float> y[12]) {
+  const float4* p = reinterpret_cast<const float4*>(H) + tile * HC * TILE + lane;
+#pragma unroll
+  for (int b = 0; b < 2; ++b) {
+    float h[36];
+#pragma unroll
+    for (int c = 0; c < 9; ++c) {
+      const float4 v = p[(9 * b + c) * TILE];
+      h[4 * c] = v.x;
+      h[4 * c + 1] = v.y;
+      h[4 * c + 2] = v.z;
+      h[4 * c + 3] = v.w;
+    }
+    herm_mv(h, 1, x + 6 * b, y + 6 * b);
+  }
+}
+
 // T psi at (B,s): (m0+4+A) psi + i tw gamma5 psi, tw the twist of the slot's parity
 template <class R>
 __device__ __forceinline__ void site_term(const R* H, const Geom& g, int B, int s, TwistR<R> twp,
                                           const cx<R> psi[12], cx<R> out[12]) {
   const R tw = s < g.half ? twp.e : twp.o;
-  const R* hp = H + fidx(g, B, s, 72);
-  herm_mv(hp, TILE, psi, out);
-  herm_mv(hp + 36L * TILE, TILE, psi + 6, out + 6);
+  herm_apply(H, (long)B * (g.bs / TILE) + s / TILE, s % TILE, psi, out);
 #pragma unroll
   for (int c = 0; c < 6; ++c) {
     out[c] += tw * times_mi(psi[c]);
@@ -129,24 +201,58 @@ __device__ __forceinline__ void site_term(const R* H, const Geom& g, int B, int 
   }
 }
 
-// T^{-1} psi on an odd slot: per chirality (H -+ i tw) M psi with M = (H^2+tw^2)^{-1}
-// (H is Hermitian, so (H + i a)^{-1} = (H - i a)(H^2 + a^2)^{-1}); chirality 0 has
-// the twist -i tw, chirality 1 +i tw.
-template <class R>
-__device__ __forceinline__ void site_inv(const R* H, const R* Minv, const Geom& g, int B, int s, TwistR<R> twp,
-                                         const cx<R> psi[12], cx<R> out[12]) {
-  const R tw = twp.o;
-  const R* hp = H + fidx(g, B, s, 72);
-  const R* mp = Minv + oidx(g, B, s - g.half, 72);
-  cx<R> t[12];
-  herm_mv(mp, TILE, psi, t);
-  herm_mv(mp + 36L * TILE, TILE, psi + 6, t + 6);
-  herm_mv(hp, TILE, t, out);
-  herm_mv(hp + 36L * TILE, TILE, t + 6, out + 6);
+// T^{-1} psi on an odd slot.  FP64: per chirality (H -+ i tw) M psi with
+// M = (H^2+tw^2)^{-1} (H is Hermitian, so (H + i a)^{-1} = (H - i a)(H^2 + a^2)^{-1});
+// chirality 0 has the twist -i tw, chirality 1 +i tw.
+__device__ __forceinline__ void site_inv(const double* H, const double* Minv, const Geom& g, int B, int s,
+                                         TwistR<double> twp, const cx<double> psi[12], cx<double> out[12]) {
+  const double tw = twp.o;
+  const int io = s - g.half;
+  cx<double> t[12];
+  herm_apply(Minv, (long)B * (g.half / TILE) + io / TILE, io % TILE, psi, t);
+  herm_apply(H, (long)B * (g.bs / TILE) + s / TILE, s % TILE, t, out);
 #pragma unroll
   for (int c = 0; c < 6; ++c) {
     out[c] += tw * times_i(t[c]);
     out[6 + c] += tw * times_mi(t[6 + c]);
+  }
+}
+// FP32: the product (H -+ i tw) M itself, formed in FP64 and rounded once: the
+// same bytes as H and M, a little over half of the multiply-adds.  Three rows
+// of a chirality block (9 chunks) at a time.
+struct TinvRows {
+  float h[36];
+};
+__device__ __forceinline__ void tinv_load(const float* Tinv, long tile, int lane, int q, TinvRows& r) {
+  const float4* p = reinterpret_cast<const float4*>(Tinv) + (tile * TC + 9 * q) * TILE + lane;
+#pragma unroll
+  for (int c = 0; c < 9; ++c) {
+    const float4 v = p[c * TILE];
+    r.h[4 * c] = v.x;
+    r.h[4 * c + 1] = v.y;
+    r.h[4 * c + 2] = v.z;
+    r.h[4 * c + 3] = v.w;
+  }
+}
+// rows 3q..3q+2 of the 12: y_i = sum_j T_ij x_j over the chirality block of q
+__device__ __forceinline__ void tinv_mv(const TinvRows& r, int q, const cx<float> x[12], cx<float> y[12]) {
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    cx<float> acc = mk<float>(0, 0);
+#pragma unroll
+    for (int j = 0; j < 6; ++j)
+      cmac(acc, mk<float>(r.h[12 * i + 2 * j], r.h[12 * i + 2 * j + 1]), x[6 * (q >> 1) + j]);
+    y[3 * q + i] = acc;
+  }
+}
+__device__ __forceinline__ void site_inv(const float*, const float* Tinv, const Geom& g, int B, int s, TwistR<float>,
+                                         const cx<float> psi[12], cx<float> out[12]) {
+  const int io = s - g.half;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    TinvRows r;
+    tinv_load(Tinv, (long)B * (g.half / TILE) + io / TILE, io % TILE, q, r);
+    tinv_mv(r, q, psi, out);
   }
 }
 
@@ -200,11 +306,11 @@ __device__ __forceinline__ void hop_staged_dir(const typename store_traits<S>::e
   int Bn, sn;
   nbr_of(g, me, MU, +1, Bn, sn);
   load_nbr_staged(in, lds, g, B, Bn, sn, psi);
-  load_link<R, S>(U, g, B, s, MU, u);
+  load_link_t<MU, R, S>(U, g, B, s, u);
   hop_accum_t<0, MU>(psi, u, out);
   nbr_of(g, me, MU, -1, Bn, sn);
   load_nbr_staged(in, lds, g, B, Bn, sn, psi);
-  load_link<R, S>(U, g, Bn, sn, MU, u);
+  load_link_t<MU, R, S>(U, g, Bn, sn, u);
   hop_accum_t<1, MU>(psi, u, out);
 }
 

@@ -114,7 +114,13 @@ void launch_assemble_fine(const Geom& g, int Nv, const cx<double>* U, const doub
                           long qstride, const int* f2c, cx<double>* Dc, cx<double>* Xs, hipStream_t st);
 template <class S>
 void launch_cvt_cx(long n, const cx<double>* in, void* out, hipStream_t st);
-void launch_cvt_real(long n, const double* in, float* out, hipStream_t st);
+// operator copies in 16-byte chunks, nt tiles of 8 sites: 16-bit links; 72 FP32
+// reals per site
+template <class S>
+void launch_chunk_links(long nt, const cx<double>* in, void* out, hipStream_t st);
+void launch_chunk_real(long nt, const double* in, float* out, hipStream_t st);
+// the odd sites' T^{-1} for twist tw, from H and M = (H^2 + tw^2)^{-1}
+void launch_chunk_tinv(const Geom& g, const double* H, const double* M, double tw, float* out, hipStream_t st);
 
 // -------------------------------------------------------------- coarse levels
 // D_c blocks: [site][5][n][n] column-major (self without twist, forward T,Z,Y,X)

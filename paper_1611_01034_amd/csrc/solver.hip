@@ -251,20 +251,23 @@ struct TimeScope {
 // on half of the sites each: T_oo^-1 r_o with x_o += t_o (1056 + 24), the
 // first rho (hops), per MR step w = T_oo^-1 D_oe rho and q = T_ee rho - D_eo w
 // with the dots and updates (5208 per pair), and the closing correction (hops,
-// T_oo^-1, two updates: 2736 per pair).
+// T_oo^-1, two updates: 2736 per pair).  In FP32 T_oo^-1 is one dense product
+// (two 6x6 blocks, 576): 480 fewer in each of its n_mr + 2 applications.
+template <class R>
 static double sap_sweep_flops(const Geom& g, int K, int n_mr) {
-  const double per_site = 4932.0 + 2604.0 * n_mr;
+  const double per_site = 4932.0 + 2604.0 * n_mr - (sizeof(R) == 4 ? 240.0 * (n_mr + 2) : 0.0);
   return 0.5 * (double)g.V * K * per_site;
 }
 
 // Algorithmic bytes of one fine SAP colour sweep of K fields (each datum
 // moved once): per site of the swept colour the links (36 entries of the
 // storage format), the clover term (72 reals) and, on odd sites, the inverse
-// factors (72 reals, 36 per site on average) once for all fields; per field
-// b, x read and written, and x of the other colour read once for the residual.
+// (72 reals in FP64, 144 in FP32) once for all fields; per field b, x read and
+// written, and x of the other colour read once for the residual.
 template <class R, class S>
 static double sap_sweep_bytes(const Geom& g, int K) {
-  const double shared = 36.0 * sizeof(typename store_traits<S>::elem) + 108.0 * sizeof(R);
+  const double shared =
+      36.0 * sizeof(typename store_traits<S>::elem) + (sizeof(R) == 4 ? 144.0 : 108.0) * sizeof(R);
   const double field = 4.0 * 12 * sizeof(cx<R>);
   return 0.5 * (double)g.V * (shared + K * field);
 }
@@ -731,23 +734,23 @@ void Ctx::ensure_32() {
   if (have_32) return;
   U32.ensure(sizeof(cx<float>) * (size_t)g.V * 36);
   H32.ensure(sizeof(float) * (size_t)g.V * 72);
-  M32.ensure(sizeof(float) * (size_t)g.V * 36);
+  T32.ensure(sizeof(float) * (size_t)g.V * 72);
   launch_cvt_cx<float>((long)g.V * 36, U64.as<cx<double>>(), U32.p, st);
-  launch_cvt_real((long)g.V * 72, H64.as<double>(), H32.as<float>(), st);
-  launch_cvt_real((long)g.V * 36, M64.as<double>(), M32.as<float>(), st);
+  launch_chunk_real(g.V / TILE, H64.as<double>(), H32.as<float>(), st);
+  launch_chunk_tinv(g, H64.as<double>(), M64.as<double>(), mu_odd, T32.as<float>(), st);
   have_32 = true;
 }
 void Ctx::ensure_16(int kind) {
   ensure_32();
   if (u16_kind == kind) return;
   U16.ensure(4 * (size_t)g.V * 36);
-  if (kind == DDAMG_FP16) launch_cvt_cx<f16>((long)g.V * 36, U64.as<cx<double>>(), U16.p, st);
-  else launch_cvt_cx<bf16>((long)g.V * 36, U64.as<cx<double>>(), U16.p, st);
+  if (kind == DDAMG_FP16) launch_chunk_links<f16>(g.V / TILE, U64.as<cx<double>>(), U16.p, st);
+  else launch_chunk_links<bf16>(g.V / TILE, U64.as<cx<double>>(), U16.p, st);
   u16_kind = kind;
 }
 void Ctx::rebuild_odd_inverse() {
   launch_odd_inverse(g, H64.as<double>(), mu_odd, M64.as<double>(), st);
-  if (have_32) launch_cvt_real((long)g.V * 36, M64.as<double>(), M32.as<float>(), st);
+  if (have_32) launch_chunk_tinv(g, H64.as<double>(), M64.as<double>(), mu_odd, T32.as<float>(), st);
 }
 void Ctx::dirac64(const cx<double>* in, cx<double>* out, Twist tw) { dirac64_multi(in, out, 1, 0, tw); }
 void Ctx::dirac64_multi(const cx<double>* in, cx<double>* out, int K, long ld, Twist tw) {
@@ -1001,7 +1004,7 @@ struct MG : MGBase {
         U = c.U16.p;
       }
       Hf = c.H32.template as<float>();
-      Mf = c.M32.template as<float>();
+      Mf = c.T32.template as<float>();
     }
     set_twists(c.twist());
     // allocations
@@ -1082,7 +1085,7 @@ struct MG : MGBase {
   void fine_sap(const cx<R>* b, cx<R>* x, int iters, int nmr) {
     for (int it = 0; it < iters; ++it)
       for (int col = 0; col < 2; ++col) {
-        TimeScope ts(c.timer, 1, sap_sweep_bytes<R, S>(c.g, 1), sap_sweep_flops(c.g, 1, nmr));
+        TimeScope ts(c.timer, 1, sap_sweep_bytes<R, S>(c.g, 1), sap_sweep_flops<R>(c.g, 1, nmr));
         launch_sap<R, S>(c.g, col, U, Hf, Mf, tw0, b, x, nmr, c.st);
       }
   }
@@ -1090,7 +1093,7 @@ struct MG : MGBase {
   void fine_sap_m(const cx<R>* b, cx<R>* x, int K, int iters, int nmr) {
     for (int it = 0; it < iters; ++it)
       for (int col = 0; col < 2; ++col) {
-        TimeScope ts(c.timer, 1, sap_sweep_bytes<R, S>(c.g, K), sap_sweep_flops(c.g, K, nmr));
+        TimeScope ts(c.timer, 1, sap_sweep_bytes<R, S>(c.g, K), sap_sweep_flops<R>(c.g, K, nmr));
         launch_sap_multi<R, S>(c.g, col, U, Hf, Mf, tw0, b, x, nmr, K, c.fine_len(), c.st);
       }
   }

@@ -297,7 +297,7 @@ struct Ctx {
   double theta[4] = {0, 0, 0, 0};  // twisted boundary conditions (0: periodic)
   bool have_gauge = false, have_setup = false;
   DevBuf U64, H64, M64;        // fine operator, FP64
-  DevBuf U32, H32, M32;        // FP32 copies
+  DevBuf U32, H32, T32;        // FP32 copies (T32: the odd sites' T^{-1})
   DevBuf U16;                  // 16-bit link copy
   int u16_kind = -1;           // DDAMG_FP16 or DDAMG_BF16
   bool have_32 = false;

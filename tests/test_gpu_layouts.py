@@ -162,3 +162,30 @@ def test_layout_conversions_of_several_fields(dd, dims, block, prec):
                     assert np.linalg.norm(host[k].reshape(want.shape) - want) <= 1e-11 * np.linalg.norm(want)
     finally:
         ctx.close()
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp16", "bf16"])
+@pytest.mark.parametrize("dims,block", [((4, 4, 4, 4), (2, 2, 2, 2)), ((4, 12, 4, 12), (2, 6, 2, 6)),
+                                        ((8, 4, 12, 8), (4, 2, 6, 4))])
+def test_reduced_precision_sap_after_twist_changes(dd, dims, block, prec):
+    """The FP32 odd-site inverses follow the odd sites' twist: sweeps at the
+    first twist, at different twists on the two parities and at a negative one,
+    each within 1e-5 of the oracle on links rounded the same way (the FP32 SAP
+    bar of the parity tests)."""
+    from oracle import dirac, sap, stencil
+    from paper_1611_01034_amd import synth
+    ctx, U, _ = _case(dd, dims, block, 8501)
+    try:
+        print(f"sap after twist changes: {dims} {block} {prec}", flush=True)
+        Ur = U.astype(np.complex64).astype(np.complex128) if prec == "fp32" else _round_links(U, prec)
+        # the clover term comes from the links as given
+        A = dirac.clover_blocks(dirac.WilsonClover(U, KAPPA, CSW, 0.0).A)
+        b, x0 = synth.spinor(dims, 8502), synth.spinor(dims, 8503)
+        for mu, mu_odd in ((MU, MU), (0.3, -0.45), (-0.2, -0.2)):
+            ctx.set_mu(mu) if mu == mu_odd else ctx.set_mu_eo(mu, mu_odd)
+            got = ctx.sap(b, x0, iters=2, mr_steps=3, precision=prec)
+            op = dirac.WilsonClover(Ur, KAPPA, CSW, mu, clover=A, mu_odd=mu_odd)
+            want = sap.sap(stencil.FineLevel(op), b.reshape(dims + (12,)), x0.reshape(dims + (12,)), block, 3, 2)
+            assert np.linalg.norm(got.reshape(want.shape) - want) <= 1e-5 * np.linalg.norm(want), (mu, mu_odd)
+    finally:
+        ctx.close()
