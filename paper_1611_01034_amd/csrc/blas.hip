@@ -426,12 +426,23 @@ void launch_zero_b(long N, cx<R>* x, long cs, int K, hipStream_t st) {
 
 // Givens step j of one column: apply the previous rotations to Hessenberg
 // column j (h = H + j*ldh), form rotation j, update g and the residual estimate.
-__device__ void givens_col(cx<double>* h, double* c_, cx<double>* s_, cx<double>* g_, int j, double* resid) {
+// The carried entry stays in registers and nothing stored here is read again, so
+// the loads of later rotations are not held back by the stores (k_cgs_scale_givens
+// on average 4.4 -> 4.0 us, with the rotations beside the sum of the partials).
+__device__ __forceinline__ void givens_prev(cx<double>* __restrict__ h, const double* __restrict__ c_,
+                                            const cx<double>* __restrict__ s_, int j) {
+  cx<double> a = h[0];
+#pragma unroll 4
   for (int i = 0; i < j; ++i) {
-    cx<double> a = h[i], b = h[i + 1];
-    h[i] = c_[i] * a + s_[i] * b;
-    h[i + 1] = c_[i] * b - conj(s_[i]) * a;
+    const double c = c_[i];
+    const cx<double> s = s_[i], b = h[i + 1];
+    h[i] = c * a + s * b;
+    a = c * b - conj(s) * a;
   }
+  h[j] = a;
+}
+__device__ __forceinline__ void givens_new(cx<double>* h, double* c_, cx<double>* s_, cx<double>* g_, int j,
+                                           double* resid) {
   cx<double> a = h[j], b = h[j + 1];
   double den = sqrt(norm2(a) + norm2(b));
   double c;
@@ -455,6 +466,10 @@ __device__ void givens_col(cx<double>* h, double* c_, cx<double>* s_, cx<double>
   g_[j + 1] = -(conj(s) * gj);
   g_[j] = c * gj;
   *resid = sqrt(norm2(g_[j + 1]));
+}
+__device__ void givens_col(cx<double>* h, double* c_, cx<double>* s_, cx<double>* g_, int j, double* resid) {
+  givens_prev(h, c_, s_, j);
+  givens_new(h, c_, s_, g_, j, resid);
 }
 
 // Givens step j of every active column: thread r handles column r.  Scalar
@@ -551,7 +566,8 @@ void launch_init_g_b(cx<double>* g, int ldh, const cx<double>* s, long scs, int 
 // ---------------------------------------------------------------------------
 // Classical Gram-Schmidt, norm and Givens step of K lock-step Arnoldi
 // processes: two Gram-Schmidt passes (four launches) or one (three launches),
-// as cgs_two_pass decides from the vector type and the cycle length.
+// as cgs_two_pass decides from the vector type and the cycle length; one launch
+// for short FP32 columns (k_cgs_column).
 // Grid (nwg, K), column r = blockIdx.y; inactive
 // columns return at once (the last launch zeroes their next basis vector).
 // Every workgroup stores per-workgroup partial sums; the next launch begins by
@@ -609,9 +625,10 @@ __device__ __forceinline__ void reduce_partials(const double* partd, int nval, i
 }
 }  // namespace
 
-// Per-thread sums and the updates w -= sum_i c_i V_i are in A (lock-step columns
-// in FP32: FP32 with the coefficients rounded to it; one column: FP64), every
-// sum across threads in FP64 from the wavefront totals on.
+// The updates w -= sum_i c_i V_i and the norm's per-thread sums are in A (lock-step
+// columns in FP32: FP32 with the coefficients rounded to it; one column: FP64), the
+// dots of FP32 vectors in FP64, every sum across threads in FP64 from the wavefront
+// totals on.
 // pa_r: partials of V_{r,i}^H w_r  (i < k)
 template <class R, class A, int KM, int BS>
 __global__ void __launch_bounds__(BS) k_cgs_dot(const cx<R>* __restrict__ V, long ldv, long csV, int k,
@@ -637,6 +654,50 @@ __global__ void __launch_bounds__(BS) k_cgs_dot(const cx<R>* __restrict__ V, lon
     }
   }
   store_partials<KP, BS / 64>(acc, 2 * k, pa + 2 * r * pcs);
+}
+
+// The same for FP32 vectors, bound by latency (a coarsest column has 500 to 80,000
+// entries): the basis vectors are spread over the wavefronts.  Wavefront q takes vectors q, q + 8, ... (NV of them) on chunks of 256 entries, four to a
+// lane, its sums in FP64.  A wavefront ends with 2 NV values to add over its lanes
+// instead of 2 k, and its totals are the workgroup's: no LDS and no barrier.  At
+// k = 24: 10.3 -> 4.0 us for one column of 512 entries, 11.9 -> 4.8 us for six
+// of 8192, 13.0 -> 6.5 us for six of 12,288.
+constexpr int DOT_CHUNK = 256;
+template <int NV>
+__global__ void __launch_bounds__(512) k_cgs_dot_waves(const cx<float>* __restrict__ V, long ldv, long csV, int k,
+                                                       const cx<float>* __restrict__ w, long csw, long N, double* pa,
+                                                       long pcs, const int* act) {
+  const int r = blockIdx.y;
+  if (act && !act[r]) return;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (wv >= k) return;
+  V += r * csV;
+  w += r * csw;
+  constexpr int NP = cgs_pow2(NV);
+  double acc[2 * NP];
+#pragma unroll
+  for (int q = 0; q < 2 * NP; ++q) acc[q] = 0.0;
+  for (long c0 = (long)blockIdx.x * DOT_CHUNK; c0 < N; c0 += (long)gridDim.x * DOT_CHUNK) {
+    cx<float> x[4], v[NV][4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const long e = c0 + 64 * q + lane, ec = e < N ? e : N - 1;
+      x[q] = w[ec];
+      if (e >= N) x[q] = mk<float>(0, 0);
+#pragma unroll
+      for (int u = 0; u < NV; ++u) v[u][q] = V[(long)min(wv + 8 * u, k - 1) * ldv + ec];  // sums past k unused
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int u = 0; u < NV; ++u) {
+        acc[2 * u] += (double)v[u][q].re * x[q].re + (double)v[u][q].im * x[q].im;
+        acc[2 * u + 1] += (double)v[u][q].re * x[q].im - (double)v[u][q].im * x[q].re;
+      }
+  }
+  const double tot = wave_transpose_sum<2 * NP>(acc, lane);
+  const int i = wv + 8 * (lane >> 1);
+  if (lane < 2 * NV && i < k) (pa + 2 * r * pcs)[2 * ((long)i * gridDim.x + blockIdx.x) + (lane & 1)] = tot;
 }
 
 // h_r = sum of pa_r (workgroup 0 stores it in hcol_r);  w_r -= sum_i h_r[i] V_{r,i};
@@ -695,6 +756,23 @@ __global__ void __launch_bounds__(BS) k_cgs_axpy_norm(const cx<R>* __restrict__ 
   w += r * csw;
   __shared__ double cf[2 * KM];
   __shared__ cx<A> cfr[KM];
+  const long stride = (long)gridDim.x * BS;
+  long e = (long)blockIdx.x * BS + threadIdx.x;
+  // FP32: the first entries, usually the only ones, are in flight while the
+  // coefficients are summed (over the steps of a coarsest solve, one column of 512
+  // entries: 5.0 -> 3.9 us a launch; six of 8192: 5.6 -> 5.3)
+  constexpr bool AHEAD = sizeof(R) == 4;
+  cx<R> v[KM], x0;
+  auto load = [&] {
+    const long ec = e < N ? e : N - 1;
+    x0 = w[ec];
+#pragma unroll
+    for (int i = 0; i < KM; ++i) v[i] = V[(long)min(i, k - 1) * ldv + ec];
+  };
+  if (AHEAD) {
+    load();
+    __builtin_amdgcn_sched_barrier(0);
+  }
   reduce_partials(pb + 2 * r * pcs, 2 * k, 2 * KM, gridDim.x, cf);
   if (blockIdx.x == 0 && threadIdx.x < 2 * k) {
     double& hv = reinterpret_cast<double*>(hcol + r * hcs)[threadIdx.x];
@@ -703,18 +781,16 @@ __global__ void __launch_bounds__(BS) k_cgs_axpy_norm(const cx<R>* __restrict__ 
   if (threadIdx.x < KM) cfr[threadIdx.x] = mk<A>((A)cf[2 * threadIdx.x], (A)cf[2 * threadIdx.x + 1]);
   __syncthreads();
   A acc[2] = {A(0), A(0)};
-  const long stride = (long)gridDim.x * BS;
-  for (long e = (long)blockIdx.x * BS + threadIdx.x; e < N; e += stride) {
-    const cx<R> x0 = w[e];
+  for (; e < N;) {
+    if (!AHEAD) load();
     cx<A> s = mk<A>(0, 0);
 #pragma unroll
-    for (int i = 0; i < KM; ++i) {  // coefficients past k are zero
-      const cx<R> v = V[(long)min(i, k - 1) * ldv + e];
-      cmac(s, cfr[i], mk<A>(v.re, v.im));
-    }
+    for (int i = 0; i < KM; ++i) cmac(s, cfr[i], mk<A>(v[i].re, v[i].im));  // coefficients past k are zero
     const cx<R> x = mk<R>((R)(x0.re - s.re), (R)(x0.im - s.im));
     w[e] = x;
     acc[0] += (A)x.re * x.re + (A)x.im * x.im;
+    e += stride;
+    if (AHEAD && e < N) load();
   }
   store_partials<1, BS / 64>(acc, 1, pa + 2 * r * pcs);
 }
@@ -736,13 +812,11 @@ __global__ void __launch_bounds__(BS) k_cgs_scale_givens(cx<R>* w, long csw, lon
     return;
   }
   __shared__ double nn[1];
-  reduce_partials(pa + 2 * r * pcs, 1, 1, gridDim.x, nn);
-  const double nv = sqrt(nn[0] > 0 ? nn[0] : 0.0);
+  __shared__ cx<double> hl[64], sl[64], gl[64];
+  __shared__ double cl[64];
+  cx<double>* h = H + (long)r * ldh * m + (long)j * ldh;
+  const int t = threadIdx.x;
   if (blockIdx.x == 0) {
-    __shared__ cx<double> hl[64], sl[64], gl[64];
-    __shared__ double cl[64];
-    cx<double>* h = H + (long)r * ldh * m + (long)j * ldh;
-    const int t = threadIdx.x;
     if (t <= j) {
       hl[t] = h[t];
       if (t < j) {
@@ -750,13 +824,17 @@ __global__ void __launch_bounds__(BS) k_cgs_scale_givens(cx<R>* w, long csw, lon
         sl[t] = sn[(long)r * m + t];
       }
     }
-    if (t == 0) {
-      hl[j + 1] = mk(nv, 0.0);
-      gl[j] = g[(long)r * ldh + j];
-    }
+    if (t == 64) gl[j] = g[(long)r * ldh + j];
     __syncthreads();
-    if (t == 0) {
-      givens_col(hl, cl, sl, gl, j, resid + r);
+    // the previous rotations while the first wavefront sums the partials
+    if (t == 64) givens_prev(hl, cl, sl, j);
+  }
+  reduce_partials(pa + 2 * r * pcs, 1, 1, gridDim.x, nn);
+  const double nv = sqrt(nn[0] > 0 ? nn[0] : 0.0);
+  if (blockIdx.x == 0) {
+    if (t == 64) {
+      hl[j + 1] = mk(nv, 0.0);
+      givens_new(hl, cl, sl, gl, j, resid + r);
       if (resid_host) resid_host[r] = resid[r];
       // rotation j and the new g entries are the only state kept besides H
       cs[(long)r * m + j] = cl[j];
@@ -774,29 +852,156 @@ __global__ void __launch_bounds__(BS) k_cgs_scale_givens(cx<R>* w, long csw, lon
   }
 }
 
-template <class R, class A, int BS>
-static void cgs_step_bs(const cx<R>* V, long ldv, long csV, int k, cx<R>* w, long csw, long N, double* a, double* b,
-                        long pcs, int nwg, cx<double>* hcol, long hcs, cx<double>* H, int ldh, int m, double* cs,
-                        cx<double>* sn, cx<double>* g, int j, double* resid, double* resid_host, int K, const int* act,
-                        hipStream_t st) {
-  const dim3 grid(nwg, K), blk(BS);
+// Entries of the columns that take k_cgs_column.  A workgroup reads the basis alone,
+// so its time grows with N: over the steps of a coarsest solve (k to 28, one or
+// six columns) 8.1 us at 512 entries and 10.4 at 1024, where the three launches
+// below take 11.5 and 11.8 us and their gaps; at 2048 entries 15.3 against 14.
+constexpr long CGS_COLUMN_MAX = 1024;
+// The whole step of a short FP32 column in one workgroup: w stays in LDS from the
+// first product to the scaled store, the dots go over the wavefronts (NV vectors
+// each, sums in FP64), the updates and the norm over the entries (whose basis
+// entries are loaded before the dots), and the previous rotations are applied to
+// the Hessenberg column beside the update.
+template <class A, int KM>
+__global__ void __launch_bounds__(512) k_cgs_column(const cx<float>* __restrict__ V, long ldv, long csV, int k,
+                                                    cx<float>* w, long csw, int N, cx<double>* H, int ldh, int m,
+                                                    double* cs, cx<double>* sn, cx<double>* g, int j, double* resid,
+                                                    double* resid_host, const int* act) {
+  constexpr int BS = 512, NW = BS / 64, NV = (KM + NW - 1) / NW, NP = cgs_pow2(NV);
+  __shared__ cx<float> wl[CGS_COLUMN_MAX];
+  __shared__ cx<double> hl[34], sl[34], gl[34];
+  __shared__ double cl[34], red[NW];
+  __shared__ cx<A> cfr[32];
+  const int r = blockIdx.x, t = threadIdx.x, lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6);
+  V += r * csV;
+  w += r * csw;
+  if (act && !act[r]) {
+    for (int e = t; e < N; e += BS) w[e] = mk<float>(0, 0);
+    return;
+  }
+  for (int e = t; e < N; e += BS) wl[e] = w[e];
+  if (t < 32) cfr[t] = mk<A>(0, 0);
+  if (t < j) {
+    cl[t] = cs[(long)r * m + t];
+    sl[t] = sn[(long)r * m + t];
+  }
+  if (t == 0) gl[j] = g[(long)r * ldh + j];
+  // the last wavefront first: the first one has the rotations to apply
+  int e = BS - 1 - t;
+  cx<float> v[KM];
+  auto load = [&] {
+#pragma unroll
+    for (int i = 0; i < KM; ++i) v[i] = V[(long)min(i, k - 1) * ldv + min(e, N - 1)];
+  };
+  load();
+  __syncthreads();
+  if (wv < k) {
+    double acc[2 * NP];
+#pragma unroll
+    for (int q = 0; q < 2 * NP; ++q) acc[q] = 0.0;
+#pragma unroll 4
+    for (int q = lane; q < N; q += 64) {
+      const cx<float> x = wl[q];
+#pragma unroll
+      for (int u = 0; u < NV; ++u) {
+        const cx<float> a = V[(long)min(wv + NW * u, k - 1) * ldv + q];  // sums past k unused
+        acc[2 * u] += (double)a.re * x.re + (double)a.im * x.im;
+        acc[2 * u + 1] += (double)a.re * x.im - (double)a.im * x.re;
+      }
+    }
+    const double tot = wave_transpose_sum<2 * NP>(acc, lane);
+    const int i = wv + NW * (lane >> 1);
+    if (lane < 2 * NV && i < k) {
+      (lane & 1 ? hl[i].im : hl[i].re) = tot;
+      (lane & 1 ? cfr[i].im : cfr[i].re) = (A)tot;
+    }
+  }
+  __syncthreads();
+  if (t == 0) givens_prev(hl, cl, sl, j);
+  double nn = 0.0;
+  while (e < N) {
+    cx<A> s = mk<A>(0, 0);
+#pragma unroll
+    for (int i = 0; i < KM; ++i) cmac(s, cfr[i], mk<A>(v[i].re, v[i].im));  // coefficients past k are zero
+    const cx<float> x0 = wl[e];
+    const cx<float> x = mk<float>((float)(x0.re - s.re), (float)(x0.im - s.im));
+    wl[e] = x;
+    nn += (double)x.re * x.re + (double)x.im * x.im;
+    e += BS;
+    if (e < N) load();
+  }
+  nn = wave_sum_n(nn, 64);
+  if (lane == 0) red[wv] = nn;
+  __syncthreads();
+  nn = 0.0;
+#pragma unroll
+  for (int q = 0; q < NW; ++q) nn += red[q];
+  const double nv = sqrt(nn > 0 ? nn : 0.0);
+  const double f = nv > 0 ? 1.0 / nv : 0.0;
+  for (e = BS - 1 - t; e < N; e += BS) {
+    const cx<float> x = wl[e];
+    w[e] = mk<float>((float)(f * x.re), (float)(f * x.im));
+  }
+  if (t == 0) {
+    hl[j + 1] = mk(nv, 0.0);
+    givens_new(hl, cl, sl, gl, j, resid + r);
+    if (resid_host) resid_host[r] = resid[r];
+    // rotation j and the new g entries are the only state kept besides H
+    cs[(long)r * m + j] = cl[j];
+    sn[(long)r * m + j] = sl[j];
+    g[(long)r * ldh + j] = gl[j];
+    g[(long)r * ldh + j + 1] = gl[j + 1];
+  }
+  __syncthreads();
+  if (t <= j + 1) H[(long)r * ldh * m + (long)j * ldh + t] = hl[t];
+}
+
+template <class R, class A>
+static void cgs_step(const cx<R>* V, long ldv, long csV, int k, cx<R>* w, long csw, long N, double* a, double* b,
+                     long pcs, int nwg, cx<double>* hcol, long hcs, cx<double>* H, int ldh, int m, double* cs,
+                     cx<double>* sn, cx<double>* g, int j, double* resid, double* resid_host, int K, const int* act,
+                     hipStream_t st) {
+  constexpr int BS = 256;
   const bool two_pass = cgs_two_pass<R>(m);
-  // the axpy kernels of 16 or more vectors hold twice the registers: half the
-  // threads per workgroup (same workgroup count, so the partials match)
-#define CGS_LAUNCH(KM)                                                                                                 \
-  {                                                                                                                    \
-    constexpr int BA = (BS == 1024 && KM >= 16) ? 512 : BS;                                                            \
-    hipLaunchKernelGGL((k_cgs_dot<R, A, KM, BS>), grid, blk, 0, st, V, ldv, csV, k, (const cx<R>*)w, csw, N, a, pcs,     \
-                       act);                                                                                           \
-    if (two_pass) {                                                                                                    \
-      hipLaunchKernelGGL((k_cgs_axpy_dot<R, A, KM, BA>), grid, dim3(BA), 0, st, V, ldv, csV, k, w, csw, N,               \
-                         (const double*)a, b, pcs, hcol, hcs, act);                                                    \
-      hipLaunchKernelGGL((k_cgs_axpy_norm<R, A, KM, BA>), grid, dim3(BA), 0, st, V, ldv, csV, k, w, csw, N,              \
-                         (const double*)b, a, pcs, hcol, hcs, act);                                                    \
-    } else {                                                                                                           \
-      hipLaunchKernelGGL((k_cgs_axpy_norm<R, A, KM, BA, true>), grid, dim3(BA), 0, st, V, ldv, csV, k, w, csw, N,        \
-                         (const double*)a, b, pcs, hcol, hcs, act);                                                    \
-    }                                                                                                                  \
+  if constexpr (sizeof(R) == 4) {
+    if (N <= CGS_COLUMN_MAX) {
+#define CGS_COLUMN(KM)                                                                                            \
+  hipLaunchKernelGGL((k_cgs_column<A, KM>), dim3(K), dim3(512), 0, st, V, ldv, csV, k, w, csw, (int)N, H, ldh, m, \
+                     cs, sn, g, j, resid, resid_host, act)
+      if (k <= 8) CGS_COLUMN(8);
+      else if (k <= 16) CGS_COLUMN(16);
+      else if (k <= 24) CGS_COLUMN(24);
+      else CGS_COLUMN(32);
+#undef CGS_COLUMN
+      return;
+    }
+  }
+  const dim3 grid(nwg, K), blk(BS);
+  if constexpr (sizeof(R) == 4) {
+#define CGS_DOT(NV) \
+  hipLaunchKernelGGL(k_cgs_dot_waves<NV>, grid, dim3(512), 0, st, V, ldv, csV, k, (const cx<R>*)w, csw, N, a, pcs, act)
+    if (k <= 8) CGS_DOT(1);
+    else if (k <= 16) CGS_DOT(2);
+    else if (k <= 24) CGS_DOT(3);
+    else CGS_DOT(4);
+#undef CGS_DOT
+  }
+#define CGS_LAUNCH(KM)                                                                                                \
+  {                                                                                                                   \
+    if constexpr (sizeof(R) == 8)                                                                                     \
+      hipLaunchKernelGGL((k_cgs_dot<R, A, KM, BS>), grid, blk, 0, st, V, ldv, csV, k, (const cx<R>*)w, csw, N, a, pcs, \
+                         act);                                                                                        \
+    if constexpr (sizeof(R) == 8) {                                                                                   \
+      if (two_pass) {                                                                                                 \
+        hipLaunchKernelGGL((k_cgs_axpy_dot<R, A, KM, BS>), grid, blk, 0, st, V, ldv, csV, k, w, csw, N,               \
+                           (const double*)a, b, pcs, hcol, hcs, act);                                                 \
+        hipLaunchKernelGGL((k_cgs_axpy_norm<R, A, KM, BS>), grid, blk, 0, st, V, ldv, csV, k, w, csw, N,              \
+                           (const double*)b, a, pcs, hcol, hcs, act);                                                 \
+      }                                                                                                               \
+    }                                                                                                                 \
+    if (!two_pass)                                                                                                    \
+      hipLaunchKernelGGL((k_cgs_axpy_norm<R, A, KM, BS, true>), grid, blk, 0, st, V, ldv, csV, k, w, csw, N,          \
+                         (const double*)a, b, pcs, hcol, hcs, act);                                                   \
   }
   // buckets of basis sizes: at most three clamped loads past k per element
   if (k <= 2) {
@@ -825,13 +1030,6 @@ static void cgs_step_bs(const cx<R>* V, long ldv, long csV, int k, cx<R>* w, lon
                      H, ldh, m, cs, sn, g, j, resid, resid_host, act);
 }
 
-// FP32 vectors: 512-thread workgroups with FP32 per-thread sums (at most 128
-// registers; with up to 256 workgroups a coarsest column of 82,944 entries
-// spreads over all 256 CUs); FP64 vectors: 256-thread workgroups
-template <class R>
-int cgs_block_size() {
-  return sizeof(R) == 4 ? 512 : 256;
-}
 template <class R>
 void launch_cgs_step(const cx<R>* V, long ldv, long csV, int k, cx<R>* w, long csw, long N, cx<double>* pa,
                      cx<double>* pb, long pcs, int nwg, cx<double>* hcol, long hcs, cx<double>* H, int ldh, int m,
@@ -840,13 +1038,15 @@ void launch_cgs_step(const cx<R>* V, long ldv, long csV, int k, cx<R>* w, long c
   double* a = reinterpret_cast<double*>(pa);
   double* b = reinterpret_cast<double*>(pb);
 #define CGS_ARGS V, ldv, csV, k, w, csw, N, a, b, pcs, nwg, hcol, hcs, H, ldh, m, cs, sn, g, j, resid, resid_host, K, act, st
-  if constexpr (sizeof(R) == 8) cgs_step_bs<R, double, 256>(CGS_ARGS);
-  else if (sums64) cgs_step_bs<R, double, 512>(CGS_ARGS);
-  else cgs_step_bs<R, R, 512>(CGS_ARGS);
+  if constexpr (sizeof(R) == 8) {
+    cgs_step<R, double>(CGS_ARGS);
+  } else {
+    if (sums64) cgs_step<R, double>(CGS_ARGS);
+    else cgs_step<R, R>(CGS_ARGS);
+  }
 #undef CGS_ARGS
 }
 #define INST_CGS(R)                                                                                             \
-  template int cgs_block_size<R>();                                                                               \
   template void launch_cgs_step<R>(const cx<R>*, long, long, int, cx<R>*, long, long, cx<double>*, cx<double>*,   \
                                    long, int, cx<double>*, long, cx<double>*, int, int, double*, cx<double>*,     \
                                    cx<double>*, int, double*, double*, int, const int*, bool, hipStream_t);

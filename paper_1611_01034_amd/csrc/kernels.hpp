@@ -243,12 +243,11 @@ template <class R>
 void launch_zero_b(long N, cx<R>* x, long cs, int K, hipStream_t st);
 // Arnoldi step of K lock-step processes: classical Gram-Schmidt against
 // V_0..V_{k-1} (k <= 32; two passes for FP64 vectors, one for FP32), norm,
-// scaling of w and Givens step j, in four (three) launches;
+// scaling of w and Givens step j, in four (three) launches, one for a short FP32
+// column (which leaves pa, pb and hcol alone);
 // pa, pb: two partial buffers of pcs >= ldh * nwg complex per column; nwg
-// workgroups of cgs_block_size<R>() threads per column; resid_host (pinned host
-// memory, may be null) receives a copy of the K residual estimates
-template <class R>
-int cgs_block_size();
+// workgroups of 256 threads per column; resid_host (pinned host memory, may be
+// null) receives a copy of the K residual estimates
 // Gram-Schmidt passes of the Arnoldi step of a cycle of m steps: two for
 // FP64 vectors in cycles longer than 8 steps, one otherwise.  One classical
 // pass loses orthogonality in proportion to the squared condition number of
@@ -258,7 +257,7 @@ template <class R>
 inline bool cgs_two_pass(int m) {
   return sizeof(R) == 8 && m > 8;
 }
-// sums64: per-thread sums and updates of FP32 vectors in FP64
+// sums64: updates and norms of FP32 vectors in FP64 per thread (the dots always are)
 template <class R>
 void launch_cgs_step(const cx<R>* V, long ldv, long csV, int k, cx<R>* w, long csw, long N, cx<double>* pa,
                      cx<double>* pb, long pcs, int nwg, cx<double>* hcol, long hcs, cx<double>* H, int ldh, int m,

@@ -273,12 +273,12 @@ static double sap_sweep_bytes(const Geom& g, int K) {
 }
 
 // ---------------------------------------------------------------------------
-// workgroups per column of the fused Arnoldi step: about one element per
-// thread of an FP32 vector (at most 128 workgroups, so every workgroup's
+// workgroups (of 256 threads) per column of the fused Arnoldi step: one element
+// per thread of an FP32 vector (at most 256 workgroups, so every workgroup's
 // prologue sums few partials), four per thread of an FP64 one (at most 1024)
 template <class R>
 static int cgs_nwg(long N) {
-  const long per = sizeof(R) == 4 ? cgs_block_size<R>() : 4L * cgs_block_size<R>();
+  const long per = sizeof(R) == 4 ? 256 : 1024;
   const long cap = sizeof(R) == 4 ? 256 : 1024;
   return (int)std::min<long>(cap, std::max<long>(1, (N + per - 1) / per));
 }

@@ -205,3 +205,37 @@ def test_coarse_solve_multi_restart_above_32(dd):
     got = ctx.coarse_solve_multi(1, bs)
     for k in range(2):
         assert rel(got[k], h.coarse_solve(1, bs[k])) < 1e-10
+
+
+@pytest.mark.parametrize("dims,nv", [((4, 4, 4, 4), 1),         # 16 entries a column: less than a wavefront
+                                     ((4, 4, 4, 4), 13),        # 208
+                                     ((4, 4, 8, 8), 16),        # 1024: the longest column of one workgroup
+                                     ((4, 4, 8, 8), 17),        # 1088: several workgroups, the last a quarter full
+                                     ((8, 8, 16, 32), 16)])     # 32,768: more than one entry per thread for 5 columns
+def test_fp32_arnoldi_steps_of_short_and_long_columns(dd, dims, nv):
+    """m fixed steps of the coarsest solve in FP32 (one column: sums in FP64;
+    five in lock step) against the FP64 solve of one column: the minimal
+    residual within 1e-3 of itself and 1e-5 of the right-hand side (the FP32
+    operator's bar; a minimal residual is stationary against the rounding of
+    the basis)."""
+    block = (2, 2, 2, 2)
+    ctx, op = make(dd, dims, block)
+    V = synth.spinor(dims, 91, nvec=nv)
+    bs = None
+    for m in (1, 2, 8, 9, 17, 25, 32):
+        kw = dict(levels=2, block=[block], nvec=[nv], coarse_mu_factor=3.0, fixed_iters=1, coarse_max_iter=m,
+                  coarse_restart=32)
+        if m > 8 and nv == 1:
+            continue  # 16 unknowns: solved to rounding
+        ctx.set_test_vectors(dd.default_params(precision="fp64", **kw), [V])
+        if bs is None:
+            cd, n = ctx.level_info(1)
+            bs = synth.gaussian((5,) + cd + (n,), 92)
+        print(f"arnoldi: {dims} n {n} m {m}", flush=True)
+        want = [np.linalg.norm(b - ctx.apply_coarse(1, ctx.coarse_solve(1, b))) for b in bs]
+        ctx.set_test_vectors(dd.default_params(precision="fp32", **kw), [V])
+        one, many = ctx.coarse_solve(1, bs[1]), ctx.coarse_solve_multi(1, bs)
+        for k, x in [(1, one)] + list(enumerate(many)):
+            got = np.linalg.norm(bs[k] - ctx.apply_coarse(1, x))
+            assert abs(got - want[k]) <= 1e-3 * want[k] + 1e-5 * np.linalg.norm(bs[k]), (m, k)
+    ctx.close()
