@@ -351,9 +351,9 @@ __global__ void __launch_bounds__(256) k_coarse_hop_inv_odd_mrhs(CGeom cg,
 constexpr int SPLIT_G = 4;
 constexpr int SPLIT_LD = 20;  // floats per output row of a partial sum (16 used; conflict-free)
 
-// part[gb][row][column] of the hops of xh (scaled by hs) and the self block on
-// xs (or null); wavefront (gb, t)
-template <class S, int RT>
+// part[gb][row][column] (rows of WT row tiles: all of them, or tile t alone) of the
+// hops of xh (scaled by hs) and the self block on xs (or null); wavefront (gb, t)
+template <class S, int RT, int WT = RT>
 __device__ __forceinline__ void stencil_split(const CGeom& cg, const typename store_traits<S>::elem* D, int site,
                                               int gb, int t, const cx<float>* xs, const cx<float>* xh, float hs, int K,
                                               long ldv, int lane, float* part) {
@@ -383,12 +383,12 @@ __device__ __forceinline__ void stencil_split(const CGeom& cg, const typename st
   for (int s = 0; s < 2 * RT; ++s) acc = mm16<S>::mma(af[s], bf[s], acc);
   if (self) acc = mm16<S>::mma(af[2 * RT], bf[2 * RT], acc);
 #pragma unroll
-  for (int e = 0; e < 4; ++e) part[(gb * n + 16 * t + 4 * grp + e) * SPLIT_LD + row] = acc[e];
+  for (int e = 0; e < 4; ++e) part[(gb * 16 * WT + 16 * (WT == 1 ? 0 : t) + 4 * grp + e) * SPLIT_LD + row] = acc[e];
 }
 // entry (row i, column r) of the sum of the four groups
-template <int RT>
+template <int WT>
 __device__ __forceinline__ cx<float> split_sum(const float* part, int i, int r) {
-  constexpr int n = 16 * RT;
+  constexpr int n = 16 * WT;
   cx<float> v = mk<float>(0.f, 0.f);
 #pragma unroll
   for (int g = 0; g < SPLIT_G; ++g) v += *reinterpret_cast<const cx<float>*>(part + (g * n + i) * SPLIT_LD + 2 * r);
@@ -422,32 +422,39 @@ __global__ void __launch_bounds__(256 * RT) k_coarse_apply_split(CGeom cg,
   }
 }
 
-template <class S, int RT>
-__global__ void __launch_bounds__(256 * RT) k_coarse_schur_even_split(CGeom cg,
+// WT = RT: a workgroup per site.  WT = 1: the rows of an even site are independent,
+// so each of n/16 workgroups of four wavefronts takes 16 of them (on one XCD) and a
+// small grid spreads over more CUs, whose load paths are what a workgroup per site
+// waits for (sizes measured: even_rows).
+template <class S, int RT, int WT>
+__global__ void __launch_bounds__(256 * WT) k_coarse_schur_even_split(CGeom cg,
                                                                       const typename store_traits<S>::elem* __restrict__ D,
                                                                       float tw, int K, long ldv,
                                                                       const cx<float>* __restrict__ v,
                                                                       const cx<float>* __restrict__ t,
                                                                       cx<float>* __restrict__ y, int mode) {
-  constexpr int n = 16 * RT;
-  __shared__ float part[SPLIT_G * n * SPLIT_LD];
-  const int site = blockIdx.x, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  stencil_split<S, RT>(cg, D, site, w / RT, w % RT, mode == 0 ? v : nullptr, t, -1.0f, K, ldv, threadIdx.x & 63, part);
+  constexpr int n = 16 * RT, nw = 16 * WT, NT = RT / WT;
+  __shared__ float part[SPLIT_G * nw * SPLIT_LD];
+  const int wg = xcd_remap(blockIdx.x, gridDim.x), site = wg / NT, t0 = wg - site * NT;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // 16 nw threads and at most 8 nw results: row il of column r, in flight early
+  const int r = threadIdx.x / nw, il = threadIdx.x % nw, i = 16 * t0 + il;
+  const bool out = r < K;
+  const long o = (long)(out ? r : 0) * ldv + (long)site * n + i;
+  const cx<float> x = v[o];
+  stencil_split<S, RT, WT>(cg, D, site, w / WT, WT == 1 ? t0 : w % WT, mode == 0 ? v : nullptr, t, -1.0f, K, ldv,
+                           threadIdx.x & 63, part);
   __syncthreads();
-  for (int e = threadIdx.x; e < n * K; e += 256 * RT) {
-    const int r = e / n, i = e - r * n;
-    const long o = (long)r * ldv + (long)site * n + i;
-    cx<float> q = split_sum<RT>(part, i, r);
-    const cx<float> x = v[o];
-    if (mode == 0) {
-      const float g = i < n / 2 ? -tw : tw;
-      q.re += -g * x.im;
-      q.im += g * x.re;
-    } else {
-      q = x + q;
-    }
-    y[o] = q;
+  if (!out) return;
+  cx<float> q = split_sum<WT>(part, il, r);
+  if (mode == 0) {
+    const float g = i < n / 2 ? -tw : tw;
+    q.re += -g * x.im;
+    q.im += g * x.re;
+  } else {
+    q = x + q;
   }
+  y[o] = q;
 }
 
 template <class S, int RT>
@@ -462,36 +469,36 @@ __global__ void __launch_bounds__(256 * RT) k_coarse_hop_inv_odd_split(CGeom cg,
   extern __shared__ char smem_raw[];
   cx<float>* us = reinterpret_cast<cx<float>*>(smem_raw);  // [n][K]
   cx<float>* ps = us + n * K;                               // [NQ][K][n]
-  const int io = blockIdx.x, site = cg.neven + io;
+  const int io = xcd_remap(blockIdx.x, gridDim.x), site = cg.neven + io;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // 16 n threads and at most 8 n results
   const int i0 = threadIdx.x % n, q = threadIdx.x / n;
+  const bool out = q < K;  // this thread's result: row i0 of column q
+  const long o = (long)(out ? q : 0) * ldv + (long)site * n + i0;
   cx<float> m[RT];
   const cx<float>* M = Minv + (long)io * n * n;
 #pragma unroll
   for (int l = 0; l < RT; ++l) m[l] = M[(long)(q * RT + l) * n + i0];
+  const cx<float> bv = base ? base[o] : mk<float>(0.f, 0.f);
   stencil_split<S, RT>(cg, D, site, w / RT, w % RT, nullptr, x, 1.0f, K, ldv, threadIdx.x & 63, part);
   __syncthreads();
-  for (int e = threadIdx.x; e < n * K; e += 256 * RT) {
-    const int r = e / n, i = e - r * n;
-    cx<float> u = split_sum<RT>(part, i, r);
-    if (base) u = base[(long)r * ldv + (long)site * n + i] - u;
-    us[i * K + r] = u;
+  if (out) {
+    const cx<float> u = split_sum<RT>(part, i0, q);
+    us[i0 * K + q] = base ? bv - u : u;
   }
   __syncthreads();
   for (int r = 0; r < K; ++r) {
-    cx<float> o = mk<float>(0.f, 0.f);
+    cx<float> p = mk<float>(0.f, 0.f);
 #pragma unroll
-    for (int l = 0; l < RT; ++l) cmac(o, m[l], us[(q * RT + l) * K + r]);
-    ps[(q * K + r) * n + i0] = o;
+    for (int l = 0; l < RT; ++l) cmac(p, m[l], us[(q * RT + l) * K + r]);
+    ps[(q * K + r) * n + i0] = p;
   }
   __syncthreads();
-  for (int e = threadIdx.x; e < n * K; e += 256 * RT) {
-    const int r = e / n, i = e - r * n;
-    cx<float> o = mk<float>(0.f, 0.f);
+  if (!out) return;
+  cx<float> y0 = mk<float>(0.f, 0.f);
 #pragma unroll
-    for (int p = 0; p < NQ; ++p) o += ps[(p * K + r) * n + i];
-    y[(long)r * ldv + (long)site * n + i] = o;
-  }
+  for (int p = 0; p < NQ; ++p) y0 += ps[(p * K + q) * n + i0];
+  y[o] = y0;
 }
 
 // SAP on the blocks of one colour of an intermediate level for K fields in
@@ -724,13 +731,30 @@ void launch_coarse_apply_mrhs(const CGeom& cg, const void* D, double tw, int K, 
   MRHS_DISPATCH_BIG(k_coarse_apply_mrhs, grid, blk, 0, st, cg, Dp, (float)tw, K, ldv, x, b, y, sites);
 }
 
+// Whether 16 rows of an even site get a workgroup: with fewer sites than CUs (six
+// columns, us per odd-even pair, a workgroup per site and now: 32 sites of n = 64
+// 17.0 and 13.4, 256 sites of n = 64 18.3 and 15.1, 256 sites of n = 48 11.4 and
+// 10.6), and at n = 64 with more (1024 sites 39.1 and 36.9; 1024 threads a site fit
+// once on a CU).  At 512 sites of n = 32 and 48 it takes 9.3 and 12.8 for 8.6 and
+// 12.4.
+static inline bool even_rows(int neven, int n) { return n == 64 || neven < 256; }
+template <class S, int RT>
+constexpr auto EVEN_ROWS = k_coarse_schur_even_split<S, RT, 1>;
+template <class S, int RT>
+constexpr auto EVEN_SITE = k_coarse_schur_even_split<S, RT, RT>;
+
 template <class S>
 void launch_coarse_schur_even_mrhs(const CGeom& cg, const void* D, double tw, int K, long ldv, const cx<float>* v,
                                    const cx<float>* t, cx<float>* y, int mode, hipStream_t st) {
   dim3 grid(cg.neven), blk(4 * cg.n);
   auto Dp = (const typename store_traits<S>::elem*)D;
   if (split_sites(cg.neven, cg.n, K)) {
-    SPLIT_DISPATCH(k_coarse_schur_even_split, grid, dim3(16 * cg.n), 0, st, cg, Dp, (float)tw, K, ldv, v, t, y, mode);
+    if (even_rows(cg.neven, cg.n)) {
+      SPLIT_DISPATCH(EVEN_ROWS, dim3(cg.neven * (cg.n / 16)), dim3(256), 0, st, cg, Dp, (float)tw, K, ldv, v, t, y,
+                     mode);
+    } else {
+      SPLIT_DISPATCH(EVEN_SITE, grid, dim3(16 * cg.n), 0, st, cg, Dp, (float)tw, K, ldv, v, t, y, mode);
+    }
     return;
   }
   MRHS_DISPATCH_BIG(k_coarse_schur_even_mrhs, grid, blk, 0, st, cg, Dp, (float)tw, K, ldv, v, t, y, mode);

@@ -110,3 +110,26 @@ def test_single_column_operators_of_any_width(nv, prec):
             want = (1 - par) * (site((1 - par) * y) - hop(u))
             got = ctx.apply_coarse_schur_multi(1, y[None])[0]
             assert np.linalg.norm(got - want) <= tol * np.linalg.norm(want)
+
+
+@pytest.mark.parametrize("dims,nv", [((4, 4, 4, 4), 16), ((4, 4, 4, 8), 24), ((4, 4, 8, 8), 24), ((4, 4, 4, 4), 32)])
+def test_even_rows_alone_on_few_sites(dims, nv):
+    """16 rows of an even site to a workgroup (8 to 32 even sites, two to four row
+    tiles): the columns alone against the same columns among sixteen, with the
+    bars of the test above."""
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    from paper_1611_01034_amd import ddamg, synth
+    block = (2, 2, 2, 2)
+    with ddamg.DDAMG(dims, block, KAPPA, CSW, MU) as ctx:
+        ctx.set_gauge(synth.gauge_field(dims, 0.3, 9401))
+        p = ddamg.default_params(levels=2, block=[block], nvec=[nv], coarse_mu_factor=5.0, precision="bf16")
+        ctx.set_test_vectors(p, [synth.spinor(dims, 9402, nvec=nv)])
+        cd, n = ctx.level_info(1)
+        xs = synth.gaussian((16,) + cd + (n,), 9403)
+        many = ctx.apply_coarse_schur_multi(1, xs)
+        for K in (1, 5, 8):
+            print(f"even rows: {dims} n {n} K {K}", flush=True)
+            got = ctx.apply_coarse_schur_multi(1, xs[:K])
+            for k in range(K):
+                assert np.linalg.norm(got[k] - many[k]) <= 2e-4 * np.linalg.norm(many[k]), (K, k)
