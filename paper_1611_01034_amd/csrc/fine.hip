@@ -68,19 +68,19 @@ template <class R>
 struct alignas(4 * sizeof(R)) cxpair {
   cx<R> a, b;
 };
-template <class R, bool NEG = false>
-__device__ __forceinline__ void pair_get(const cxpair<R>* f, int hs, int idx, cx<R> v[12]) {
+template <class R, bool NEG = false, int NP = 6>
+__device__ __forceinline__ void pair_get(const cxpair<R>* f, int hs, int idx, cx<R>* v) {
 #pragma unroll
-  for (int p = 0; p < 6; ++p) {
+  for (int p = 0; p < NP; ++p) {
     const cxpair<R> q = f[p * hs + idx];
     v[2 * p] = NEG ? -q.a : q.a;
     v[2 * p + 1] = NEG ? -q.b : q.b;
   }
 }
-template <class R>
-__device__ __forceinline__ void pair_put(cxpair<R>* f, int hs, int idx, const cx<R> v[12]) {
+template <class R, int NP = 6>
+__device__ __forceinline__ void pair_put(cxpair<R>* f, int hs, int idx, const cx<R>* v) {
 #pragma unroll
-  for (int p = 0; p < 6; ++p) f[p * hs + idx] = cxpair<R>{v[2 * p], v[2 * p + 1]};
+  for (int p = 0; p < NP; ++p) f[p * hs + idx] = cxpair<R>{v[2 * p], v[2 * p + 1]};
 }
 
 // the links of direction MU's two in-block hops at a slot; a dropped backward hop
@@ -165,16 +165,16 @@ __device__ __forceinline__ void hop_inv_block(const typename store_traits<S>::el
     __builtin_amdgcn_sched_barrier(0);
     tinv_load(Minv, tt, tl, 1, b);
     __builtin_amdgcn_sched_barrier(0);
-    tinv_mv(a, 0, u, w);
+    tinv_mv(a, u, w);
     __builtin_amdgcn_sched_barrier(0);
     tinv_load(Minv, tt, tl, 2, a);
     __builtin_amdgcn_sched_barrier(0);
-    tinv_mv(b, 1, u, w);
+    tinv_mv(b, u, w + 3);
     __builtin_amdgcn_sched_barrier(0);
     tinv_load(Minv, tt, tl, 3, b);
     __builtin_amdgcn_sched_barrier(0);
-    tinv_mv(a, 2, u, w);
-    tinv_mv(b, 3, u, w);
+    tinv_mv(a, u + 6, w + 6);
+    tinv_mv(b, u + 6, w + 9);
   }
 }
 
@@ -195,9 +195,9 @@ __device__ __forceinline__ void hop_inv_block(const typename store_traits<S>::el
 // compile-time spin projections, T_oo^{-1} as one product, 16-byte loads and LDS
 // accesses, each direction's links and each third of T_oo^{-1}'s rows loaded
 // while the one before multiplies.  1042 -> 769 us a sweep there, 105 -> 84 us
-// with one field and FP32 links at 24x16x16x24, 79 -> 57 us on 8x8x8x16.  All
-// 256 registers are in use: with 168 (three wavefronts per SIMD) the sweeps take
-// 1086 and 129 us, and two threads for each pair of slots spill at any count.
+// with one field and FP32 links at 24x16x16x24.  All 256 registers are in use:
+// with 168 (three wavefronts per SIMD) these take 1086 and 129 us.  Small grids and
+// one field with FP32 links take k_sap_two.
 template <class R, class S>
 __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(sizeof(R) == 8 ? 1 : 2, 8)))
 k_sap(Geom g, int colour, const typename store_traits<S>::elem* __restrict__ U, const R* __restrict__ H,
@@ -338,6 +338,277 @@ k_sap(Geom g, int colour, const typename store_traits<S>::elem* __restrict__ U, 
   store_spinor(x, g, B, se, tmp);
 }
 
+// The two threads of a site pair: thread `part` takes directions 2 part and
+// 2 part + 1 of every hop sum and chirality `part` of everything diagonal in
+// it.  A hop sum's halves meet through LDS: each thread hands over its partial
+// sums of the other chirality (ex: [chirality][3 pairs][stride]) and keeps its
+// own; ends with the sum, and contains one barrier.
+__device__ __forceinline__ void exchange_halves(cxpair<float>* ex, int stride, int i, int part, bool live, const cx<float> v[12],
+                                                cx<float> own[6]) {
+  cx<float> give[6];
+#pragma unroll
+  for (int c = 0; c < 6; ++c) {
+    own[c] = part ? v[6 + c] : v[c];
+    give[c] = part ? v[c] : v[6 + c];
+  }
+  if (live) pair_put<float, 3>(ex + (part ? 0 : 3) * stride, stride, i, give);
+  __syncthreads();
+  pair_get<float, false, 3>(ex + (part ? 3 : 0) * stride, stride, i, give);
+#pragma unroll
+  for (int c = 0; c < 6; ++c) own[c] += give[c];
+}
+
+// a thread's links of a slot's in-block hops: forward and backward, its two directions
+template <class S>
+struct PartLinks {
+  RawLink<S> f[2], b[2];
+};
+template <class S>
+__device__ __forceinline__ void part_links(const typename store_traits<S>::elem* U, const Geom& g, int B, int s,
+                                           BlockNbr nb, int noff, int part, PartLinks<S>& l) {
+  const long site_s = link_site<S>(g, B, s);
+  const unsigned wd = part ? nb.w[1] : nb.w[0];
+#pragma unroll
+  for (int d = 0; d < 2; ++d) {
+    const int sb = (wd >> (16 * d + 8)) & 255;
+    load_raw<S>(U, site_s, 2 * part + d, l.f[d]);
+    load_raw<S>(U, link_site<S>(g, B, min(sb, g.half - 1) + noff), 2 * part + d, l.b[d]);
+  }
+}
+// FP16: a copy whose conversion stays where it is used; hoisted out of the MR steps
+// the converted links spill (BF16 links do not, and take 36.9 us so, 38.5 this way)
+template <class S>
+__device__ __forceinline__ RawLink<S> use_link(RawLink<S> r) {
+  if constexpr (std::is_same<S, f16>::value) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+#pragma unroll
+      for (int w = 0; w < 4; ++w) __asm__ volatile("" : "+v"(r.c[c].w[w]));
+  }
+  return r;
+}
+// own += (or -= with SUB) this thread's chirality of the in-block hops of its slot,
+// the other parity's field in lds
+template <class S, bool SUB>
+__device__ __forceinline__ void hop_two(const PartLinks<S>& l, const Geom& g, BlockNbr nb, const cxpair<float>* lds,
+                                        int hs, cxpair<float>* ex, int i, int part, bool live, cx<float> own[6]) {
+  cx<float> h[12], sum[6];
+#pragma unroll
+  for (int c = 0; c < 12; ++c) h[c] = mk<float>(0, 0);
+  if (part == 0) {
+    hop_block_dir<0, float, S, SUB>(use_link<S>(l.f[0]), use_link<S>(l.b[0]), lds, hs, nb, h);
+    hop_block_dir<1, float, S, SUB>(use_link<S>(l.f[1]), use_link<S>(l.b[1]), lds, hs, nb, h);
+  } else {
+    hop_block_dir<2, float, S, SUB>(use_link<S>(l.f[0]), use_link<S>(l.b[0]), lds, hs, nb, h);
+    hop_block_dir<3, float, S, SUB>(use_link<S>(l.f[1]), use_link<S>(l.b[1]), lds, hs, nb, h);
+  }
+  exchange_halves(ex, g.half, i, part, live, h, sum);
+#pragma unroll
+  for (int c = 0; c < 6; ++c) own[c] += sum[c];
+}
+// chirality block `part` of T psi and of T^{-1} psi
+__device__ __forceinline__ void term_two(const float h[36], int part, float tw, const cx<float> psi[6],
+                                         cx<float> out[6]) {
+  const float t = part ? tw : -tw;
+  herm_mv(h, 1, psi, out);
+#pragma unroll
+  for (int c = 0; c < 6; ++c) out[c] += t * times_i(psi[c]);
+}
+__device__ __forceinline__ void inv_two(const TinvRows r[2], const cx<float> psi[6], cx<float> out[6]) {
+  tinv_mv(r[0], psi, out);
+  tinv_mv(r[1], psi, out + 3);
+}
+
+// The sweep for grids that leave most of the chip idle, and for one field with FP32
+// links: two threads for a pair of slots, in wavefronts of their own, and a
+// wavefront alone on its SIMD.  Bound by the chain of an MR step (two hop sums, two
+// exchanges, the dots), so that is what is halved, and the operator entries of a
+// thread (200 to 250 registers) are loaded once and stay in the register file of
+// 512 through the MR steps.  Sizes measured: sap_two.
+template <class S>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 2)))
+k_sap_two(Geom g, int colour, const typename store_traits<S>::elem* __restrict__ U, const float* __restrict__ H,
+          const float* __restrict__ Tinv, TwistR<float> tw, const cx<float>* __restrict__ b, cx<float>* __restrict__ x,
+          int n_mr, int K, long ld) {
+  extern __shared__ char smem_raw[];
+  // the residual stages x of the block parity-split (24 x half); the block
+  // solve then keeps one field per parity as 6 pairs x hs (hs = half + 1: entry
+  // half is the zero spinor of dropped hops), and the halves of a hop sum pass
+  // through ex
+  const int hs = g.half + 1;
+  cx<float>* xs = reinterpret_cast<cx<float>*>(smem_raw);
+  cxpair<float>* ev = reinterpret_cast<cxpair<float>*>(smem_raw);  // even slots
+  cxpair<float>* od = ev + 6 * hs;                                  // odd slots
+  cxpair<float>* ex = od + 6 * hs;                                  // 6 x half
+  __shared__ double red[2][3][4];                                   // per-wavefront sums, by MR step parity
+  int B;
+  {
+    // K right-hand sides interleaved: consecutive workgroups (same XCD) take
+    // the same lattice block for different fields, so its links, clover and
+    // odd-site inverses are shared through L2
+    const int w = xcd_remap(blockIdx.x, gridDim.x);
+    const int pair = w / K, rr = w - pair * K;
+    b += (long)rr * ld;
+    x += (long)rr * ld;
+    int B0 = 2 * pair;
+    int bc[4];
+    block_coords(g, B0, bc);
+    int par = (bc[0] + bc[1] + bc[2] + bc[3]) & 1;
+    B = B0 + ((par ^ colour) & 1);
+  }
+  const int nt = blockDim.x >> 1;  // threads of one part: half rounded up to wavefronts
+  const int part = __builtin_amdgcn_readfirstlane(threadIdx.x >= nt ? 1 : 0);
+  const int i0 = threadIdx.x - part * nt;
+  const bool live = i0 < g.half;
+  // threads past the block's slots follow the last one and store nothing
+  const int i = live ? i0 : g.half - 1;
+  const int se = i, so = g.half + i;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  const long oe = fidx(g, B, se, 12) + (long)(6 * part) * TILE, oo = fidx(g, B, so, 12) + (long)(6 * part) * TILE;
+  SiteNbr me_e, me_o;
+  me_of(g, B, se, me_e);
+  me_of(g, B, so, me_o);
+  cx<float> rho[6], ee[6], tmp[6];
+  // the block operator of the thread's two slots stays in registers
+  const BlockNbr nb_e = block_nbrs(g, me_e), nb_o = block_nbrs(g, me_o);
+  float he[36];
+  TinvRows ti[2];
+  PartLinks<S> le, lo;
+  herm_load(H, (long)B * (g.bs / TILE) + se / TILE, se % TILE, part, he);
+  {
+    // r = b - D x with x of this block staged in LDS
+    cx<float> ro[6], xe[6], xo[6];
+#pragma unroll
+    for (int c = 0; c < 6; ++c) {
+      xe[c] = x[oe + (long)c * TILE];
+      xo[c] = x[oo + (long)c * TILE];
+    }
+    if (live) {
+#pragma unroll
+      for (int c = 0; c < 6; ++c) {
+        *lds_site(xs, g, se, 6 * part + c) = xe[c];
+        *lds_site(xs, g, so, 6 * part + c) = xo[c];
+      }
+    }
+    term_two(he, part, tw.e, xe, rho);
+    {
+      float ho[36];
+      herm_load(H, (long)B * (g.bs / TILE) + so / TILE, so % TILE, part, ho);
+      term_two(ho, part, tw.o, xo, ro);
+    }
+    __syncthreads();
+    cx<float> h[12];
+#pragma unroll
+    for (int c = 0; c < 12; ++c) h[c] = mk<float>(0, 0);
+    hop_staged<float, S>(U, x, xs, g, B, se, me_e, h, 2 * part, 2 * part + 2);
+    exchange_halves(ex, g.half, i, part, live, h, tmp);
+#pragma unroll
+    for (int c = 0; c < 6; ++c) rho[c] = b[oe + (long)c * TILE] - (rho[c] + tmp[c]);
+#pragma unroll
+    for (int c = 0; c < 12; ++c) h[c] = mk<float>(0, 0);
+    hop_staged<float, S>(U, x, xs, g, B, so, me_o, h, 2 * part, 2 * part + 2);
+    __syncthreads();  // the first exchange has been read
+    exchange_halves(ex, g.half, i, part, live, h, tmp);
+#pragma unroll
+    for (int c = 0; c < 6; ++c) ro[c] = b[oo + (long)c * TILE] - (ro[c] + tmp[c]);
+    // (every thread has passed the exchange's barrier: xs is free)
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+      tinv_load(Tinv, (long)B * (g.half / TILE) + i / TILE, i % TILE, 2 * part + q, ti[q]);
+    part_links<S>(U, g, B, se, nb_e, g.half, part, le);
+    part_links<S>(U, g, B, so, nb_o, 0, part, lo);
+    inv_two(ti, ro, tmp);
+    if (live) {
+      pair_put<float, 3>(od + 3 * part * hs, hs, i, tmp);
+#pragma unroll
+      for (int c = 0; c < 6; ++c) x[oo + (long)c * TILE] = xo[c] + tmp[c];
+    }
+    // od follows ev: 12 rows whose entry `half` is zero
+    if (threadIdx.x < 12) ev[threadIdx.x * hs + g.half] = cxpair<float>{mk<float>(0, 0), mk<float>(0, 0)};
+  }
+  __syncthreads();
+  // rho = r_e - D_eo t_o
+  hop_two<S, true>(le, g, nb_e, od, hs, ex, i, part, live, rho);
+#pragma unroll
+  for (int c = 0; c < 6; ++c) ee[c] = mk<float>(0, 0);
+  cxpair<float>* evp = ev + 3 * part * hs;
+  cxpair<float>* odp = od + 3 * part * hs;
+  if (live) pair_put<float, 3>(evp, hs, i, rho);
+  for (int k = 0; k < n_mr; ++k) {
+    __syncthreads();
+    {  // w = T_oo^{-1} D_oe rho
+      cx<float> u[6];
+#pragma unroll
+      for (int c = 0; c < 6; ++c) u[c] = mk<float>(0, 0);
+      hop_two<S, false>(lo, g, nb_o, ev, hs, ex, i, part, live, u);
+      inv_two(ti, u, tmp);
+      if (live) pair_put<float, 3>(odp, hs, i, tmp);
+    }
+    __syncthreads();
+    // q = T_ee rho - D_eo w
+    term_two(he, part, tw.e, rho, tmp);
+    hop_two<S, true>(le, g, nb_e, od, hs, ex, i, part, live, tmp);
+    double qr_re = 0, qr_im = 0, qq = 0;
+    if (live) {
+#pragma unroll
+      for (int c = 0; c < 6; ++c) {
+        qr_re += (double)tmp[c].re * rho[c].re + (double)tmp[c].im * rho[c].im;
+        qr_im += (double)tmp[c].re * rho[c].im - (double)tmp[c].im * rho[c].re;
+        qq += (double)tmp[c].re * tmp[c].re + (double)tmp[c].im * tmp[c].im;
+      }
+    }
+    qr_re = wave_sum_n(qr_re, 64);
+    qr_im = wave_sum_n(qr_im, 64);
+    qq = wave_sum_n(qq, 64);
+    if (lane == 0) {
+      red[k & 1][0][wv] = qr_re;
+      red[k & 1][1][wv] = qr_im;
+      red[k & 1][2][wv] = qq;
+    }
+    __syncthreads();
+    double sr = 0, si = 0, sq = 0;
+    for (int v = 0; v < nw; ++v) {
+      sr += red[k & 1][0][v];
+      si += red[k & 1][1][v];
+      sq += red[k & 1][2][v];
+    }
+    cx<float> alpha = mk<float>(0, 0);
+    if (sq > 0) alpha = mk<float>((float)(sr / sq), (float)(si / sq));
+#pragma unroll
+    for (int c = 0; c < 6; ++c) {
+      ee[c] += alpha * rho[c];
+      rho[c] -= alpha * tmp[c];
+    }
+    if (live) pair_put<float, 3>(evp, hs, i, rho);
+  }
+  if (live) pair_put<float, 3>(evp, hs, i, ee);
+  __syncthreads();
+  {  // x_o -= T_oo^{-1} D_oe e_e
+    cx<float> u[6];
+#pragma unroll
+    for (int c = 0; c < 6; ++c) u[c] = mk<float>(0, 0);
+    hop_two<S, false>(lo, g, nb_o, ev, hs, ex, i, part, live, u);
+    inv_two(ti, u, tmp);
+  }
+  if (!live) return;
+#pragma unroll
+  for (int c = 0; c < 6; ++c) x[oo + (long)c * TILE] = x[oo + (long)c * TILE] - tmp[c];
+#pragma unroll
+  for (int c = 0; c < 6; ++c) x[oe + (long)c * TILE] = x[oe + (long)c * TILE] + ee[c];
+}
+
+// Whether a sweep of nwg workgroups takes k_sap_two.  While every SIMD has at most
+// one wavefront of it (two or four a workgroup), the shorter chain wins: 8x8x8x16
+// 54 -> 37 us with 16-bit links and 57 -> 38 with FP32, 256 workgroups of 256 sites
+// 58 -> 40 and 64 -> 42; past that its second round costs more (288 workgroups
+// 74 -> 82 us, six fields on 16^4 73 -> 117).  One field with FP32 links is bound by
+// reading the operator again in every step, so there it also wins once the rounds
+// are full: 384 workgroups 91 -> 86 us, 768 179 -> 141, 2304 556 -> 429 (288: 83, 83).
+template <class S>
+static inline bool sap_two(const Geom& g, int nwg, int K) {
+  const long waves = (long)nwg * 2 * ((g.half + 63) / 64);
+  return waves <= 1024 || (sizeof(S) == 4 && K == 1 && waves >= 1536);
+}
 template <class R, class S>
 void launch_sap(const Geom& g, int colour, const void* U, const R* H, const R* Minv, Twist tw, const cx<R>* b,
                 cx<R>* x, int n_mr, hipStream_t st) {
@@ -346,6 +617,15 @@ void launch_sap(const Geom& g, int colour, const void* U, const R* H, const R* M
 template <class R, class S>
 void launch_sap_multi(const Geom& g, int colour, const void* U, const R* H, const R* Minv, Twist tw, const cx<R>* b,
                       cx<R>* x, int n_mr, int K, long ld, hipStream_t st) {
+  if constexpr (sizeof(R) == 4) {
+    if (sap_two<S>(g, (g.nblocks / 2) * K, K)) {
+      // ev and od (which the staged x, 24 half entries, fits in) and ex
+      const size_t sm = (12 * (size_t)(g.half + 1) + 6 * (size_t)g.half) * sizeof(cxpair<float>);
+      hipLaunchKernelGGL(k_sap_two<S>, dim3((g.nblocks / 2) * K), dim3(2 * ((g.half + 63) / 64 * 64)), sm, st, g, colour,
+                         (const typename store_traits<S>::elem*)U, H, Minv, TwistR<R>(tw), b, x, n_mr, K, ld);
+      return;
+    }
+  }
   size_t sm = 2 * 12 * (size_t)(g.half + 1) * sizeof(cx<R>);
   hipLaunchKernelGGL((k_sap<R, S>), dim3((g.nblocks / 2) * K), dim3(g.half), sm, st, g, colour,
                      (const typename store_traits<S>::elem*)U, H, Minv, TwistR<R>(tw), b, x, n_mr, K, ld);

@@ -162,6 +162,18 @@ __device__ __forceinline__ void herm_mv(const R* hp, long stride, const cx<R> x[
     }
 }
 
+// chirality block b of the packed Hermitian matrix, 9 chunks of 16 bytes
+__device__ __forceinline__ void herm_load(const float* H, long tile, int lane, int b, float h[36]) {
+  const float4* p = reinterpret_cast<const float4*>(H) + (tile * HC + 9 * b) * TILE + lane;
+#pragma unroll
+  for (int c = 0; c < 9; ++c) {
+    const float4 v = p[c * TILE];
+    h[4 * c] = v.x;
+    h[4 * c + 1] = v.y;
+    h[4 * c + 2] = v.z;
+    h[4 * c + 3] = v.w;
+  }
+}
 // both chirality blocks of the packed Hermitian matrix of site `lane` of tile
 // `tile`: FP64 in the tiled layout, FP32 in 16-byte chunks (9 per block)
 __device__ __forceinline__ void herm_apply(const double* H, long tile, int lane, const cx<double> x[12],
@@ -172,18 +184,10 @@ __device__ __forceinline__ void herm_apply(const double* H, long tile, int lane,
 }
 __device__ __forceinline__ void herm_apply(const float* H, long tile, int lane, const cx<float> x[12],
                                            cx<float> y[12]) {
-  const float4* p = reinterpret_cast<const float4*>(H) + tile * HC * TILE + lane;
 #pragma unroll
   for (int b = 0; b < 2; ++b) {
     float h[36];
-#pragma unroll
-    for (int c = 0; c < 9; ++c) {
-      const float4 v = p[(9 * b + c) * TILE];
-      h[4 * c] = v.x;
-      h[4 * c + 1] = v.y;
-      h[4 * c + 2] = v.z;
-      h[4 * c + 3] = v.w;
-    }
+    herm_load(H, tile, lane, b, h);
     herm_mv(h, 1, x + 6 * b, y + 6 * b);
   }
 }
@@ -234,15 +238,14 @@ __device__ __forceinline__ void tinv_load(const float* Tinv, long tile, int lane
     r.h[4 * c + 3] = v.w;
   }
 }
-// rows 3q..3q+2 of the 12: y_i = sum_j T_ij x_j over the chirality block of q
-__device__ __forceinline__ void tinv_mv(const TinvRows& r, int q, const cx<float> x[12], cx<float> y[12]) {
+// the three rows times the chirality block x they act on
+__device__ __forceinline__ void tinv_mv(const TinvRows& r, const cx<float> x[6], cx<float> y[3]) {
 #pragma unroll
   for (int i = 0; i < 3; ++i) {
     cx<float> acc = mk<float>(0, 0);
 #pragma unroll
-    for (int j = 0; j < 6; ++j)
-      cmac(acc, mk<float>(r.h[12 * i + 2 * j], r.h[12 * i + 2 * j + 1]), x[6 * (q >> 1) + j]);
-    y[3 * q + i] = acc;
+    for (int j = 0; j < 6; ++j) cmac(acc, mk<float>(r.h[12 * i + 2 * j], r.h[12 * i + 2 * j + 1]), x[j]);
+    y[i] = acc;
   }
 }
 __device__ __forceinline__ void site_inv(const float*, const float* Tinv, const Geom& g, int B, int s, TwistR<float>,
@@ -252,7 +255,7 @@ __device__ __forceinline__ void site_inv(const float*, const float* Tinv, const 
   for (int q = 0; q < 4; ++q) {
     TinvRows r;
     tinv_load(Tinv, (long)B * (g.half / TILE) + io / TILE, io % TILE, q, r);
-    tinv_mv(r, q, psi, out);
+    tinv_mv(r, psi + 6 * (q >> 1), out + 3 * q);
   }
 }
 
@@ -316,9 +319,10 @@ __device__ __forceinline__ void hop_staged_dir(const typename store_traits<S>::e
 
 template <class R, class S>
 __device__ __forceinline__ void hop_staged(const typename store_traits<S>::elem* U, const cx<R>* in, const cx<R>* lds,
-                                           const Geom& g, int B, int s, const SiteNbr& me, cx<R> out[12]) {
+                                           const Geom& g, int B, int s, const SiteNbr& me, cx<R> out[12], int mu0 = 0,
+                                           int mu1 = 4) {
 #pragma unroll 1
-  for (int mu = 0; mu < g.ndir; ++mu) {
+  for (int mu = mu0; mu < min(mu1, g.ndir); ++mu) {
     switch (mu) {
       case 0: hop_staged_dir<0, R, S>(U, in, lds, g, B, s, me, out); break;
       case 1: hop_staged_dir<1, R, S>(U, in, lds, g, B, s, me, out); break;

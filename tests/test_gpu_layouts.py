@@ -189,3 +189,26 @@ def test_reduced_precision_sap_after_twist_changes(dd, dims, block, prec):
             assert np.linalg.norm(got.reshape(want.shape) - want) <= 1e-5 * np.linalg.norm(want), (mu, mu_odd)
     finally:
         ctx.close()
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp16", "bf16"])
+@pytest.mark.parametrize("dims,block,K", [((4, 12, 8, 24), (2, 6, 2, 6), 16),     # 32 workgroups a field: 128 wavefronts
+                                          ((8, 4, 24, 8), (4, 2, 6, 4), 16),      # 16 workgroups: 64, and 1024 together
+                                          ((8, 8, 16, 24), (2, 2, 2, 2), 2)])     # 768 workgroups: 1536 wavefronts
+def test_sap_on_few_and_many_blocks(dd, dims, block, K, prec):
+    """A sweep of few workgroups (and of one field with FP32 links on many) gives
+    two threads to a pair of slots, the others one: K fields in one call against
+    one at a time, each within 1e-5 of the exact sweep, so 2e-5 apart.  n_MR = 0
+    too, where only the odd sites move."""
+    from paper_1611_01034_amd import synth
+    ctx, _, _ = _case(dd, dims, block, 8601)
+    try:
+        print(f"sap few and many: {dims} {block} {K} {prec}", flush=True)
+        b, x0 = synth.spinor(dims, 8602, nvec=K), synth.spinor(dims, 8603, nvec=K)
+        for n_mr in (0, 3):
+            many = ctx.sap_multi(b, x0, 2, n_mr, prec)
+            for k in (0, K - 1):
+                one = ctx.sap(b[k], x0[k], 2, n_mr, prec)
+                assert np.linalg.norm(one - many[k]) <= 2e-5 * np.linalg.norm(many[k]), (n_mr, k)
+    finally:
+        ctx.close()
