@@ -239,3 +239,21 @@ def test_fp32_arnoldi_steps_of_short_and_long_columns(dd, dims, nv):
             got = np.linalg.norm(bs[k] - ctx.apply_coarse(1, x))
             assert abs(got - want[k]) <= 1e-3 * want[k] + 1e-5 * np.linalg.norm(bs[k]), (m, k)
     ctx.close()
+
+
+@pytest.mark.parametrize("dims,block,nv", [((4, 4, 4, 4), (2, 2, 2, 2), 3),      # 16 sites a block, one group of vectors
+                                           ((4, 12, 4, 12), (2, 6, 2, 6), 9),    # 144 sites, three groups, the last of one
+                                           ((8, 8, 16, 32), (2, 2, 2, 2), 5)])   # 2048 blocks: groups in one workgroup
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_restriction_of_one_field(dd, dims, block, nv, prec):
+    """One field against the K-column restriction: sums of 6 x (sites of a block)
+    products, 1e-12 of the norm in FP64, 1e-6 in FP32 (the other side's FP32 sums)."""
+    ctx, op = make(dd, dims, block)
+    ctx.set_test_vectors(dd.default_params(levels=2, block=[block], nvec=[nv], precision=prec),
+                         [synth.spinor(dims, 94, nvec=nv)])
+    r = synth.spinor(dims, 95, nvec=2)
+    print(f"restriction: {dims} {block} {nv} {prec}", flush=True)
+    many = ctx.restrict_multi(0, r)
+    for k in range(2):
+        assert rel(ctx.restrict(0, r[k]), many[k]) <= (1e-12 if prec == "fp64" else 1e-6)
+    ctx.close()
