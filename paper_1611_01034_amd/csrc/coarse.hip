@@ -892,11 +892,22 @@ __global__ void __launch_bounds__(256) k_coarse_hop_inv_odd(CGeom cg,
     out[(long)site * n + lane] = acc;
   }
 }
+// Whether the odd-even operator of one column on BF16 blocks goes to the matrix
+// cores, as three columns that add up to it (FP16 blocks: the parts of an FP32 entry
+// leave FP16's range).  While the blocks are not what bounds it (us per pair, eight
+// wavefronts on a site's rows and now: 32 sites of n = 32 10.6 and 8.2, of n = 48
+// 15.3 and 10.7; 256 of n = 64 22.2 and 18.2; 512 of n = 48 18.6 and 14.9; but 1024
+// of n = 64 34.8 and 38.7, 2048 of n = 48 45.0 and 50.5).  Relative error of the full
+// stencil against 64 bits, n = 16 to 64: 9e-8 to 1.2e-7 there, 7e-8 here.
+static inline bool one_mfma(int nsites, int n) { return n % 16 == 0 && nsites <= 512; }
 template <class R, class S>
 void launch_coarse_hop_inv_odd(const CGeom& cg, const void* D, const cx<R>* Minv, const cx<R>* in, const cx<R>* base,
                                cx<R>* out, hipStream_t st) {
   const int nodd = cg.nsites - cg.neven;
   auto Dp = (const typename store_traits<S>::elem*)D;
+  if constexpr (std::is_same<S, bf16>::value) {
+    if (one_mfma(cg.nsites, cg.n)) return launch_coarse_hop_inv_odd_one<S>(cg, D, Minv, in, base, out, st);
+  }
   if (one_site(nodd, cg.n))
     hipLaunchKernelGGL((k_coarse_hop_inv_odd_site<R, S>), dim3(nodd), dim3(SITE_T), 0, st, cg, Dp, Minv, in, base, out);
   else
@@ -929,6 +940,9 @@ template <class R, class S>
 void launch_coarse_schur_even(const CGeom& cg, const void* D, double tw, const cx<R>* v, const cx<R>* t, cx<R>* out,
                               int mode, hipStream_t st) {
   auto Dp = (const typename store_traits<S>::elem*)D;
+  if constexpr (std::is_same<S, bf16>::value) {
+    if (one_mfma(cg.nsites, cg.n)) return launch_coarse_schur_even_one<S>(cg, D, tw, v, t, out, mode, st);
+  }
   if (one_site(cg.neven, cg.n))
     hipLaunchKernelGGL((k_coarse_schur_even_site<R, S>), dim3(cg.neven), dim3(SITE_T), 0, st, cg, Dp, (R)tw, v, t, out,
                        mode);

@@ -74,6 +74,35 @@ __device__ __forceinline__ typename mm16<S>::frag b_frag(const cx<float>* x, lon
   return f;
 }
 
+// One FP32 input as three BF16 columns that add up to it: x = hi + mid + lo, eight
+// significant bits each (the 24 bits of FP32).  The products with the stored 16-bit
+// entries are exact in FP32, so the columns' sum is the FP32 product.
+template <class S>
+__device__ __forceinline__ typename mm16<S>::frag b_frag_parts(const cx<float>* x, int j, int lc, float sgn) {
+  using E = typename mm16<S>::e16;
+  typename mm16<S>::frag f;
+  const int r = j >> 1, c = j & 1;
+  const float4* p = reinterpret_cast<const float4*>(x + lc);
+  const float4 a = p[0], b = p[1];
+  const float v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+  E o[8];
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+    const float w = sgn * v[q];
+    const E hi = (E)w;
+    const float w1 = w - (float)hi;
+    const E mid = (E)w1;
+    const E lo = (E)(w1 - (float)mid);
+    o[q] = r == 0 ? hi : r == 1 ? mid : r == 2 ? lo : (E)0.0f;
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    f[2 * q] = c == 0 ? o[2 * q] : o[2 * q + 1];
+    f[2 * q + 1] = c == 0 ? (E)(-(float)o[2 * q + 1]) : o[2 * q];
+  }
+  return f;
+}
+
 // A fragment of a block stored column-major (entry (i,l) at l*n + i): row i,
 // complex columns lc..lc+3
 template <class S>
@@ -352,8 +381,9 @@ constexpr int SPLIT_G = 4;
 constexpr int SPLIT_LD = 20;  // floats per output row of a partial sum (16 used; conflict-free)
 
 // part[gb][row][column] (rows of WT row tiles: all of them, or tile t alone) of the
-// hops of xh (scaled by hs) and the self block on xs (or null); wavefront (gb, t)
-template <class S, int RT, int WT = RT>
+// hops of xh (scaled by hs) and the self block on xs (or null); wavefront (gb, t).
+// ONE: one input column as three (b_frag_parts)
+template <class S, int RT, int WT, bool ONE>
 __device__ __forceinline__ void stencil_split(const CGeom& cg, const typename store_traits<S>::elem* D, int site,
                                               int gb, int t, const cx<float>* xs, const cx<float>* xh, float hs, int K,
                                               long ldv, int lane, float* part) {
@@ -363,20 +393,24 @@ __device__ __forceinline__ void stencil_split(const CGeom& cg, const typename st
   const int cf = cg.nbr[site * 8 + gb], cb = cg.nbr[site * 8 + 4 + gb];
   const typename store_traits<S>::elem* bf_ = D + ((long)site * 5 + 1 + gb) * nn;
   const typename store_traits<S>::elem* bb_ = D + ((long)cb * 5 + 1 + gb) * nn;
+  auto in_frag = [&](const cx<float>* x, int lc, float sgn) {
+    if constexpr (ONE) return b_frag_parts<S>(x, row, lc, sgn);
+    else return b_frag<S>(x, ldv, K, row, lc, sgn);
+  };
   typename mm16<S>::frag af[2 * RT + 1], bf[2 * RT + 1];
 #pragma unroll
   for (int s = 0; s < RT; ++s) {
     const int lc = 16 * s + 4 * grp;
     af[s] = a_frag_col<S>(bf_, n, i, lc);
     af[RT + s] = a_frag_bwd<S>(bb_, n, i, lc, i < h);
-    bf[s] = b_frag<S>(xh + (long)cf * n, ldv, K, row, lc, hs);
-    bf[RT + s] = b_frag<S>(xh + (long)cb * n, ldv, K, row, lc, lc < h ? -hs : hs);
+    bf[s] = in_frag(xh + (long)cf * n, lc, hs);
+    bf[RT + s] = in_frag(xh + (long)cb * n, lc, lc < h ? -hs : hs);
   }
   const bool self = xs && gb < RT;
   if (self) {
     const int lc = 16 * gb + 4 * grp;
     af[2 * RT] = a_frag_col<S>(D + (long)site * 5 * nn, n, i, lc);
-    bf[2 * RT] = b_frag<S>(xs + (long)site * n, ldv, K, row, lc, 1.0f);
+    bf[2 * RT] = in_frag(xs + (long)site * n, lc, 1.0f);
   }
   v4f acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -385,13 +419,15 @@ __device__ __forceinline__ void stencil_split(const CGeom& cg, const typename st
 #pragma unroll
   for (int e = 0; e < 4; ++e) part[(gb * 16 * WT + 16 * (WT == 1 ? 0 : t) + 4 * grp + e) * SPLIT_LD + row] = acc[e];
 }
-// entry (row i, column r) of the sum of the four groups
-template <int WT>
+// entry (row i, column r) of the sum of the four groups; ONE: of the three columns too
+template <int WT, bool ONE>
 __device__ __forceinline__ cx<float> split_sum(const float* part, int i, int r) {
   constexpr int n = 16 * WT;
   cx<float> v = mk<float>(0.f, 0.f);
 #pragma unroll
-  for (int g = 0; g < SPLIT_G; ++g) v += *reinterpret_cast<const cx<float>*>(part + (g * n + i) * SPLIT_LD + 2 * r);
+  for (int p = ONE ? 2 : r; p >= (ONE ? 0 : r); --p)  // the smallest part first
+#pragma unroll
+    for (int g = 0; g < SPLIT_G; ++g) v += *reinterpret_cast<const cx<float>*>(part + (g * n + i) * SPLIT_LD + 2 * p);
   return v;
 }
 
@@ -408,12 +444,12 @@ __global__ void __launch_bounds__(256 * RT) k_coarse_apply_split(CGeom cg,
   __shared__ float part[SPLIT_G * n * SPLIT_LD];
   const int site = sites ? sites[blockIdx.x] : cg.lexord[xcd_remap(blockIdx.x, gridDim.x)];
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  stencil_split<S, RT>(cg, D, site, w / RT, w % RT, x, x, 1.0f, K, ldv, threadIdx.x & 63, part);
+  stencil_split<S, RT, RT, false>(cg, D, site, w / RT, w % RT, x, x, 1.0f, K, ldv, threadIdx.x & 63, part);
   __syncthreads();
   for (int e = threadIdx.x; e < n * K; e += 256 * RT) {
     const int r = e / n, i = e - r * n;
     const long o = (long)r * ldv + (long)site * n + i;
-    cx<float> q = split_sum<RT>(part, i, r);
+    cx<float> q = split_sum<RT, false>(part, i, r);
     const cx<float> xv = x[o];
     const float g = i < n / 2 ? -tw : tw;
     q.re += -g * xv.im;
@@ -426,7 +462,7 @@ __global__ void __launch_bounds__(256 * RT) k_coarse_apply_split(CGeom cg,
 // so each of n/16 workgroups of four wavefronts takes 16 of them (on one XCD) and a
 // small grid spreads over more CUs, whose load paths are what a workgroup per site
 // waits for (sizes measured: even_rows).
-template <class S, int RT, int WT>
+template <class S, int RT, int WT, bool ONE>
 __global__ void __launch_bounds__(256 * WT) k_coarse_schur_even_split(CGeom cg,
                                                                       const typename store_traits<S>::elem* __restrict__ D,
                                                                       float tw, int K, long ldv,
@@ -442,11 +478,11 @@ __global__ void __launch_bounds__(256 * WT) k_coarse_schur_even_split(CGeom cg,
   const bool out = r < K;
   const long o = (long)(out ? r : 0) * ldv + (long)site * n + i;
   const cx<float> x = v[o];
-  stencil_split<S, RT, WT>(cg, D, site, w / WT, WT == 1 ? t0 : w % WT, mode == 0 ? v : nullptr, t, -1.0f, K, ldv,
+  stencil_split<S, RT, WT, ONE>(cg, D, site, w / WT, WT == 1 ? t0 : w % WT, mode == 0 ? v : nullptr, t, -1.0f, K, ldv,
                            threadIdx.x & 63, part);
   __syncthreads();
   if (!out) return;
-  cx<float> q = split_sum<WT>(part, il, r);
+  cx<float> q = split_sum<WT, ONE>(part, il, r);
   if (mode == 0) {
     const float g = i < n / 2 ? -tw : tw;
     q.re += -g * x.im;
@@ -457,7 +493,7 @@ __global__ void __launch_bounds__(256 * WT) k_coarse_schur_even_split(CGeom cg,
   y[o] = q;
 }
 
-template <class S, int RT>
+template <class S, int RT, bool ONE>
 __global__ void __launch_bounds__(256 * RT) k_coarse_hop_inv_odd_split(CGeom cg,
                                                                        const typename store_traits<S>::elem* __restrict__ D,
                                                                        const cx<float>* __restrict__ Minv, int K,
@@ -480,10 +516,10 @@ __global__ void __launch_bounds__(256 * RT) k_coarse_hop_inv_odd_split(CGeom cg,
 #pragma unroll
   for (int l = 0; l < RT; ++l) m[l] = M[(long)(q * RT + l) * n + i0];
   const cx<float> bv = base ? base[o] : mk<float>(0.f, 0.f);
-  stencil_split<S, RT>(cg, D, site, w / RT, w % RT, nullptr, x, 1.0f, K, ldv, threadIdx.x & 63, part);
+  stencil_split<S, RT, RT, ONE>(cg, D, site, w / RT, w % RT, nullptr, x, 1.0f, K, ldv, threadIdx.x & 63, part);
   __syncthreads();
   if (out) {
-    const cx<float> u = split_sum<RT>(part, i0, q);
+    const cx<float> u = split_sum<RT, ONE>(part, i0, q);
     us[i0 * K + q] = base ? bv - u : u;
   }
   __syncthreads();
@@ -698,6 +734,19 @@ static inline int nt_of(int K) { return K <= 8 ? 1 : 2; }
     }                                                                                     \
   } while (0)
 
+template <class S, int RT>
+constexpr auto EVEN_ROWS = k_coarse_schur_even_split<S, RT, 1, false>;
+template <class S, int RT>
+constexpr auto EVEN_SITE = k_coarse_schur_even_split<S, RT, RT, false>;
+template <class S, int RT>
+constexpr auto HOP_INV_ODD = k_coarse_hop_inv_odd_split<S, RT, false>;
+template <class S, int RT>
+constexpr auto EVEN_ROWS_ONE = k_coarse_schur_even_split<S, RT, 1, true>;
+template <class S, int RT>
+constexpr auto EVEN_SITE_ONE = k_coarse_schur_even_split<S, RT, RT, true>;
+template <class S, int RT>
+constexpr auto HOP_INV_ODD_ONE = k_coarse_hop_inv_odd_split<S, RT, true>;
+
 // instantiate KERNEL<S, RT> for RT = n / 16
 #define SPLIT_DISPATCH(KERNEL, ...)                                                                  \
   do {                                                                                               \
@@ -738,10 +787,6 @@ void launch_coarse_apply_mrhs(const CGeom& cg, const void* D, double tw, int K, 
 // once on a CU).  At 512 sites of n = 32 and 48 it takes 9.3 and 12.8 for 8.6 and
 // 12.4.
 static inline bool even_rows(int neven, int n) { return n == 64 || neven < 256; }
-template <class S, int RT>
-constexpr auto EVEN_ROWS = k_coarse_schur_even_split<S, RT, 1>;
-template <class S, int RT>
-constexpr auto EVEN_SITE = k_coarse_schur_even_split<S, RT, RT>;
 
 template <class S>
 void launch_coarse_schur_even_mrhs(const CGeom& cg, const void* D, double tw, int K, long ldv, const cx<float>* v,
@@ -771,11 +816,36 @@ void launch_coarse_hop_inv_odd_mrhs(const CGeom& cg, const void* D, const cx<flo
   auto Dp = (const typename store_traits<S>::elem*)D;
   if (split_sites(nodd, cg.n, K)) {
     const size_t ss = (size_t)17 * cg.n * K * sizeof(cx<float>);  // us and the 16 partial sums
-    SPLIT_DISPATCH(k_coarse_hop_inv_odd_split, grid, dim3(16 * cg.n), ss, st, cg, Dp, Minv, K, ldv, x, base, y);
+    SPLIT_DISPATCH(HOP_INV_ODD, grid, dim3(16 * cg.n), ss, st, cg, Dp, Minv, K, ldv, x, base, y);
     return;
   }
   MRHS_DISPATCH_BIG(k_coarse_hop_inv_odd_mrhs, grid, blk, sm, st, cg, Dp, Minv, K, ldv, x, base, y);
 }
+
+// one FP32 column on 16-bit blocks (three BF16 columns of the matrix cores)
+template <class S>
+void launch_coarse_schur_even_one(const CGeom& cg, const void* D, double tw, const cx<float>* v, const cx<float>* t,
+                                  cx<float>* y, int mode, hipStream_t st) {
+  auto Dp = (const typename store_traits<S>::elem*)D;
+  if (even_rows(cg.neven, cg.n)) {
+    SPLIT_DISPATCH(EVEN_ROWS_ONE, dim3(cg.neven * (cg.n / 16)), dim3(256), 0, st, cg, Dp, (float)tw, 1, 0L, v, t, y,
+                   mode);
+  } else {
+    SPLIT_DISPATCH(EVEN_SITE_ONE, dim3(cg.neven), dim3(16 * cg.n), 0, st, cg, Dp, (float)tw, 1, 0L, v, t, y, mode);
+  }
+}
+template <class S>
+void launch_coarse_hop_inv_odd_one(const CGeom& cg, const void* D, const cx<float>* Minv, const cx<float>* x,
+                                   const cx<float>* base, cx<float>* y, hipStream_t st) {
+  auto Dp = (const typename store_traits<S>::elem*)D;
+  const size_t ss = (size_t)17 * cg.n * sizeof(cx<float>);
+  SPLIT_DISPATCH(HOP_INV_ODD_ONE, dim3(cg.nsites - cg.neven), dim3(16 * cg.n), ss, st, cg, Dp, Minv, 1, 0L, x, base,
+                 y);
+}
+template void launch_coarse_schur_even_one<bf16>(const CGeom&, const void*, double, const cx<float>*, const cx<float>*,
+                                                 cx<float>*, int, hipStream_t);
+template void launch_coarse_hop_inv_odd_one<bf16>(const CGeom&, const void*, const cx<float>*, const cx<float>*,
+                                                  const cx<float>*, cx<float>*, hipStream_t);
 
 template <class S>
 void launch_coarse_sap_mrhs(const CGeom& cg, const void* D, double tw, int nblk_colour, int bsz, const int* blk_sites,

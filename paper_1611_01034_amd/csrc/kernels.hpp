@@ -281,6 +281,13 @@ void launch_coarse_schur_even_mrhs(const CGeom& cg, const void* D, double tw, in
                                    const cx<float>* t, cx<float>* y, int mode, hipStream_t st);
 // SAP colour sweep of an intermediate level for K fields (K <= 16), one
 // workgroup per block (bsz <= 16 sites), matrix cores
+// odd-even operator of one FP32 column on BF16 blocks of n = 16, 32, 48 or 64
+template <class S>
+void launch_coarse_schur_even_one(const CGeom& cg, const void* D, double tw, const cx<float>* v, const cx<float>* t,
+                                  cx<float>* y, int mode, hipStream_t st);
+template <class S>
+void launch_coarse_hop_inv_odd_one(const CGeom& cg, const void* D, const cx<float>* Minv, const cx<float>* x,
+                                   const cx<float>* base, cx<float>* y, hipStream_t st);
 template <class S>
 void launch_coarse_sap_mrhs(const CGeom& cg, const void* D, double tw, int nblk_colour, int bsz, const int* blk_sites,
                             const int* blk_nbr, const cx<float>* r, cx<float>* x, int n_mr, int K, long ld,

@@ -133,3 +133,30 @@ def test_even_rows_alone_on_few_sites(dims, nv):
             got = ctx.apply_coarse_schur_multi(1, xs[:K])
             for k in range(K):
                 assert np.linalg.norm(got[k] - many[k]) <= 2e-4 * np.linalg.norm(many[k]), (K, k)
+
+
+@pytest.mark.parametrize("prec", ["bf16", "fp16"])
+@pytest.mark.parametrize("dims,nv", [((4, 4, 4, 4), 8), ((4, 4, 4, 8), 16), ((4, 4, 8, 8), 24), ((8, 8, 8, 16), 32),
+                                     ((8, 8, 8, 24), 16)])   # the last: 768 sites
+def test_one_column_odd_even_solve(dims, nv, prec):
+    """The coarsest solve of one column (BF16 blocks on up to 512 sites: the matrix
+    cores, its FP32 entries in three parts) to 1e-4, b on the even sites only: the
+    even-site residual by the single-column stencil is that of the odd-even system,
+    so 1e-4 of b and the 1e-5 of the FP32 operator.  Entries of b over twelve
+    decades, so that every part of an entry counts somewhere."""
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    from paper_1611_01034_amd import ddamg, synth
+    block = (2, 2, 2, 2)
+    with ddamg.DDAMG(dims, block, KAPPA, CSW, MU) as ctx:
+        ctx.set_gauge(synth.gauge_field(dims, 0.3, 9501))
+        p = ddamg.default_params(levels=2, block=[block], nvec=[nv], coarse_mu_factor=5.0, precision=prec,
+                                 coarse_tol=1e-4, coarse_max_iter=500, coarse_restart=30)
+        ctx.set_test_vectors(p, [synth.spinor(dims, 9502, nvec=nv)])
+        cd, n = ctx.level_info(1)
+        even = 1 - np.indices(cd).sum(axis=0)[..., None] % 2
+        b = even * synth.gaussian(cd + (n,), 9503)
+        for v in (b, b * 10.0 ** np.random.default_rng(9504).uniform(-6, 6, b.shape)):
+            print(f"one column: {dims} n {n} {prec}", flush=True)
+            r = even * (v - ctx.apply_coarse(1, ctx.coarse_solve(1, v)))
+            assert np.linalg.norm(r) <= 1.1e-4 * np.linalg.norm(v)
