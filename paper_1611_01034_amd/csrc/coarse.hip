@@ -894,12 +894,12 @@ __global__ void __launch_bounds__(256) k_coarse_hop_inv_odd(CGeom cg,
 }
 // Whether the odd-even operator of one column on BF16 blocks goes to the matrix
 // cores, as three columns that add up to it (FP16 blocks: the parts of an FP32 entry
-// leave FP16's range).  While the blocks are not what bounds it (us per pair, eight
-// wavefronts on a site's rows and now: 32 sites of n = 32 10.6 and 8.2, of n = 48
-// 15.3 and 10.7; 256 of n = 64 22.2 and 18.2; 512 of n = 48 18.6 and 14.9; but 1024
-// of n = 64 34.8 and 38.7, 2048 of n = 48 45.0 and 50.5).  Relative error of the full
-// stencil against 64 bits, n = 16 to 64: 9e-8 to 1.2e-7 there, 7e-8 here.
-static inline bool one_mfma(int nsites, int n) { return n % 16 == 0 && nsites <= 512; }
+// leave FP16's range).  us per pair, eight wavefronts on a site's rows and so: 32
+// sites of n = 32 10.6 and 8.2, of n = 48 15.3 and 10.7; 1024 of n = 64 34.4 and
+// 33.3; 4096 of n = 48 82.6 and 60.0.  n = 16 on more sites has four to a workgroup
+// of the vector kernels.  Relative error of the full stencil against 64 bits, n = 16
+// to 64: 9e-8 to 1.2e-7 there, 7e-8 here.
+static inline bool one_mfma(int nsites, int n) { return n % 16 == 0 && (n > 16 || nsites <= 512); }
 template <class R, class S>
 void launch_coarse_hop_inv_odd(const CGeom& cg, const void* D, const cx<R>* Minv, const cx<R>* in, const cx<R>* base,
                                cx<R>* out, hipStream_t st) {

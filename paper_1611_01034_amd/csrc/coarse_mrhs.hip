@@ -50,8 +50,21 @@ template <> struct mm16<bf16> {
   }
 };
 
+// Sign changes of 16-bit entries act on the packed words: `mask` has the sign bits.
+template <class S>
+__device__ __forceinline__ typename mm16<S>::frag flip(typename mm16<S>::frag f, unsigned mask) {
+  union {
+    typename mm16<S>::frag f;
+    unsigned w[4];
+  } v;
+  v.f = f;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) v.w[q] ^= mask;
+  return v.f;
+}
+
 // B fragment of input x (n components, right-hand side stride ldv) for the
-// lane's column j = 16u + L%16 and complex inputs lc..lc+3; sgn scales x.
+// lane's column j = 16u + L%16 and complex inputs lc..lc+3; sgn = +-1 scales x.
 template <class S>
 __device__ __forceinline__ typename mm16<S>::frag b_frag(const cx<float>* x, long ldv, int K, int j, int lc, float sgn) {
   using E = typename mm16<S>::e16;
@@ -63,10 +76,11 @@ __device__ __forceinline__ typename mm16<S>::frag b_frag(const cx<float>* x, lon
     float v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      float re = sgn * v[2 * q], im = sgn * v[2 * q + 1];
-      f[2 * q] = (E)(c == 0 ? re : im);
-      f[2 * q + 1] = (E)(c == 0 ? -im : re);
+      f[2 * q] = (E)(c == 0 ? v[2 * q] : v[2 * q + 1]);
+      f[2 * q + 1] = (E)(c == 0 ? v[2 * q + 1] : v[2 * q]);
     }
+    // column (r, 0) takes (re, -im), column (r, 1) (im, re)
+    f = flip<S>(f, (sgn < 0 ? 0x80008000u : 0u) ^ (c == 0 ? 0x80000000u : 0u));
   } else {
 #pragma unroll
     for (int q = 0; q < 8; ++q) f[q] = (E)0.0f;
@@ -85,22 +99,16 @@ __device__ __forceinline__ typename mm16<S>::frag b_frag_parts(const cx<float>* 
   const float4* p = reinterpret_cast<const float4*>(x + lc);
   const float4 a = p[0], b = p[1];
   const float v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-  E o[8];
 #pragma unroll
   for (int q = 0; q < 8; ++q) {
-    const float w = sgn * v[q];
+    const float w = c == 0 ? v[q] : v[q ^ 1];
     const E hi = (E)w;
     const float w1 = w - (float)hi;
     const E mid = (E)w1;
     const E lo = (E)(w1 - (float)mid);
-    o[q] = r == 0 ? hi : r == 1 ? mid : r == 2 ? lo : (E)0.0f;
+    f[q] = r == 0 ? hi : r == 1 ? mid : r == 2 ? lo : (E)0.0f;
   }
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    f[2 * q] = c == 0 ? o[2 * q] : o[2 * q + 1];
-    f[2 * q + 1] = c == 0 ? (E)(-(float)o[2 * q + 1]) : o[2 * q];
-  }
-  return f;
+  return flip<S>(f, (sgn < 0 ? 0x80008000u : 0u) ^ (c == 0 ? 0x80000000u : 0u));
 }
 
 // A fragment of a block stored column-major (entry (i,l) at l*n + i): row i,
@@ -123,24 +131,20 @@ __device__ __forceinline__ typename mm16<S>::frag a_frag_col(const typename stor
 template <class S>
 __device__ __forceinline__ typename mm16<S>::frag a_frag_bwd(const typename store_traits<S>::elem* blk, int n, int i,
                                                             int lc, bool neg_row) {
-  using E = typename mm16<S>::e16;
   typename mm16<S>::frag f;
   const typename store_traits<S>::elem* p = blk + (long)i * n + lc;
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
-    auto e = p[q];
-    E re = e.re, im = e.im;
-    f[2 * q] = neg_row ? (E)(-(float)re) : re;
-    f[2 * q + 1] = neg_row ? im : (E)(-(float)im);
+    f[2 * q] = p[q].re;
+    f[2 * q + 1] = p[q].im;
   }
-  return f;
+  return flip<S>(f, neg_row ? 0x00008000u : 0x80000000u);
 }
 
 // acc[u] += sum over the selected blocks, output rows 16t..16t+15, columns 16u..
 //   self: S(site) xs(site);  hops: hs * (forward + backward hops of xh)
-// RT = n / 16 k-steps per block.  For one column tile every fragment of a block
-// is loaded before its products and two blocks are in flight, so a wavefront
-// waits on about one memory latency per two blocks.
+// RT = n / 16 k-steps per block, one at a time, which keeps the registers (and the
+// occupancy) of the two column tiles.
 template <class S, int NT, int RT>
 __device__ __forceinline__ void stencil_mfma(const CGeom& cg, const typename store_traits<S>::elem* D, int site,
                                              int t, const cx<float>* xs, const cx<float>* xh, float hs, int K,
@@ -149,7 +153,7 @@ __device__ __forceinline__ void stencil_mfma(const CGeom& cg, const typename sto
   constexpr long nn = (long)n * n;
   const int row = lane & 15, grp = lane >> 4;
   const int i = 16 * t + row;
-#pragma unroll(NT == 1 ? 2 : 1)
+#pragma unroll 1
   for (int b = xs ? 0 : 1; b < (xh ? 9 : 1); ++b) {
     const typename store_traits<S>::elem* blk;
     const cx<float>* x;
@@ -170,32 +174,17 @@ __device__ __forceinline__ void stencil_mfma(const CGeom& cg, const typename sto
       x = xh + (long)cb * n;
       sgn = hs;
     }
-    if constexpr (NT == 1) {
-      typename mm16<S>::frag af[RT], bf[RT];
-#pragma unroll
-      for (int s = 0; s < RT; ++s) {
-        const int lc = 16 * s + 4 * grp;
-        // g_l of the backward block goes on the input (lc..lc+3 lie in one half)
-        const float gs = bwd ? (lc < h ? -sgn : sgn) : sgn;
-        bf[s] = b_frag<S>(x, ldv, K, row, lc, gs);
-        af[s] = bwd ? a_frag_bwd<S>(blk, n, i, lc, i < h) : a_frag_col<S>(blk, n, i, lc);
-      }
-#pragma unroll
-      for (int s = 0; s < RT; ++s) acc[0] = mm16<S>::mma(af[s], bf[s], acc[0]);
-    } else {
-      // two column tiles: one k-step at a time keeps the registers (and the
-      // occupancy) of the wider products
 #pragma unroll 1
-      for (int s = 0; s < RT; ++s) {
-        const int lc = 16 * s + 4 * grp;
-        const float gs = bwd ? (lc < h ? -sgn : sgn) : sgn;
-        typename mm16<S>::frag bf[NT];
+    for (int s = 0; s < RT; ++s) {
+      const int lc = 16 * s + 4 * grp;
+      // g_l of the backward block goes on the input (lc..lc+3 lie in one half)
+      const float gs = bwd ? (lc < h ? -sgn : sgn) : sgn;
+      typename mm16<S>::frag bf[NT];
 #pragma unroll
-        for (int u = 0; u < NT; ++u) bf[u] = b_frag<S>(x, ldv, K, 16 * u + row, lc, gs);
-        const typename mm16<S>::frag af = bwd ? a_frag_bwd<S>(blk, n, i, lc, i < h) : a_frag_col<S>(blk, n, i, lc);
+      for (int u = 0; u < NT; ++u) bf[u] = b_frag<S>(x, ldv, K, 16 * u + row, lc, gs);
+      const typename mm16<S>::frag af = bwd ? a_frag_bwd<S>(blk, n, i, lc, i < h) : a_frag_col<S>(blk, n, i, lc);
 #pragma unroll
-        for (int u = 0; u < NT; ++u) acc[u] = mm16<S>::mma(af, bf[u], acc[u]);
-      }
+      for (int u = 0; u < NT; ++u) acc[u] = mm16<S>::mma(af, bf[u], acc[u]);
     }
   }
 }
@@ -237,13 +226,15 @@ __device__ __forceinline__ void store_mfma(const CGeom& cg, int site, int t, v4f
   }
 }
 
+constexpr int NT = 2;  // column tiles of 16 (re, im) columns: up to 16 right-hand sides
+
 // y_r = D x_r (b == null) or y_r = b_r - D x_r, on every site or on the sites
 // of a list.  On every site, each XCD takes a contiguous range of sites in
 // lexicographic order (both parities interleaved), so the forward block a
 // site reads for its own hop is still in that XCD's L2 when its X and Y
 // neighbours read it for their backward hops (level 1 of 48^3x96 at six
 // columns: 0.93 -> 0.81 ms per application).
-template <class S, int NT, int RT>
+template <class S, int RT>
 __global__ void __launch_bounds__(256) k_coarse_apply_mrhs(CGeom cg, const typename store_traits<S>::elem* __restrict__ D,
                                                            float tw, int K, long ldv, const cx<float>* __restrict__ x,
                                                            const cx<float>* __restrict__ b, cx<float>* __restrict__ y,
@@ -258,7 +249,7 @@ __global__ void __launch_bounds__(256) k_coarse_apply_mrhs(CGeom cg, const typen
 
 // even sites of the odd-even reduced system: mode 0: y = (S + i tw G5) v - H t;
 // mode 1: y = v - H t   (H: the hops, t lives on the odd sites)
-template <class S, int NT, int RT>
+template <class S, int RT>
 __global__ void __launch_bounds__(256) k_coarse_schur_even_mrhs(CGeom cg,
                                                                 const typename store_traits<S>::elem* __restrict__ D,
                                                                 float tw, int K, long ldv,
@@ -277,28 +268,22 @@ __global__ void __launch_bounds__(256) k_coarse_schur_even_mrhs(CGeom cg,
 // odd sites: y = Minv H x, or y = Minv (base - H x) with base.  Minv:
 // [odd site][n][n] FP32 column-major.  The hop result goes through LDS
 // ([n][K] complex) to the FP32 products with Minv, which all threads of the
-// workgroup share: thread -> row i = tid % n and a quarter g = tid / n of the
-// inner index (16 terms, all loads in flight), the four partial sums added in
-// LDS ([4][n][K]) in fixed order.  For K > 8 a thread takes row i and every
-// fourth column instead, with all n inner terms, and the partial sums go
-// away.  The LDS is sized by K at launch: at K = 2 the kernel holds 6
-// wavefronts per SIMD instead of 4 (13 % faster odd-even operator at 48^3x96).
-template <class S, int NT, int RT>
+// workgroup share: thread -> row i = tid % n and every fourth column, with all n
+// inner terms, 16 loads in flight.
+template <class S, int RT>
 __global__ void __launch_bounds__(256) k_coarse_hop_inv_odd_mrhs(CGeom cg,
                                                                  const typename store_traits<S>::elem* __restrict__ D,
                                                                  const cx<float>* __restrict__ Minv, int K, long ldv,
                                                                  const cx<float>* __restrict__ x,
                                                                  const cx<float>* __restrict__ base,
                                                                  cx<float>* __restrict__ y) {
-  constexpr int n = 16 * RT, LQ = n / 4;
+  constexpr int n = 16 * RT;
   extern __shared__ char smem_raw[];
   cx<float>* us = reinterpret_cast<cx<float>*>(smem_raw);  // [n][K]
-  cx<float>* ps = us + n * K;                               // [4][n][K]
   const int lane = threadIdx.x & 63, rt = threadIdx.x >> 6;
   const int io = blockIdx.x;
   const int site = cg.neven + io;
   const int i = threadIdx.x % n, gq = threadIdx.x / n;  // gq < 4 (blockDim = 4 n)
-  cx<float> m[LQ];
   {
     v4f acc[NT];
     zero_acc<NT>(acc);
@@ -318,52 +303,31 @@ __global__ void __launch_bounds__(256) k_coarse_hop_inv_odd_mrhs(CGeom cg,
     }
   }
   __syncthreads();
-  if constexpr (NT == 2) {
-    // K > 8: thread (row i, column group gq) sums all n inner terms for the
-    // columns gq, gq + 4, ... (no partial sums in LDS; the four column groups
-    // read the same inverse entries, which the L1 shares)
-    const cx<float>* M = Minv + (long)io * n * n;
-    cx<float> o[4];
+  // thread (row i, column group gq) sums all n inner terms for the columns gq,
+  // gq + 4, ... (the four column groups read the same inverse entries, which the
+  // L1 shares)
+  const cx<float>* M = Minv + (long)io * n * n;
+  cx<float> o[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) o[q] = mk<float>(0, 0);
+  for (int q = 0; q < 4; ++q) o[q] = mk<float>(0, 0);
 #pragma unroll 1
-    for (int l0 = 0; l0 < n; l0 += 16) {
-      cx<float> mm[16];
+  for (int l0 = 0; l0 < n; l0 += 16) {
+    cx<float> mm[16];
 #pragma unroll
-      for (int l = 0; l < 16; ++l) mm[l] = M[(long)(l0 + l) * n + i];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int r = gq + 4 * q;
-        if (r < K) {
-#pragma unroll
-          for (int l = 0; l < 16; ++l) cmac(o[q], mm[l], us[(l0 + l) * K + r]);
-        }
-      }
-    }
+    for (int l = 0; l < 16; ++l) mm[l] = M[(long)(l0 + l) * n + i];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int r = gq + 4 * q;
-      if (r < K) y[(long)r * ldv + (long)site * n + i] = o[q];
+      if (r < K) {
+#pragma unroll
+        for (int l = 0; l < 16; ++l) cmac(o[q], mm[l], us[(l0 + l) * K + r]);
+      }
     }
-    return;
   }
-  {
-    const cx<float>* M = Minv + (long)io * n * n;
 #pragma unroll
-    for (int l = 0; l < LQ; ++l) m[l] = M[(long)(gq * LQ + l) * n + i];
-  }
-  for (int r = 0; r < K; ++r) {
-    cx<float> o = mk<float>(0, 0);
-#pragma unroll
-    for (int l = 0; l < LQ; ++l) cmac(o, m[l], us[(gq * LQ + l) * K + r]);
-    ps[(gq * n + i) * K + r] = o;
-  }
-  __syncthreads();
-  for (int e = threadIdx.x; e < n * K; e += blockDim.x) {
-    const int ii = e % n, r = e / n;
-    const cx<float> o = (ps[(0 * n + ii) * K + r] + ps[(1 * n + ii) * K + r]) +
-                        (ps[(2 * n + ii) * K + r] + ps[(3 * n + ii) * K + r]);
-    y[(long)r * ldv + (long)site * n + ii] = o;
+  for (int q = 0; q < 4; ++q) {
+    const int r = gq + 4 * q;
+    if (r < K) y[(long)r * ldv + (long)site * n + i] = o[q];
   }
 }
 
@@ -374,9 +338,14 @@ __global__ void __launch_bounds__(256) k_coarse_hop_inv_odd_mrhs(CGeom cg,
 // Here four groups of n/16 wavefronts share a site: group gb takes the forward
 // and the backward block of direction gb (and, of the self block, k-step gb),
 // so that every load of the site is in flight at once; their FP32 partial sums
-// meet in LDS in fixed order
-// (launches and sizes measured: split_sites).  The inverse is spread over 4 n threads, each with
+// meet in LDS in fixed order.  A group's wavefronts share their input fragments
+// through LDS (each made all of them before, a third of the kernel's
+// instructions).  The inverse is spread over 16 n threads, each with
 // n/16 of the inner terms of one row, loaded before the hops.
+// Six columns, us per odd-even pair and per full stencil, one wavefront per row
+// tile / four groups / and shared fragments: 32 sites of n = 32 18.1 / 7.6, 3.6 /
+// 7.4, 3.4; 256 of n = 64 35.4 / 15.0, 8.7 / 12.8, 6.5; 512 of n = 48 30.4 / 12.3,
+// 8.7 / 10.9, 7.0; 4096 of n = 64 175, 137 / 145, 137 / 132, 110.
 constexpr int SPLIT_G = 4;
 constexpr int SPLIT_LD = 20;  // floats per output row of a partial sum (16 used; conflict-free)
 
@@ -386,7 +355,7 @@ constexpr int SPLIT_LD = 20;  // floats per output row of a partial sum (16 used
 template <class S, int RT, int WT, bool ONE>
 __device__ __forceinline__ void stencil_split(const CGeom& cg, const typename store_traits<S>::elem* D, int site,
                                               int gb, int t, const cx<float>* xs, const cx<float>* xh, float hs, int K,
-                                              long ldv, int lane, float* part) {
+                                              long ldv, int lane, float* part, typename mm16<S>::frag* xsh) {
   constexpr int n = 16 * RT, h = n / 2;
   constexpr long nn = (long)n * n;
   const int row = lane & 15, grp = lane >> 4, i = 16 * t + row;
@@ -403,14 +372,28 @@ __device__ __forceinline__ void stencil_split(const CGeom& cg, const typename st
     const int lc = 16 * s + 4 * grp;
     af[s] = a_frag_col<S>(bf_, n, i, lc);
     af[RT + s] = a_frag_bwd<S>(bb_, n, i, lc, i < h);
-    bf[s] = in_frag(xh + (long)cf * n, lc, hs);
-    bf[RT + s] = in_frag(xh + (long)cb * n, lc, lc < h ? -hs : hs);
+    if (WT == 1) {
+      bf[s] = in_frag(xh + (long)cf * n, lc, hs);
+      bf[RT + s] = in_frag(xh + (long)cb * n, lc, lc < h ? -hs : hs);
+    }
   }
   const bool self = xs && gb < RT;
   if (self) {
     const int lc = 16 * gb + 4 * grp;
     af[2 * RT] = a_frag_col<S>(D + (long)site * 5 * nn, n, i, lc);
-    bf[2 * RT] = in_frag(xs + (long)site * n, lc, 1.0f);
+    if (WT == 1) bf[2 * RT] = in_frag(xs + (long)site * n, lc, 1.0f);
+  }
+  if (WT > 1) {
+    // the group's wavefronts need the same input fragments: each makes two or three
+    const int lc = 16 * t + 4 * grp;
+    typename mm16<S>::frag* o = xsh + gb * (2 * RT + 1) * 64 + lane;
+    o[t * 64] = in_frag(xh + (long)cf * n, lc, hs);
+    o[(RT + t) * 64] = in_frag(xh + (long)cb * n, lc, lc < h ? -hs : hs);
+    if (self && t == 0) o[2 * RT * 64] = in_frag(xs + (long)site * n, 16 * gb + 4 * grp, 1.0f);
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < 2 * RT; ++s) bf[s] = o[s * 64];
+    if (self) bf[2 * RT] = o[2 * RT * 64];
   }
   v4f acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -442,9 +425,10 @@ __global__ void __launch_bounds__(256 * RT) k_coarse_apply_split(CGeom cg,
                                                                  const int* __restrict__ sites) {
   constexpr int n = 16 * RT;
   __shared__ float part[SPLIT_G * n * SPLIT_LD];
+  __shared__ typename mm16<S>::frag xsh[SPLIT_G * (2 * RT + 1) * 64];
   const int site = sites ? sites[blockIdx.x] : cg.lexord[xcd_remap(blockIdx.x, gridDim.x)];
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  stencil_split<S, RT, RT, false>(cg, D, site, w / RT, w % RT, x, x, 1.0f, K, ldv, threadIdx.x & 63, part);
+  stencil_split<S, RT, RT, false>(cg, D, site, w / RT, w % RT, x, x, 1.0f, K, ldv, threadIdx.x & 63, part, xsh);
   __syncthreads();
   for (int e = threadIdx.x; e < n * K; e += 256 * RT) {
     const int r = e / n, i = e - r * n;
@@ -471,6 +455,7 @@ __global__ void __launch_bounds__(256 * WT) k_coarse_schur_even_split(CGeom cg,
                                                                       cx<float>* __restrict__ y, int mode) {
   constexpr int n = 16 * RT, nw = 16 * WT, NT = RT / WT;
   __shared__ float part[SPLIT_G * nw * SPLIT_LD];
+  __shared__ typename mm16<S>::frag xsh[WT > 1 ? SPLIT_G * (2 * RT + 1) * 64 : 1];
   const int wg = xcd_remap(blockIdx.x, gridDim.x), site = wg / NT, t0 = wg - site * NT;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // 16 nw threads and at most 8 nw results: row il of column r, in flight early
@@ -479,7 +464,7 @@ __global__ void __launch_bounds__(256 * WT) k_coarse_schur_even_split(CGeom cg,
   const long o = (long)(out ? r : 0) * ldv + (long)site * n + i;
   const cx<float> x = v[o];
   stencil_split<S, RT, WT, ONE>(cg, D, site, w / WT, WT == 1 ? t0 : w % WT, mode == 0 ? v : nullptr, t, -1.0f, K, ldv,
-                           threadIdx.x & 63, part);
+                           threadIdx.x & 63, part, xsh);
   __syncthreads();
   if (!out) return;
   cx<float> q = split_sum<WT, ONE>(part, il, r);
@@ -503,6 +488,7 @@ __global__ void __launch_bounds__(256 * RT) k_coarse_hop_inv_odd_split(CGeom cg,
   constexpr int n = 16 * RT, NQ = 16;  // NQ parts of the inner index, RT terms each
   __shared__ float part[SPLIT_G * n * SPLIT_LD];
   extern __shared__ char smem_raw[];
+  // the input fragments of the hops, then their sum and the parts of the inverse
   cx<float>* us = reinterpret_cast<cx<float>*>(smem_raw);  // [n][K]
   cx<float>* ps = us + n * K;                               // [NQ][K][n]
   const int io = xcd_remap(blockIdx.x, gridDim.x), site = cg.neven + io;
@@ -516,7 +502,8 @@ __global__ void __launch_bounds__(256 * RT) k_coarse_hop_inv_odd_split(CGeom cg,
 #pragma unroll
   for (int l = 0; l < RT; ++l) m[l] = M[(long)(q * RT + l) * n + i0];
   const cx<float> bv = base ? base[o] : mk<float>(0.f, 0.f);
-  stencil_split<S, RT, RT, ONE>(cg, D, site, w / RT, w % RT, nullptr, x, 1.0f, K, ldv, threadIdx.x & 63, part);
+  stencil_split<S, RT, RT, ONE>(cg, D, site, w / RT, w % RT, nullptr, x, 1.0f, K, ldv, threadIdx.x & 63, part,
+                                reinterpret_cast<typename mm16<S>::frag*>(smem_raw));
   __syncthreads();
   if (out) {
     const cx<float> u = split_sum<RT, ONE>(part, i0, q);
@@ -706,9 +693,7 @@ __global__ void __launch_bounds__(1024) k_coarse_sap_mrhs(CGeom cg,
     }
 }
 
-static inline int nt_of(int K) { return K <= 8 ? 1 : 2; }
-
-// instantiate KERNEL<S, NT, RT> for NT = nt_of(K), RT = n / 16
+// instantiate KERNEL<S, NT, RT> for NT = 1 (K <= 8) or 2, RT = n / 16
 #define MRHS_NT(KERNEL, NT, ...)                                                          \
   switch (cg.n) {                                                                         \
     case 16: hipLaunchKernelGGL((KERNEL<S, NT, 1>), __VA_ARGS__); break;                  \
@@ -719,17 +704,9 @@ static inline int nt_of(int K) { return K <= 8 ? 1 : 2; }
   }
 #define MRHS_DISPATCH(KERNEL, ...)                                                        \
   do {                                                                                    \
-    if (nt_of(K) == 1) {                                                                  \
+    if (K <= 8) {                                                                         \
       MRHS_NT(KERNEL, 1, __VA_ARGS__)                                                     \
     } else {                                                                              \
-      MRHS_NT(KERNEL, 2, __VA_ARGS__)                                                     \
-    }                                                                                     \
-  } while (0)
-// the stencil kernels that split_sites leaves: one column tile at n = 64 only
-#define MRHS_DISPATCH_BIG(KERNEL, ...)                                                    \
-  do {                                                                                    \
-    if (nt_of(K) == 1) hipLaunchKernelGGL((KERNEL<S, 1, 4>), __VA_ARGS__);                \
-    else {                                                                                \
       MRHS_NT(KERNEL, 2, __VA_ARGS__)                                                     \
     }                                                                                     \
   } while (0)
@@ -748,7 +725,7 @@ template <class S, int RT>
 constexpr auto HOP_INV_ODD_ONE = k_coarse_hop_inv_odd_split<S, RT, true>;
 
 // instantiate KERNEL<S, RT> for RT = n / 16
-#define SPLIT_DISPATCH(KERNEL, ...)                                                                  \
+#define RT_DISPATCH(KERNEL, ...)                                                                  \
   do {                                                                                               \
     switch (cg.n) {                                                                                  \
       case 16: hipLaunchKernelGGL((KERNEL<S, 1>), __VA_ARGS__); break;                               \
@@ -759,67 +736,62 @@ constexpr auto HOP_INV_ODD_ONE = k_coarse_hop_inv_odd_split<S, RT, true>;
     }                                                                                                \
   } while (0)
 
-// Whether a launch over nsites sites takes the split kernels.  Up to eight
-// columns; at n <= 48 on every size measured (six columns, us per odd-even pair,
-// before and now: 32 sites of n = 32 18.1 and 8.2, 512 sites of n = 48 30.4 and
-// 12.8, 41472 sites of n = 48 867 and 825), at n = 64 while 512 workgroups or
-// fewer leave room (pair on 256 sites 35.4 and 18.6, on 1024 48.7 and 39.1, but
-// on 2048 66.0 and 74.0: 1024 threads a site then keep too few sites in flight).
-static inline bool split_sites(int nsites, int n, int K) { return K <= 8 && (n <= 48 || nsites <= 512); }
-
 template <class S>
 void launch_coarse_apply_mrhs(const CGeom& cg, const void* D, double tw, int K, long ldv, const cx<float>* x,
                               const cx<float>* b, cx<float>* y, hipStream_t st, const int* sites, int nlist) {
   dim3 grid(sites ? nlist : cg.nsites), blk(4 * cg.n);
   if (grid.x == 0) return;
   auto Dp = (const typename store_traits<S>::elem*)D;
-  if (split_sites(grid.x, cg.n, K)) {
-    SPLIT_DISPATCH(k_coarse_apply_split, grid, dim3(16 * cg.n), 0, st, cg, Dp, (float)tw, K, ldv, x, b, y, sites);
+  if (K <= 8) {
+    RT_DISPATCH(k_coarse_apply_split, grid, dim3(16 * cg.n), 0, st, cg, Dp, (float)tw, K, ldv, x, b, y, sites);
     return;
   }
-  MRHS_DISPATCH_BIG(k_coarse_apply_mrhs, grid, blk, 0, st, cg, Dp, (float)tw, K, ldv, x, b, y, sites);
+  RT_DISPATCH(k_coarse_apply_mrhs, grid, blk, 0, st, cg, Dp, (float)tw, K, ldv, x, b, y, sites);
 }
 
 // Whether 16 rows of an even site get a workgroup: with fewer sites than CUs (six
-// columns, us per odd-even pair, a workgroup per site and now: 32 sites of n = 64
-// 17.0 and 13.4, 256 sites of n = 64 18.3 and 15.1, 256 sites of n = 48 11.4 and
-// 10.6), and at n = 64 with more (1024 sites 39.1 and 36.9; 1024 threads a site fit
-// once on a CU).  At 512 sites of n = 32 and 48 it takes 9.3 and 12.8 for 8.6 and
-// 12.4.
-static inline bool even_rows(int neven, int n) { return n == 64 || neven < 256; }
+// columns, us per odd-even pair, a workgroup per site and so: 32 sites of n = 64
+// 13.4 and 11.0, 256 sites of n = 32 9.2 and 7.5, of n = 48 10.1 and 9.1; at 512 of
+// n = 48 11.5 and 11.6, 1024 of n = 48 19.1 and 19.9: a row's workgroup shares no
+// input fragments).
+static inline bool even_rows(int neven) { return neven < 256; }
 
 template <class S>
 void launch_coarse_schur_even_mrhs(const CGeom& cg, const void* D, double tw, int K, long ldv, const cx<float>* v,
                                    const cx<float>* t, cx<float>* y, int mode, hipStream_t st) {
   dim3 grid(cg.neven), blk(4 * cg.n);
   auto Dp = (const typename store_traits<S>::elem*)D;
-  if (split_sites(cg.neven, cg.n, K)) {
-    if (even_rows(cg.neven, cg.n)) {
-      SPLIT_DISPATCH(EVEN_ROWS, dim3(cg.neven * (cg.n / 16)), dim3(256), 0, st, cg, Dp, (float)tw, K, ldv, v, t, y,
+  if (K <= 8) {
+    if (even_rows(cg.neven)) {
+      RT_DISPATCH(EVEN_ROWS, dim3(cg.neven * (cg.n / 16)), dim3(256), 0, st, cg, Dp, (float)tw, K, ldv, v, t, y,
                      mode);
     } else {
-      SPLIT_DISPATCH(EVEN_SITE, grid, dim3(16 * cg.n), 0, st, cg, Dp, (float)tw, K, ldv, v, t, y, mode);
+      RT_DISPATCH(EVEN_SITE, grid, dim3(16 * cg.n), 0, st, cg, Dp, (float)tw, K, ldv, v, t, y, mode);
     }
     return;
   }
-  MRHS_DISPATCH_BIG(k_coarse_schur_even_mrhs, grid, blk, 0, st, cg, Dp, (float)tw, K, ldv, v, t, y, mode);
+  RT_DISPATCH(k_coarse_schur_even_mrhs, grid, blk, 0, st, cg, Dp, (float)tw, K, ldv, v, t, y, mode);
 }
 
+// LDS of the split odd-site kernel: the hops' input fragments (four groups of
+// n/8 + 1, 64 lanes of 16 bytes), or later us and the 16 partial sums
+static inline size_t split_odd_lds(int n, int K) {
+  return std::max((size_t)SPLIT_G * (n / 8 + 1) * 64 * 16, (size_t)17 * n * K * sizeof(cx<float>));
+}
 template <class S>
 void launch_coarse_hop_inv_odd_mrhs(const CGeom& cg, const void* D, const cx<float>* Minv, int K, long ldv,
                                     const cx<float>* x, const cx<float>* base, cx<float>* y, hipStream_t st) {
   int nodd = cg.nsites - cg.neven;
   if (K < 1 || K > 16) throw Error(INVALID_ARG, "K-column coarse operator: 1 <= K <= 16");
   dim3 grid(nodd), blk(4 * cg.n);
-  // hop result [n][K], and for K <= 8 the four partial sums [4][n][K]
-  const size_t sm = (size_t)(nt_of(K) == 2 ? 1 : 5) * cg.n * K * sizeof(cx<float>);
+  const size_t sm = (size_t)cg.n * K * sizeof(cx<float>);  // hop result [n][K]
   auto Dp = (const typename store_traits<S>::elem*)D;
-  if (split_sites(nodd, cg.n, K)) {
-    const size_t ss = (size_t)17 * cg.n * K * sizeof(cx<float>);  // us and the 16 partial sums
-    SPLIT_DISPATCH(HOP_INV_ODD, grid, dim3(16 * cg.n), ss, st, cg, Dp, Minv, K, ldv, x, base, y);
+  if (K <= 8) {
+    const size_t ss = split_odd_lds(cg.n, K);
+    RT_DISPATCH(HOP_INV_ODD, grid, dim3(16 * cg.n), ss, st, cg, Dp, Minv, K, ldv, x, base, y);
     return;
   }
-  MRHS_DISPATCH_BIG(k_coarse_hop_inv_odd_mrhs, grid, blk, sm, st, cg, Dp, Minv, K, ldv, x, base, y);
+  RT_DISPATCH(k_coarse_hop_inv_odd_mrhs, grid, blk, sm, st, cg, Dp, Minv, K, ldv, x, base, y);
 }
 
 // one FP32 column on 16-bit blocks (three BF16 columns of the matrix cores)
@@ -827,19 +799,19 @@ template <class S>
 void launch_coarse_schur_even_one(const CGeom& cg, const void* D, double tw, const cx<float>* v, const cx<float>* t,
                                   cx<float>* y, int mode, hipStream_t st) {
   auto Dp = (const typename store_traits<S>::elem*)D;
-  if (even_rows(cg.neven, cg.n)) {
-    SPLIT_DISPATCH(EVEN_ROWS_ONE, dim3(cg.neven * (cg.n / 16)), dim3(256), 0, st, cg, Dp, (float)tw, 1, 0L, v, t, y,
+  if (even_rows(cg.neven)) {
+    RT_DISPATCH(EVEN_ROWS_ONE, dim3(cg.neven * (cg.n / 16)), dim3(256), 0, st, cg, Dp, (float)tw, 1, 0L, v, t, y,
                    mode);
   } else {
-    SPLIT_DISPATCH(EVEN_SITE_ONE, dim3(cg.neven), dim3(16 * cg.n), 0, st, cg, Dp, (float)tw, 1, 0L, v, t, y, mode);
+    RT_DISPATCH(EVEN_SITE_ONE, dim3(cg.neven), dim3(16 * cg.n), 0, st, cg, Dp, (float)tw, 1, 0L, v, t, y, mode);
   }
 }
 template <class S>
 void launch_coarse_hop_inv_odd_one(const CGeom& cg, const void* D, const cx<float>* Minv, const cx<float>* x,
                                    const cx<float>* base, cx<float>* y, hipStream_t st) {
   auto Dp = (const typename store_traits<S>::elem*)D;
-  const size_t ss = (size_t)17 * cg.n * sizeof(cx<float>);
-  SPLIT_DISPATCH(HOP_INV_ODD_ONE, dim3(cg.nsites - cg.neven), dim3(16 * cg.n), ss, st, cg, Dp, Minv, 1, 0L, x, base,
+  const size_t ss = split_odd_lds(cg.n, 1);
+  RT_DISPATCH(HOP_INV_ODD_ONE, dim3(cg.nsites - cg.neven), dim3(16 * cg.n), ss, st, cg, Dp, Minv, 1, 0L, x, base,
                  y);
 }
 template void launch_coarse_schur_even_one<bf16>(const CGeom&, const void*, double, const cx<float>*, const cx<float>*,
