@@ -1,7 +1,7 @@
 """Profiling driver for the fine operator: a fixed number of D(mu) applies on
-a seeded synthetic field (or, with --nfields K > 1, on K Gaussian fields in
-one launch each, as the lock-step outer solve applies it), followed by a
-plain device copy of known size.
+a seeded synthetic field (or, with --nfields K > 1, the launches on K fields
+of a lock-step outer solve of about that many iterations), followed by a plain
+device copy of known size.
 
 The copy calibrates rocprofv3's HBM byte counters (FETCH_SIZE, WRITE_SIZE):
 it reads and writes exactly `--copy-mib` MiB, so counter / known bytes is the
@@ -45,10 +45,14 @@ def main():
         if a.nfields == 1:
             ctx.bench_dirac(a.napply, a.precision)
         else:
-            psis = synth.gaussian_device((a.nfields,) + dims + (4, 3), a.seed + 1)
+            # the outer solve's own launches: a few lock-step iterations on a small hierarchy
+            block = (4, 4, 4, 4)
+            p = ddamg.default_params(levels=2, block=[block], nvec=[4], precision="fp32", coarse_mu_factor=5.0,
+                                     restart=4, max_iter=a.napply, rhs_batch=a.nfields, coarse_max_iter=4)
+            ctx.set_test_vectors(p, [synth.gaussian_device((4,) + dims + (4, 3), a.seed + 2)])
+            bs = synth.gaussian_device((a.nfields,) + dims + (4, 3), a.seed + 1)
             torch.cuda.empty_cache()
-            for _ in range(a.napply):
-                ctx.apply_dirac_multi(psis, precision=a.precision)
+            ctx.solve(bs, tol=1e-14, allow_not_converged=True)
         torch.cuda.synchronize()
     n = a.copy_mib * (1 << 20) // 8
     src = torch.ones(n, dtype=torch.float64, device="cuda")
