@@ -22,10 +22,11 @@
 // v_mfma_f32_16x16x32_{f16,bf16} (wave64) fragments: lane L holds A[L%16][8(L/16) + e]
 // and B[8(L/16) + e][L%16] for e < 8; the result D[4(L/16) + e][L%16] for e < 4.
 //
-// One workgroup per coarse site with n/16 wavefronts, wavefront t computing
-// output rows 16t..16t+15 (n = 2 N_v a multiple of 16, n <= 64): short
-// dependency chains and n/16 times the wavefronts of a one-per-site mapping,
-// which is what keeps these small, latency-bound grids busy.
+// For 9 to 16 columns, one workgroup per coarse site with n/16 wavefronts, wavefront
+// t computing output rows 16t..16t+15 (n = 2 N_v a multiple of 16, n <= 64): short
+// dependency chains and n/16 times the wavefronts of a one-per-site mapping, which
+// is what keeps these small, latency-bound grids busy.  Up to 8 columns take the
+// split kernels further down, four groups of such wavefronts to a site.
 #include "kernels.hpp"
 
 namespace ddamg {
