@@ -145,8 +145,7 @@ void load_links(Ctx& c, const void* links, int on_device) {
   }
   launch_links_from_lex(c.g, src, c.U64.as<cx<double>>(), ph, c.st);
   launch_clover(c.g, c.U64.as<cx<double>>(), c.csw, c.m0 + 4.0, c.H64.as<double>(), c.st);
-  c.have_32 = false;
-  c.u16_kind = -1;
+  c.drop_copies();
   c.rebuild_odd_inverse();
   c.sync();
   c.have_gauge = true;
@@ -308,8 +307,7 @@ int ddamg_set_boundary_phases(ddamg_ctx* ctx, const double theta[4]) {
         ph.im[d] = std::sin(theta[d] - c.theta[d]);
       }
       launch_link_phase(c.g, c.U64.as<cx<double>>(), ph, c.st);
-      c.have_32 = false;
-      c.u16_kind = -1;
+      c.drop_copies();
       c.sync();
       c.have_setup = false;
       c.mg.reset();
@@ -372,8 +370,7 @@ int ddamg_set_clover(ddamg_ctx* ctx, const void* clover, int on_device) {
       check_finite(c, (const double*)src, (long)c.g.V * 144);
       launch_clover_from_lex(c.g, src, c.m0 + 4.0, c.H64.as<double>(), c.st);
     }
-    c.have_32 = false;
-    c.u16_kind = -1;
+    c.drop_copies();
     c.rebuild_odd_inverse();
     c.sync();
     c.have_setup = false;
@@ -723,12 +720,9 @@ int ddamg_sap_multi(ddamg_ctx* ctx, int nfields, const void* b, void* x, int ite
                                            b64.as<cx<double>>(), x64.as<cx<double>>(), mr_steps, K, N, c.st);
       c.download_fields(x64.as<cx<double>>(), x, on_device, K);
     } else {
-      c.ensure_32();
-      const void* U = c.U32.p;
-      if (precision != DDAMG_FP32) {
-        c.ensure_16(precision);
-        U = c.U16.p;
-      }
+      const void* U = c.links(precision);
+      const float* H = c.clover32();
+      const float* T = c.tinv32();
       DevBuf b32, x32;
       b32.alloc(sizeof(cx<float>) * (size_t)N * K);
       x32.alloc(sizeof(cx<float>) * (size_t)N * K);
@@ -736,15 +730,13 @@ int ddamg_sap_multi(ddamg_ctx* ctx, int nfields, const void* b, void* x, int ite
       c.upload_fields(x, on_device, x32.as<cx<float>>(), K);
       for (int it = 0; it < iters; ++it)
         for (int col = 0; col < 2; ++col) {
+          cx<float>*bp = b32.as<cx<float>>(), *xp = x32.as<cx<float>>();
           if (precision == DDAMG_FP32)
-            launch_sap_multi<float, float>(c.g, col, U, c.H32.as<float>(), c.T32.as<float>(), c.twist(),
-                                           b32.as<cx<float>>(), x32.as<cx<float>>(), mr_steps, K, N, c.st);
+            launch_sap_multi<float, float>(c.g, col, U, H, T, c.twist(), bp, xp, mr_steps, K, N, c.st);
           else if (precision == DDAMG_FP16)
-            launch_sap_multi<float, f16>(c.g, col, U, c.H32.as<float>(), c.T32.as<float>(), c.twist(),
-                                         b32.as<cx<float>>(), x32.as<cx<float>>(), mr_steps, K, N, c.st);
+            launch_sap_multi<float, f16>(c.g, col, U, H, T, c.twist(), bp, xp, mr_steps, K, N, c.st);
           else
-            launch_sap_multi<float, bf16>(c.g, col, U, c.H32.as<float>(), c.T32.as<float>(), c.twist(),
-                                          b32.as<cx<float>>(), x32.as<cx<float>>(), mr_steps, K, N, c.st);
+            launch_sap_multi<float, bf16>(c.g, col, U, H, T, c.twist(), bp, xp, mr_steps, K, N, c.st);
         }
       c.download_fields(x32.as<cx<float>>(), x, on_device, K);
     }
@@ -939,22 +931,18 @@ int ddamg_bench_dirac(ddamg_ctx* ctx, int precision, int napply) {
       }
       return DDAMG_OK;
     }
-    c.ensure_32();
     c.f32a.ensure(sizeof(cx<float>) * N);
     c.f32b.ensure(sizeof(cx<float>) * N);
-    const void* U = c.U32.p;
-    if (precision == DDAMG_FP16 || precision == DDAMG_BF16) {
-      c.ensure_16(precision);
-      U = c.U16.p;
-    }
+    const void* U = c.links(precision);
+    const float* H = c.clover32();
     for (int i = 0; i < napply; ++i) {
       const cx<float>* in = (i & 1) ? c.f32b.as<cx<float>>() : c.f32a.as<cx<float>>();
       cx<float>* out = (i & 1) ? c.f32a.as<cx<float>>() : c.f32b.as<cx<float>>();
       hipEvent_t a;
       c.timer.begin(4, &a);
-      if (precision == DDAMG_FP32) launch_dirac<float, float>(c.g, U, c.H32.as<float>(), c.twist(), in, out, c.st);
-      else if (precision == DDAMG_FP16) launch_dirac<float, f16>(c.g, U, c.H32.as<float>(), c.twist(), in, out, c.st);
-      else launch_dirac<float, bf16>(c.g, U, c.H32.as<float>(), c.twist(), in, out, c.st);
+      if (precision == DDAMG_FP32) launch_dirac<float, float>(c.g, U, H, c.twist(), in, out, c.st);
+      else if (precision == DDAMG_FP16) launch_dirac<float, f16>(c.g, U, H, c.twist(), in, out, c.st);
+      else launch_dirac<float, bf16>(c.g, U, H, c.twist(), in, out, c.st);
       c.timer.end(4, a);
     }
     return DDAMG_OK;
@@ -1197,7 +1185,7 @@ int ddamg_setup_learned(ddamg_ctx* ctx, const ddamg_params* p, const void* noise
     if (!noise || (p->levels == 3 && !coarse_init)) throw Error(INVALID_ARG, "NULL input");
     if (noise_precision != DDAMG_FP64 && noise_precision != DDAMG_FP32)
       throw Error(INVALID_ARG, "noise must be complex128 (DDAMG_FP64) or complex64 (DDAMG_FP32)");
-    c.ensure_32();
+    c.links(DDAMG_FP32);
     const long fl = c.fine_len(), f = (long)c.net.C * fl;
     DevBuf A, B;
     A.alloc(sizeof(cx<float>) * f, true);
@@ -1300,7 +1288,7 @@ int ddamg_net_forward(ddamg_ctx* ctx, const void* noise, void* out, int on_devic
     Ctx& c = ctx->c;
     net_need(c);
     if (!noise || !out) throw Error(INVALID_ARG, "NULL field");
-    c.ensure_32();
+    c.links(DDAMG_FP32);
     net_buffers(c);
     NetState& n = c.net;
     net_upload(c, noise, on_device, n.act.as<cx<float>>());
@@ -1319,7 +1307,7 @@ int ddamg_net_loss_grad(ddamg_ctx* ctx, const void* noise, const void* target, i
     Ctx& c = ctx->c;
     net_need(c);
     if (!noise || !target) throw Error(INVALID_ARG, "NULL field");
-    c.ensure_32();
+    c.links(DDAMG_FP32);
     net_buffers(c);
     NetState& n = c.net;
     net_upload(c, noise, on_device, n.act.as<cx<float>>());
@@ -1342,7 +1330,7 @@ int ddamg_net_train_step(ddamg_ctx* ctx, const void* noise, const void* target, 
     net_need(c);
     if (!noise || !target) throw Error(INVALID_ARG, "NULL field");
     if (!(lr > 0) || !std::isfinite(lr)) throw Error(INVALID_ARG, "lr must be > 0");
-    c.ensure_32();
+    c.links(DDAMG_FP32);
     net_buffers(c);
     NetState& n = c.net;
     net_upload(c, noise, on_device, n.act.as<cx<float>>());

@@ -1641,7 +1641,9 @@ template void launch_cvt_cx<f16>(long, const cx<double>*, void*, hipStream_t);
 template void launch_cvt_cx<bf16>(long, const cx<double>*, void*, hipStream_t);
 
 // FP64 operator fields -> copies in 16-byte chunks: nt tiles of 8 sites, per site
-// 36 complex link entries in 16 bits or (k_chunk_real) 72 reals in FP32
+// 36 complex link entries in 16 bits (a thread an entry) or 72 reals in FP32 (a
+// thread a chunk; us at 48x24x24x24: a thread a chunk of links 100, an entry 85;
+// a chunk of reals 94, a real 117).
 template <class S>
 __global__ void k_chunk_links(long nt, const cx<double>* __restrict__ in,
                               typename store_traits<S>::elem* __restrict__ out) {
@@ -1659,50 +1661,63 @@ void launch_chunk_links(long nt, const cx<double>* in, void* out, hipStream_t st
 template void launch_chunk_links<f16>(long, const cx<double>*, void*, hipStream_t);
 template void launch_chunk_links<bf16>(long, const cx<double>*, void*, hipStream_t);
 
-__global__ void k_chunk_real(long nt, const double* __restrict__ in, float* __restrict__ out) {
+__global__ void __launch_bounds__(256) k_chunk_real(long nt, const double* __restrict__ in, float4* __restrict__ out) {
   const long gid = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (gid >= nt * 72 * TILE) return;
-  const int lane = (int)(gid % TILE), k = (int)(gid / TILE % 72);
-  const long tile = gid / (72 * TILE);
-  out[((tile * HC + (k >> 2)) * TILE + lane) * 4 + (k & 3)] = (float)in[gid];
+  if (gid >= nt * HC * TILE) return;
+  const double* p = in + (gid / TILE) * 4 * TILE + gid % TILE;
+  out[gid] = float4{(float)p[0], (float)p[TILE], (float)p[2 * TILE], (float)p[3 * TILE]};
 }
+void launch_chunk_real(long nt, const double* in, float* out, hipStream_t st) {
+  hipLaunchKernelGGL(k_chunk_real, dim3((unsigned)((nt * HC * TILE + 255) / 256)), dim3(256), 0, st, nt, in,
+                     (float4*)out);
+}
+
 // T^{-1} = (H + i tw) M on chirality 0, (H - i tw) M on chirality 1 of every odd
-// site, from the FP64 H and M; one thread per (odd site, row of 12)
-__global__ void k_chunk_tinv(Geom g, const double* __restrict__ H, const double* __restrict__ M, double tw,
-                             float* __restrict__ out) {
+// site, from the FP64 H and M.  One thread per (odd site, chirality), as in
+// k_odd_inverse: the packed M stays in registers, H is read a row at a time, and
+// every row is stored in whole chunks (48x24x24x24: 117 us, 4.9 TB/s; a thread per
+// row reading both 371 us).
+__global__ void __launch_bounds__(128) k_chunk_tinv(Geom g, const double* __restrict__ H,
+                                                    const double* __restrict__ M, double tw,
+                                                    float4* __restrict__ out) {
   const long gid = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  const int lane = (int)(gid % TILE), i12 = (int)(gid / TILE % 12);
-  const long tile = gid / (12 * TILE);  // tile of odd sites
+  const int lane = (int)(gid & 7), c = (int)(gid >> 3) & 1;
+  const long tile = gid >> 4;  // tile of odd sites
   if (tile >= (long)g.nblocks * (g.half / TILE)) return;
-  const int b = i12 / 6, i = i12 - 6 * b;
   const int B = (int)(tile / (g.half / TILE)), io = (int)(tile % (g.half / TILE)) * TILE + lane;
-  const double* h = H + fidx(g, B, g.half + io, 72) + 36L * b * TILE;
-  const double* m = M + oidx(g, B, io, 72) + 36L * b * TILE;
-  auto get = [](const double* p, int r, int c) {
-    if (r == c) return mk(p[(long)r * TILE], 0.0);
-    const int k = 6 + 2 * (r < c ? herm_idx(r, c) : herm_idx(c, r));
-    return mk(p[(long)k * TILE], r < c ? p[(long)(k + 1) * TILE] : -p[(long)(k + 1) * TILE]);
+  const double* hp = H + fidx(g, B, g.half + io, 72) + 36L * c * TILE;
+  const double* mp = M + oidx(g, B, io, 72) + 36L * c * TILE;
+  double m[36];
+#pragma unroll
+  for (int k = 0; k < 36; ++k) m[k] = mp[k * TILE];
+  auto hget = [hp](int i, int j) {
+    if (i == j) return mk(hp[i * TILE], 0.0);
+    return i < j ? mk(hp[pk(i, j) * TILE], hp[(pk(i, j) + 1) * TILE])
+                 : mk(hp[pk(j, i) * TILE], -hp[(pk(j, i) + 1) * TILE]);
   };
-  for (int j = 0; j < 6; ++j) {
-    cx<double> acc = mk(0.0, 0.0);
-    for (int k = 0; k < 6; ++k) {
-      cx<double> a = get(h, i, k);
-      if (k == i) a.im += b == 0 ? tw : -tw;
-      cmac(acc, a, get(m, k, j));
+  float4* o = out + (tile * TC + 18 * c) * TILE + lane;
+#pragma unroll
+  for (int i = 0; i < 6; ++i) {
+    cx<double> a[6], row[6];
+#pragma unroll
+    for (int k = 0; k < 6; ++k) a[k] = hget(i, k);
+    a[i].im += c == 0 ? tw : -tw;
+#pragma unroll
+    for (int j = 0; j < 6; ++j) {
+      row[j] = mk(0.0, 0.0);
+#pragma unroll
+      for (int k = 0; k < 6; ++k) cmac(row[j], a[k], pget(m, k, j));
     }
-    const int w = i12 * 12 + 2 * j;  // word of the real part
-    float* o = out + ((tile * TC + (w >> 2)) * TILE + lane) * 4 + (w & 3);
-    o[0] = (float)acc.re;
-    o[1] = (float)acc.im;
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+      o[(3 * i + q) * TILE] =
+          float4{(float)row[2 * q].re, (float)row[2 * q].im, (float)row[2 * q + 1].re, (float)row[2 * q + 1].im};
+    __builtin_amdgcn_sched_barrier(0);
   }
 }
 void launch_chunk_tinv(const Geom& g, const double* H, const double* M, double tw, float* out, hipStream_t st) {
-  const long n = (long)g.nblocks * g.half * 12;
-  hipLaunchKernelGGL(k_chunk_tinv, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, g, H, M, tw, out);
-}
-
-void launch_chunk_real(long nt, const double* in, float* out, hipStream_t st) {
-  hipLaunchKernelGGL(k_chunk_real, dim3((unsigned)((nt * 72 * TILE + 255) / 256)), dim3(256), 0, st, nt, in, out);
+  const long n = 2 * (long)g.nblocks * g.half;
+  hipLaunchKernelGGL(k_chunk_tinv, dim3((unsigned)((n + 127) / 128)), dim3(128), 0, st, g, H, M, tw, (float4*)out);
 }
 
 // ---------------------------------------------------------------------------

@@ -730,27 +730,48 @@ template KrylovResult fgmres<float>(Ctx&, KrylovWS<float>&, long,
                                     cx<float>*, double, int, bool, bool);
 
 // ---------------------------------------------------------------------------
-void Ctx::ensure_32() {
-  if (have_32) return;
-  U32.ensure(sizeof(cx<float>) * (size_t)g.V * 36);
-  H32.ensure(sizeof(float) * (size_t)g.V * 72);
-  T32.ensure(sizeof(float) * (size_t)g.V * 72);
-  launch_cvt_cx<float>((long)g.V * 36, U64.as<cx<double>>(), U32.p, st);
-  launch_chunk_real(g.V / TILE, H64.as<double>(), H32.as<float>(), st);
-  launch_chunk_tinv(g, H64.as<double>(), M64.as<double>(), mu_odd, T32.as<float>(), st);
-  have_32 = true;
+const void* Ctx::links(int precision) {
+  if (precision == DDAMG_FP32) {
+    if (!have_u32) {
+      U32.ensure(sizeof(cx<float>) * (size_t)g.V * 36);
+      launch_cvt_cx<float>((long)g.V * 36, U64.as<cx<double>>(), U32.p, st);
+      have_u32 = true;
+    }
+    return U32.p;
+  }
+  const int kind = precision == DDAMG_FP16 ? DDAMG_FP16 : DDAMG_BF16;
+  if (u16_kind != kind) {
+    U16.ensure(4 * (size_t)g.V * 36);
+    if (kind == DDAMG_FP16) launch_chunk_links<f16>(g.V / TILE, U64.as<cx<double>>(), U16.p, st);
+    else launch_chunk_links<bf16>(g.V / TILE, U64.as<cx<double>>(), U16.p, st);
+    u16_kind = kind;
+  }
+  return U16.p;
 }
-void Ctx::ensure_16(int kind) {
-  ensure_32();
-  if (u16_kind == kind) return;
-  U16.ensure(4 * (size_t)g.V * 36);
-  if (kind == DDAMG_FP16) launch_chunk_links<f16>(g.V / TILE, U64.as<cx<double>>(), U16.p, st);
-  else launch_chunk_links<bf16>(g.V / TILE, U64.as<cx<double>>(), U16.p, st);
-  u16_kind = kind;
+const float* Ctx::clover32() {
+  if (!have_h32) {
+    H32.ensure(sizeof(float) * (size_t)g.V * 72);
+    launch_chunk_real(g.V / TILE, H64.as<double>(), H32.as<float>(), st);
+    have_h32 = true;
+  }
+  return H32.as<float>();
+}
+const float* Ctx::tinv32() {
+  if (!have_t32) {
+    T32.ensure(sizeof(float) * (size_t)g.V * 72);
+    launch_chunk_tinv(g, H64.as<double>(), M64.as<double>(), mu_odd, T32.as<float>(), st);
+    have_t32 = true;
+  }
+  return T32.as<float>();
+}
+void Ctx::drop_copies() {
+  have_u32 = have_h32 = have_t32 = false;
+  u16_kind = -1;
 }
 void Ctx::rebuild_odd_inverse() {
   launch_odd_inverse(g, H64.as<double>(), mu_odd, M64.as<double>(), st);
-  if (have_32) launch_chunk_tinv(g, H64.as<double>(), M64.as<double>(), mu_odd, T32.as<float>(), st);
+  // a hierarchy reads T32 where it is: renew it here, not at the next call
+  if (have_t32) launch_chunk_tinv(g, H64.as<double>(), M64.as<double>(), mu_odd, T32.as<float>(), st);
 }
 void Ctx::dirac64(const cx<double>* in, cx<double>* out, Twist tw) { dirac64_multi(in, out, 1, 0, tw); }
 void Ctx::dirac64_multi(const cx<double>* in, cx<double>* out, int K, long ld, Twist tw) {
@@ -766,14 +787,11 @@ void Ctx::dirac_lex(const cx<double>* in, cx<double>* out, int K, Twist tw, int 
     launch_dirac_lex<double, double>(g, U64.p, H64.as<double>(), tw, K, N, in, out, st);
     return;
   }
-  ensure_32();
-  if (precision == DDAMG_FP32) {
-    launch_dirac_lex<float, float>(g, U32.p, H32.as<float>(), tw, K, N, in, out, st);
-    return;
-  }
-  ensure_16(precision);
-  if (precision == DDAMG_FP16) launch_dirac_lex<float, f16>(g, U16.p, H32.as<float>(), tw, K, N, in, out, st);
-  else launch_dirac_lex<float, bf16>(g, U16.p, H32.as<float>(), tw, K, N, in, out, st);
+  const void* U = links(precision);
+  const float* H = clover32();
+  if (precision == DDAMG_FP32) launch_dirac_lex<float, float>(g, U, H, tw, K, N, in, out, st);
+  else if (precision == DDAMG_FP16) launch_dirac_lex<float, f16>(g, U, H, tw, K, N, in, out, st);
+  else launch_dirac_lex<float, bf16>(g, U, H, tw, K, N, in, out, st);
 }
 template <class R>
 void Ctx::upload_fields(const void* src, int on_device, cx<R>* dst, int K) {
@@ -996,15 +1014,9 @@ struct MG : MGBase {
       Hf = c.H64.as<double>();
       Mf = c.M64.as<double>();
     } else {
-      if constexpr (std::is_same<S, float>::value) {
-        c.ensure_32();
-        U = c.U32.p;
-      } else {
-        c.ensure_16(std::is_same<S, f16>::value ? DDAMG_FP16 : DDAMG_BF16);
-        U = c.U16.p;
-      }
-      Hf = c.H32.template as<float>();
-      Mf = c.T32.template as<float>();
+      U = c.links(std::is_same<S, float>::value ? DDAMG_FP32 : std::is_same<S, f16>::value ? DDAMG_FP16 : DDAMG_BF16);
+      Hf = c.clover32();
+      Mf = c.tinv32();
     }
     set_twists(c.twist());
     // allocations

@@ -297,10 +297,12 @@ struct Ctx {
   double theta[4] = {0, 0, 0, 0};  // twisted boundary conditions (0: periodic)
   bool have_gauge = false, have_setup = false;
   DevBuf U64, H64, M64;        // fine operator, FP64
-  DevBuf U32, H32, T32;        // FP32 copies (T32: the odd sites' T^{-1})
+  // reduced-precision copies, each made by the first call that reads it (a
+  // 16-bit D(mu) takes 16-bit links and FP32 clover term only)
+  DevBuf U32, H32, T32;        // FP32 links, clover term, odd sites' T^{-1}
   DevBuf U16;                  // 16-bit link copy
   int u16_kind = -1;           // DDAMG_FP16 or DDAMG_BF16
-  bool have_32 = false;
+  bool have_u32 = false, have_h32 = false, have_t32 = false;
   DevBuf lex;                  // host-layout FP64 staging (one fine field)
   DevBuf f64a, f64b, f64c;     // fine FP64 block-layout vectors
   DevBuf f32a, f32b;           // fine FP32 block-layout vectors
@@ -316,8 +318,10 @@ struct Ctx {
   void* progress_user = nullptr;
 
   long fine_len() const { return g.V * 12; }
-  void ensure_32();
-  void ensure_16(int kind);
+  const void* links(int precision);  // links as `precision` stores them (FP32, FP16, BF16)
+  const float* clover32();
+  const float* tinv32();
+  void drop_copies();
   void rebuild_odd_inverse();
   void sync() { HIP_CHECK(hipStreamSynchronize(st)); }
   // the fine operator's twists, both negated for sign < 0 (D(-mu))
