@@ -739,14 +739,20 @@ const void* Ctx::links(int precision) {
     }
     return U32.p;
   }
-  const int kind = precision == DDAMG_FP16 ? DDAMG_FP16 : DDAMG_BF16;
-  if (u16_kind != kind) {
-    U16.ensure(4 * (size_t)g.V * 36);
-    if (kind == DDAMG_FP16) launch_chunk_links<f16>(g.V / TILE, U64.as<cx<double>>(), U16.p, st);
-    else launch_chunk_links<bf16>(g.V / TILE, U64.as<cx<double>>(), U16.p, st);
-    u16_kind = kind;
+  if (precision == DDAMG_FP16) {
+    if (!have_u16) {
+      U16.ensure(4 * (size_t)g.V * 36);
+      launch_chunk_links<f16>(g.V / TILE, U64.as<cx<double>>(), U16.p, st);
+      have_u16 = true;
+    }
+    return U16.p;
   }
-  return U16.p;
+  if (!have_ub16) {
+    Ub16.ensure(4 * (size_t)g.V * 36);
+    launch_chunk_links<bf16>(g.V / TILE, U64.as<cx<double>>(), Ub16.p, st);
+    have_ub16 = true;
+  }
+  return Ub16.p;
 }
 const float* Ctx::clover32() {
   if (!have_h32) {
@@ -765,8 +771,7 @@ const float* Ctx::tinv32() {
   return T32.as<float>();
 }
 void Ctx::drop_copies() {
-  have_u32 = have_h32 = have_t32 = false;
-  u16_kind = -1;
+  have_u32 = have_u16 = have_ub16 = have_h32 = have_t32 = false;
 }
 void Ctx::rebuild_odd_inverse() {
   launch_odd_inverse(g, H64.as<double>(), mu_odd, M64.as<double>(), st);

@@ -300,9 +300,8 @@ struct Ctx {
   // reduced-precision copies, each made by the first call that reads it (a
   // 16-bit D(mu) takes 16-bit links and FP32 clover term only)
   DevBuf U32, H32, T32;        // FP32 links, clover term, odd sites' T^{-1}
-  DevBuf U16;                  // 16-bit link copy
-  int u16_kind = -1;           // DDAMG_FP16 or DDAMG_BF16
-  bool have_u32 = false, have_h32 = false, have_t32 = false;
+  DevBuf U16, Ub16;            // FP16 and BF16 links (apart: a hierarchy keeps reading its own)
+  bool have_u32 = false, have_u16 = false, have_ub16 = false, have_h32 = false, have_t32 = false;
   DevBuf lex;                  // host-layout FP64 staging (one fine field)
   DevBuf f64a, f64b, f64c;     // fine FP64 block-layout vectors
   DevBuf f32a, f32b;           // fine FP32 block-layout vectors

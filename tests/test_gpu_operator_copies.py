@@ -78,3 +78,21 @@ def test_copies_follow_the_operator(dd, dims, block, prec):
                 want = both(fresh)
             for g, w in zip(got, want):
                 assert np.array_equal(g, w), changes[n - 1][0]
+
+
+@pytest.mark.parametrize("own,other", [("fp16", "bf16"), ("bf16", "fp16")])
+def test_hierarchy_keeps_its_links(dd, own, other):
+    """Calls in the other 16-bit type between two applications of a hierarchy's
+    cycle leave it as it was: the same bits."""
+    from paper_1611_01034_amd import synth
+    dims, block = (8, 8, 8, 8), (4, 4, 4, 4)
+    with _ctx(dd, dims, block) as ctx:
+        ctx.set_gauge(synth.gauge_field(dims, 0.3, 8901))
+        p = dd.default_params(levels=2, block=[block], nvec=[8], coarse_mu_factor=5.0, precision=own)
+        ctx.set_test_vectors(p, [synth.spinor(dims, 8902, nvec=8)])
+        b = synth.spinor(dims, 8903)
+        first = ctx.vcycle(b)
+        for call in (lambda: ctx.apply_dirac(b, precision=other), lambda: ctx.sap(b, b, 1, 4, other)):
+            print(f"{own} hierarchy among {other} calls", flush=True)
+            call()
+            assert np.array_equal(ctx.vcycle(b), first)
