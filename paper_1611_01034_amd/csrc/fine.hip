@@ -196,8 +196,8 @@ __device__ __forceinline__ void hop_inv_block(const typename store_traits<S>::el
 // accesses, each direction's links and each third of T_oo^{-1}'s rows loaded
 // while the one before multiplies.  1042 -> 769 us a sweep there, 105 -> 84 us
 // with one field and FP32 links at 24x16x16x24.  All 256 registers are in use:
-// with 168 (three wavefronts per SIMD) these take 1086 and 129 us.  Small grids and
-// one field with FP32 links take k_sap_two.
+// with 168 (three wavefronts per SIMD) these take 1086 and 129 us.  Small grids, and
+// one field with FP32 links on blocks that fill its wavefronts, take k_sap_two.
 template <class R, class S>
 __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(sizeof(R) == 8 ? 1 : 2, 8)))
 k_sap(Geom g, int colour, const typename store_traits<S>::elem* __restrict__ U, const R* __restrict__ H,
@@ -420,7 +420,7 @@ __device__ __forceinline__ void inv_two(const TinvRows r[2], const cx<float> psi
 }
 
 // The sweep for grids that leave most of the chip idle, and for one field with FP32
-// links: two threads for a pair of slots, in wavefronts of their own, and a
+// links on large blocks: two threads for a pair of slots, in wavefronts of their own, and a
 // wavefront alone on its SIMD.  Bound by the chain of an MR step (two hop sums, two
 // exchanges, the dots), so that is what is halved, and the operator entries of a
 // thread (200 to 250 registers) are loaded once and stay in the register file of
@@ -597,17 +597,33 @@ k_sap_two(Geom g, int colour, const typename store_traits<S>::elem* __restrict__
   for (int c = 0; c < 6; ++c) x[oe + (long)c * TILE] = x[oe + (long)c * TILE] + ee[c];
 }
 
-// Whether a sweep of nwg workgroups takes k_sap_two.  While every SIMD has at most
-// one wavefront of it (two or four a workgroup), the shorter chain wins: 8x8x8x16
-// 54 -> 37 us with 16-bit links and 57 -> 38 with FP32, 256 workgroups of 256 sites
-// 58 -> 40 and 64 -> 42; past that its second round costs more (288 workgroups
-// 74 -> 82 us, six fields on 16^4 73 -> 117).  One field with FP32 links is bound by
-// reading the operator again in every step, so there it also wins once the rounds
-// are full: 384 workgroups 91 -> 86 us, 768 179 -> 141, 2304 556 -> 429 (288: 83, 83).
+// Whether a sweep of nwg workgroups takes k_sap_two (us a sweep, k_sap and it).
+// While every SIMD has at most one wavefront of it (two or four a workgroup), the
+// shorter chain wins for every block: 8x8x8x16 54 and 37 with 16-bit links, 57 and
+// 38 with FP32, 432 workgroups of 8 pairs 97 and 39, 512 of 32 pairs 61 and 40, 256 of
+// 128 pairs 58 and 40; past that its second round costs more (288 of 128 pairs 74
+// and 82, six fields on 16^4 73 and 117).  Blocks of 8 pairs: k_sap's workgroups
+// are one short wavefront, and up to about 1000 of them the dispatcher puts some in
+// twos on a SIMD while others idle (648: 41 % of the wavefront cycles wait for the
+// issue slot), so that two rounds of this kernel still win: 864 146 and 75, 1152 90
+// and 113; with FP16 links three nearly do, 1152 145 and 107, 1296 126 and 107, 1536
+// 108 and 109.
+// One field with FP32 links of large blocks is bound by reading the operator again
+// in every step, so there it also wins once the rounds are full, if most lanes of
+// its wavefronts have a pair: 64 pairs 864 workgroups 102 and 83, 5120 627 and 463;
+// 104 pairs 1200 264 and 227; 128 pairs 432 100 and 88, 3200 789 and 623; 56 and
+// 112 pairs within these.  At three quarters (48 and 96 pairs) only from 6000
+// wavefronts on: 1728 of 48 pairs 161 and 166, 3456 340 and 301.  Emptier
+// wavefronts multiply by nothing: 8 pairs 16464 workgroups 813 and 1263, 24 pairs
+// 5184 306 and 438, 32 pairs 4608 315 and 375, 72 pairs 2592 378 and 477, 88 pairs
+// 3136 554 and 579.
 template <class S>
 static inline bool sap_two(const Geom& g, int nwg, int K) {
-  const long waves = (long)nwg * 2 * ((g.half + 63) / 64);
-  return waves <= 1024 || (sizeof(S) == 4 && K == 1 && waves >= 1536);
+  const int slots = (g.half + 63) / 64 * 64;  // lanes of a part; g.half of them have a pair
+  const long waves = (long)nwg * (slots / 32);
+  if (waves <= (g.half > 8 ? 1024 : std::is_same<S, f16>::value ? 2816 : 2048)) return true;
+  if (sizeof(S) != 4 || K != 1) return false;
+  return 4 * g.half > 3 * slots ? waves >= 1536 : 4 * g.half == 3 * slots && waves >= 6144;
 }
 template <class R, class S>
 void launch_sap(const Geom& g, int colour, const void* U, const R* H, const R* Minv, Twist tw, const cx<R>* b,
