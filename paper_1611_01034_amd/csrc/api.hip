@@ -675,7 +675,8 @@ int ddamg_apply_dirac(ddamg_ctx* ctx, const void* in, void* out, int sign, int p
     need_gauge(c);
     if (!in || !out) throw Error(INVALID_ARG, "NULL field");
     if (precision < DDAMG_FP64 || precision > DDAMG_BF16) throw Error(INVALID_ARG, "unknown precision");
-    apply_dirac_fields(c, in, out, 1, c.twist(sign), precision, on_device, c.lex, c.f64b, false);
+    // the context's own FP64 vectors: no memory beyond what it holds already
+    apply_dirac_fields(c, in, out, 1, c.twist(sign), precision, on_device, c.f64a, c.f64b, false);
     return DDAMG_OK;
   });
 }

@@ -96,3 +96,24 @@ def test_hierarchy_keeps_its_links(dd, own, other):
             print(f"{own} hierarchy among {other} calls", flush=True)
             call()
             assert np.array_equal(ctx.vcycle(b), first)
+
+
+def test_single_dirac_takes_no_memory(dd):
+    """In place (out = in), on separate fields and on host fields: D(mu) of one
+    field works in the context's own vectors, so it also runs when the device
+    has no room for one more field."""
+    import ctypes
+    from paper_1611_01034_amd import synth
+    dims, block = (32, 32, 16, 32), (4, 4, 4, 4)
+    with _ctx(dd, dims, block) as ctx:
+        ctx.set_gauge(synth.gauge_field_device(dims, 0.3, 8951))
+        psi = synth.gaussian_device(dims + (4, 3), 8952)
+        before = ctx.release_memory()
+        want = ctx.apply_dirac(psi)
+        print("one field on the host", flush=True)
+        assert np.array_equal(ctx.apply_dirac(psi.cpu().numpy()), want.cpu().numpy())
+        print("one field in place", flush=True)
+        p = ctypes.c_void_p(psi.data_ptr())
+        ctx._check(dd._lib.ddamg_apply_dirac(ctx._h, p, p, 1, dd.FP64, 1))
+        assert torch.equal(psi, want)
+        assert ctx.release_memory() == before
