@@ -625,12 +625,12 @@ __device__ __forceinline__ void reduce_partials(const double* partd, int nval, i
 }
 }  // namespace
 
-// The updates w -= sum_i c_i V_i and the norm's per-thread sums are in A (lock-step
-// columns in FP32: FP32 with the coefficients rounded to it; one column: FP64), the
-// dots of FP32 vectors in FP64, every sum across threads in FP64 from the wavefront
-// totals on.
+// The updates w -= sum_i c_i V_i and the norm's per-thread sums of FP32 vectors are in
+// A (lock-step columns: FP32 with the coefficients rounded to it; one column: FP64),
+// their dots in FP64 (k_cgs_dot_waves; k_cgs_dot and k_cgs_axpy_dot are for FP64
+// vectors), every sum across threads in FP64 from the wavefront totals on.
 // pa_r: partials of V_{r,i}^H w_r  (i < k)
-template <class R, class A, int KM, int BS>
+template <class R, int KM, int BS>
 __global__ void __launch_bounds__(BS) k_cgs_dot(const cx<R>* __restrict__ V, long ldv, long csV, int k,
                                                 const cx<R>* __restrict__ w, long csw, long N, double* pa,
                                                 long pcs, const int* act) {
@@ -640,17 +640,17 @@ __global__ void __launch_bounds__(BS) k_cgs_dot(const cx<R>* __restrict__ V, lon
   w += r * csw;
   // sums for KM vectors, padded to a power of two for the wavefront reduction
   constexpr int KP = cgs_pow2(KM);
-  A acc[2 * KP];
+  R acc[2 * KP];
 #pragma unroll
-  for (int q = 0; q < 2 * KP; ++q) acc[q] = A(0);
+  for (int q = 0; q < 2 * KP; ++q) acc[q] = R(0);
   const long stride = (long)gridDim.x * BS;
   for (long e = (long)blockIdx.x * BS + threadIdx.x; e < N; e += stride) {
     const cx<R> x = w[e];
 #pragma unroll
     for (int i = 0; i < KM; ++i) {  // every load issued (index clamped); sums past k unused
       const cx<R> v = V[(long)min(i, k - 1) * ldv + e];
-      acc[2 * i] += (A)v.re * x.re + (A)v.im * x.im;
-      acc[2 * i + 1] += (A)v.re * x.im - (A)v.im * x.re;
+      acc[2 * i] += v.re * x.re + v.im * x.im;
+      acc[2 * i + 1] += v.re * x.im - v.im * x.re;
     }
   }
   store_partials<KP, BS / 64>(acc, 2 * k, pa + 2 * r * pcs);
@@ -702,7 +702,7 @@ __global__ void __launch_bounds__(512) k_cgs_dot_waves(const cx<float>* __restri
 
 // h_r = sum of pa_r (workgroup 0 stores it in hcol_r);  w_r -= sum_i h_r[i] V_{r,i};
 // pb_r: partials of V_{r,i}^H w_r
-template <class R, class A, int KM, int BS>
+template <class R, int KM, int BS>
 __global__ void __launch_bounds__(BS) k_cgs_axpy_dot(const cx<R>* __restrict__ V, long ldv, long csV, int k,
                                                      cx<R>* w, long csw, long N, const double* pa, double* pb,
                                                      long pcs, cx<double>* hcol, long hcs, const int* act) {
@@ -715,35 +715,35 @@ __global__ void __launch_bounds__(BS) k_cgs_axpy_dot(const cx<R>* __restrict__ V
   V += r * csV;
   w += r * csw;
   __shared__ double cf[2 * KM];
-  __shared__ cx<A> cfr[KM];
+  __shared__ cx<R> cfr[KM];
   reduce_partials(pa + 2 * r * pcs, 2 * k, 2 * KM, gridDim.x, cf);
   if (blockIdx.x == 0 && threadIdx.x < 2 * k) reinterpret_cast<double*>(hcol + r * hcs)[threadIdx.x] = cf[threadIdx.x];
-  if (threadIdx.x < KM) cfr[threadIdx.x] = mk<A>((A)cf[2 * threadIdx.x], (A)cf[2 * threadIdx.x + 1]);
+  if (threadIdx.x < KM) cfr[threadIdx.x] = mk<R>((R)cf[2 * threadIdx.x], (R)cf[2 * threadIdx.x + 1]);
   __syncthreads();
   // sums for KM vectors, padded to a power of two for the wavefront reduction
   constexpr int KP = cgs_pow2(KM);
-  A acc[2 * KP];
+  R acc[2 * KP];
 #pragma unroll
-  for (int q = 0; q < 2 * KP; ++q) acc[q] = A(0);
+  for (int q = 0; q < 2 * KP; ++q) acc[q] = R(0);
   const long stride = (long)gridDim.x * BS;
   for (long e = (long)blockIdx.x * BS + threadIdx.x; e < N; e += stride) {
     const cx<R> x0 = w[e];
-    cx<A> s = mk<A>(0, 0);
+    cx<R> s = mk<R>(0, 0);
     cx<R> held[HELD];
 #pragma unroll
     for (int i = 0; i < KM; ++i) {  // coefficients past k are zero
       const cx<R> v = V[(long)min(i, k - 1) * ldv + e];
       if (i < HELD) held[i] = v;
-      cmac(s, cfr[i], mk<A>(v.re, v.im));
+      cmac(s, cfr[i], v);
     }
-    const cx<R> x = mk<R>((R)(x0.re - s.re), (R)(x0.im - s.im));
+    const cx<R> x = mk<R>(x0.re - s.re, x0.im - s.im);
     w[e] = x;
     if (KM > HELD) __asm__ volatile("" ::: "memory");
 #pragma unroll
     for (int i = 0; i < KM; ++i) {
       const cx<R> v = i < HELD ? held[i] : V[(long)min(i, k - 1) * ldv + e];
-      acc[2 * i] += (A)v.re * x.re + (A)v.im * x.im;
-      acc[2 * i + 1] += (A)v.re * x.im - (A)v.im * x.re;
+      acc[2 * i] += v.re * x.re + v.im * x.im;
+      acc[2 * i + 1] += v.re * x.im - v.im * x.re;
     }
   }
   store_partials<KP, BS / 64>(acc, 2 * k, pb + 2 * r * pcs);
@@ -994,11 +994,11 @@ static void cgs_step(const cx<R>* V, long ldv, long csV, int k, cx<R>* w, long c
 #define CGS_LAUNCH(KM)                                                                                                \
   {                                                                                                                   \
     if constexpr (sizeof(R) == 8)                                                                                     \
-      hipLaunchKernelGGL((k_cgs_dot<R, A, KM, BS>), grid, blk, 0, st, V, ldv, csV, k, (const cx<R>*)w, csw, N, a, pcs, \
+      hipLaunchKernelGGL((k_cgs_dot<R, KM, BS>), grid, blk, 0, st, V, ldv, csV, k, (const cx<R>*)w, csw, N, a, pcs,   \
                          act);                                                                                        \
     if constexpr (sizeof(R) == 8) {                                                                                   \
       if (two_pass) {                                                                                                 \
-        hipLaunchKernelGGL((k_cgs_axpy_dot<R, A, KM, BS>), grid, blk, 0, st, V, ldv, csV, k, w, csw, N,               \
+        hipLaunchKernelGGL((k_cgs_axpy_dot<R, KM, BS>), grid, blk, 0, st, V, ldv, csV, k, w, csw, N,                  \
                            (const double*)a, b, pcs, hcol, hcs, act);                                                 \
         hipLaunchKernelGGL((k_cgs_axpy_norm<R, A, KM, BS>), grid, blk, 0, st, V, ldv, csV, k, w, csw, N,              \
                            (const double*)b, a, pcs, hcol, hcs, act);                                                 \

@@ -209,27 +209,6 @@ __host__ __device__ __forceinline__ void site_coords(const Geom& g, int B, int s
   for (int d = 0; d < 4; ++d) x[d] = bc[d] * g.b[d] + l[d];
 }
 
-// (block, slot) of global coordinates
-__host__ __device__ __forceinline__ void coords_site(const Geom& g, const int x[4], int& B, int& s) {
-  int bc[4], l[4];
-  for (int d = 0; d < 4; ++d) {
-    bc[d] = x[d] / g.b[d];
-    l[d] = x[d] - bc[d] * g.b[d];
-  }
-  B = block_index(g, bc);
-  s = local_slot(g, l);
-}
-
-// neighbour of (B,s) one step in direction mu with sign dir (+1 / -1), periodic
-__host__ __device__ __forceinline__ void neighbour(const Geom& g, int B, int s, int mu, int dir, int& Bn, int& sn) {
-  int x[4];
-  site_coords(g, B, s, x);
-  x[mu] += dir;
-  if (x[mu] == g.L[mu]) x[mu] = 0;
-  if (x[mu] < 0) x[mu] = g.L[mu] - 1;
-  coords_site(g, x, Bn, sn);
-}
-
 // Workgroups of a launch are dispatched round-robin over the 8 XCDs, each with
 // its own L2.  Map workgroup w of nwg to a logical index so that every XCD
 // owns one contiguous range of logical indices (lattice blocks that are

@@ -61,16 +61,6 @@ __device__ __forceinline__ void hop_accum_t(const cx<R> psi[12], const cx<R> u[9
   }
 }
 
-template <int BWD, class R>
-__device__ __forceinline__ void hop_accum(int mu, const cx<R> psi[12], const cx<R> u[9], cx<R> out[12]) {
-  switch (mu) {
-    case 0: hop_accum_t<BWD, 0>(psi, u, out); break;
-    case 1: hop_accum_t<BWD, 1>(psi, u, out); break;
-    case 2: hop_accum_t<BWD, 2>(psi, u, out); break;
-    default: hop_accum_t<BWD, 3>(psi, u, out); break;
-  }
-}
-
 // The 9 entries of one link as loaded, converted later: 16-bit links as the
 // three chunks that hold direction mu's nine words (they begin at word mu of
 // the site's chunk 2 mu), others as the entries themselves.
