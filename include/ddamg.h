@@ -279,9 +279,8 @@ int ddamg_apply_dirac(ddamg_ctx* ctx, const void* in, void* out, int sign, int p
  * for all fields, as the lock-step outer solve does.  Same arithmetic per
  * field as ddamg_apply_dirac (bit-identical results); host fields, and device
  * fields of which in and out overlap, are staged in device memory of the
- * library's own for the call.  INVALID_ARG for NULL
- * fields, nfields out of range or an unknown precision; BAD_STATE without a
- * gauge field. */
+ * library's own for the call.  INVALID_ARG for NULL fields, nfields out of range
+ * or an unknown precision; BAD_STATE without a gauge field. */
 int ddamg_apply_dirac_multi(ddamg_ctx* ctx, int nfields, const void* in, void* out, int sign, int precision,
                             int on_device);
 /* out = D(sign*mu) in in FP64, allocating nothing: for callers that cannot
@@ -296,8 +295,8 @@ int ddamg_apply_dirac_multi(ddamg_ctx* ctx, int nfields, const void* in, void* o
  * context's stream and returns: out is ready when that stream reaches them.
  * Calls with overlapping fields on one device share the scratch array, so two
  * of them that can overlap on one GPU (contexts on different streams) race;
- * the array needs no clearing, since each call writes every entry it reads.  sign must be +1 or -1; BAD_STATE
- * without a gauge field. */
+ * the array needs no clearing, since each call writes every entry it reads.
+ * sign must be +1 or -1; BAD_STATE without a gauge field. */
 int ddamg_apply_dirac_noalloc(ddamg_ctx* ctx, const void* in, void* out, int sign);
 /* iters SAP iterations on D x = b starting from x (updated in place): the
  * smoother M of Eq. (1) (Sec. 1), red then black 4^4 blocks, each block solved

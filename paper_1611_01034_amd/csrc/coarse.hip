@@ -261,10 +261,11 @@ __global__ void __launch_bounds__(256) k_coarse_apply(CGeom cg, const typename s
   }
 }
 
-// Whether a launch over nsites sites takes one workgroup per site.  From n = 26
-// on it is as fast or faster on every size measured (us, before and now; apply:
-// FP64 n = 48 on 32 sites 31 and 11, on 2048 116 and 115, on 8192 620 and 452;
-// FP32 n = 64 on 512 55 and 27; odd-even pair: 16-bit n = 52 on 1024 94 and 30).
+// Whether a launch over nsites sites (of one parity in the odd-even operator) takes
+// one workgroup per site.  From n = 26 on it is as fast or faster on every size
+// measured (us, before and now; apply: FP64 n = 48 on 32 sites 31 and 11, on 2048
+// 116 and 115, on 8192 620 and 452; FP32 n = 64 on 512 55 and 27; odd-even pair:
+// 16-bit n = 52 on 1024 94 and 30).
 // Smaller sites give eight wavefronts too little work once the grid fills the
 // card (FP32 n = 16: pair on 512 sites 23 and 11, apply on 1024 10.5 and 11.9,
 // on 8192 45 and 82).
@@ -880,8 +881,8 @@ __global__ void __launch_bounds__(256) k_coarse_hop_inv_odd(CGeom cg,
 // cores, as three columns that add up to it (FP16 blocks: the parts of an FP32 entry
 // leave FP16's range).  us per pair, eight wavefronts on a site's rows and so: 32
 // sites of n = 32 10.6 and 8.2, of n = 48 15.3 and 10.7; 1024 of n = 64 34.4 and
-// 33.3; 4096 of n = 48 82.6 and 60.0.  n = 16 on more sites has four to a workgroup
-// of the vector kernels.  Relative error of the full stencil against 64 bits, n = 16
+// 33.3; 4096 of n = 48 82.6 and 60.0.  n = 16 on more than 512 sites stays on the
+// vector kernels (one_site: above 1024 sites, four to a workgroup).  Relative error of the full stencil against 64 bits, n = 16
 // to 64: 9e-8 to 1.2e-7 there, 7e-8 here.
 static inline bool one_mfma(int nsites, int n) { return n % 16 == 0 && (n > 16 || nsites <= 512); }
 template <class R, class S>

@@ -193,8 +193,8 @@ __device__ __forceinline__ void hop_inv_block(const typename store_traits<S>::el
 // clover and inverses of a block come from L2 after the first MR step), so the
 // levers are fewer instructions and no idle issue slots: unrolled directions with
 // compile-time spin projections, T_oo^{-1} as one product, 16-byte loads and LDS
-// accesses, each direction's links and each third of T_oo^{-1}'s rows loaded
-// while the one before multiplies.  1042 -> 769 us a sweep there, 105 -> 84 us
+// accesses, each direction's links and each three rows of T_oo^{-1} loaded while
+// those before multiply.  1042 -> 769 us a sweep there, 105 -> 84 us
 // with one field and FP32 links at 24x16x16x24.  All 256 registers are in use:
 // with 168 (three wavefronts per SIMD) these take 1086 and 129 us.  Small grids, and
 // one field with FP32 links on blocks that fill its wavefronts, take k_sap_two.
@@ -626,25 +626,25 @@ static inline bool sap_two(const Geom& g, int nwg, int K) {
   return 4 * g.half > 3 * slots ? waves >= 1536 : 4 * g.half == 3 * slots && waves >= 6144;
 }
 template <class R, class S>
-void launch_sap(const Geom& g, int colour, const void* U, const R* H, const R* Minv, Twist tw, const cx<R>* b,
+void launch_sap(const Geom& g, int colour, const void* U, const R* H, const R* Tinv, Twist tw, const cx<R>* b,
                 cx<R>* x, int n_mr, hipStream_t st) {
-  launch_sap_multi<R, S>(g, colour, U, H, Minv, tw, b, x, n_mr, 1, 0, st);
+  launch_sap_multi<R, S>(g, colour, U, H, Tinv, tw, b, x, n_mr, 1, 0, st);
 }
 template <class R, class S>
-void launch_sap_multi(const Geom& g, int colour, const void* U, const R* H, const R* Minv, Twist tw, const cx<R>* b,
+void launch_sap_multi(const Geom& g, int colour, const void* U, const R* H, const R* Tinv, Twist tw, const cx<R>* b,
                       cx<R>* x, int n_mr, int K, long ld, hipStream_t st) {
   if constexpr (sizeof(R) == 4) {
     if (sap_two<S>(g, (g.nblocks / 2) * K, K)) {
       // ev and od (which the staged x, 24 half entries, fits in) and ex
       const size_t sm = (12 * (size_t)(g.half + 1) + 6 * (size_t)g.half) * sizeof(cxpair<float>);
       hipLaunchKernelGGL(k_sap_two<S>, dim3((g.nblocks / 2) * K), dim3(2 * ((g.half + 63) / 64 * 64)), sm, st, g, colour,
-                         (const typename store_traits<S>::elem*)U, H, Minv, TwistR<R>(tw), b, x, n_mr, K, ld);
+                         (const typename store_traits<S>::elem*)U, H, Tinv, TwistR<R>(tw), b, x, n_mr, K, ld);
       return;
     }
   }
   size_t sm = 2 * 12 * (size_t)(g.half + 1) * sizeof(cx<R>);
   hipLaunchKernelGGL((k_sap<R, S>), dim3((g.nblocks / 2) * K), dim3(g.half), sm, st, g, colour,
-                     (const typename store_traits<S>::elem*)U, H, Minv, TwistR<R>(tw), b, x, n_mr, K, ld);
+                     (const typename store_traits<S>::elem*)U, H, Tinv, TwistR<R>(tw), b, x, n_mr, K, ld);
 }
 template void launch_sap_multi<double, double>(const Geom&, int, const void*, const double*, const double*, Twist,
                                                const cx<double>*, cx<double>*, int, int, long, hipStream_t);

@@ -62,11 +62,15 @@ void launch_dirac_multi(const Geom& g, const void* U, const R* H, Twist tw, int 
 template <class R, class S>
 void launch_dirac_lex(const Geom& g, const void* U, const R* H, Twist tw, int K, long ld, const cx<double>* in,
                       cx<double>* out, hipStream_t st);
+// one SAP colour sweep of one field, of K fields at a stride of ld.  Tinv, the odd
+// sites' inverses: R = double, M = (H^2 + tw.o^2)^{-1} of launch_odd_inverse, which serves
+// both signs of tw.o; R = float, T^{-1} of launch_chunk_tinv for exactly tw.o, sign
+// included (the sweep does not look at tw.o there)
 template <class R, class S>
-void launch_sap(const Geom& g, int colour, const void* U, const R* H, const R* Minv, Twist tw, const cx<R>* b,
+void launch_sap(const Geom& g, int colour, const void* U, const R* H, const R* Tinv, Twist tw, const cx<R>* b,
                 cx<R>* x, int n_mr, hipStream_t st);
 template <class R, class S>
-void launch_sap_multi(const Geom& g, int colour, const void* U, const R* H, const R* Minv, Twist tw, const cx<R>* b,
+void launch_sap_multi(const Geom& g, int colour, const void* U, const R* H, const R* Tinv, Twist tw, const cx<R>* b,
                       cx<R>* x, int n_mr, int K, long ld, hipStream_t st);
 // K spinor fields, lexicographic (stride ldl) <-> block layout (stride ldb)
 template <class L, class R>
@@ -279,8 +283,6 @@ void launch_coarse_apply_mrhs(const CGeom& cg, const void* D, double tw, int K, 
 template <class S>
 void launch_coarse_schur_even_mrhs(const CGeom& cg, const void* D, double tw, int K, long ldv, const cx<float>* v,
                                    const cx<float>* t, cx<float>* y, int mode, hipStream_t st);
-// SAP colour sweep of an intermediate level for K fields (K <= 16), one
-// workgroup per block (bsz <= 16 sites), matrix cores
 // odd-even operator of one FP32 column on BF16 blocks of n = 16, 32, 48 or 64
 template <class S>
 void launch_coarse_schur_even_one(const CGeom& cg, const void* D, double tw, const cx<float>* v, const cx<float>* t,
@@ -288,6 +290,8 @@ void launch_coarse_schur_even_one(const CGeom& cg, const void* D, double tw, con
 template <class S>
 void launch_coarse_hop_inv_odd_one(const CGeom& cg, const void* D, const cx<float>* Minv, const cx<float>* x,
                                    const cx<float>* base, cx<float>* y, hipStream_t st);
+// SAP colour sweep of an intermediate level for K fields (K <= 16), one
+// workgroup per block (bsz <= 16 sites), matrix cores
 template <class S>
 void launch_coarse_sap_mrhs(const CGeom& cg, const void* D, double tw, int nblk_colour, int bsz, const int* blk_sites,
                             const int* blk_nbr, const cx<float>* r, cx<float>* x, int n_mr, int K, long ld,

@@ -1,6 +1,5 @@
 """K-column coarse operators of small and large grids, on the GPU: up to eight
-columns take the kernels that split a site over four groups of wavefronts
-(n = 64 on more than 512 sites per launch: one wavefront per 16 rows), more
+columns take the kernels that split a site over four groups of wavefronts, more
 columns the two-tile kernels.  The first columns of a 16-column application and
 the same columns alone take different kernels on equally rounded inputs, so
 they differ by the FP32 summation order only: 1e-5 of the norm of the
@@ -23,7 +22,7 @@ KAPPA, CSW, MU = 0.13729, 1.57551, 0.0009
 @pytest.mark.parametrize("dims,nv", [((4, 4, 4, 4), 8),       # 16 sites, n = 16
                                      ((8, 8, 8, 16), 16),     # 512 sites, n = 32
                                      ((8, 8, 8, 16), 24),     # n = 48
-                                     ((8, 8, 8, 32), 32),     # 1024 sites, n = 64: 512 per parity, split
+                                     ((8, 8, 8, 32), 32),     # 1024 sites, n = 64: 512 per parity
                                      ((8, 8, 16, 24), 32)])   # 1536 sites, n = 64: 768 per parity
 def test_columns_alone_and_among_sixteen(dims, nv, prec):
     if not torch.cuda.is_available():
@@ -139,11 +138,11 @@ def test_even_rows_alone_on_few_sites(dims, nv):
 @pytest.mark.parametrize("dims,nv", [((4, 4, 4, 4), 8), ((4, 4, 4, 8), 16), ((4, 4, 8, 8), 24), ((8, 8, 8, 16), 32),
                                      ((8, 8, 8, 24), 16)])   # the last: 768 sites
 def test_one_column_odd_even_solve(dims, nv, prec):
-    """The coarsest solve of one column (BF16 blocks on up to 512 sites: the matrix
-    cores, its FP32 entries in three parts) to 1e-4, b on the even sites only: the
+    """The coarsest solve of one column (BF16 blocks: the matrix cores, its FP32
+    entries in three parts) to 1e-4, b on the even sites only: the
     even-site residual by the single-column stencil is that of the odd-even system,
     so 1e-4 of b and the 1e-5 of the FP32 operator.  Entries of b over twelve
-    decades, so that every part of an entry counts somewhere."""
+    decades too.  (The accuracy of the operators themselves: test_gpu_one_column.py.)"""
     if not torch.cuda.is_available():
         pytest.skip("needs a GPU")
     from paper_1611_01034_amd import ddamg, synth
