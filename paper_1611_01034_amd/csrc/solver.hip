@@ -61,9 +61,15 @@ __global__ void __launch_bounds__(256) k_minv_odd(CGeom cg, const cx<R>* __restr
   }
 }
 
-__global__ void k_all_finite(long n, const double* __restrict__ a, int* __restrict__ flag) {
-  long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n && !isfinite(a[i])) atomicOr(flag, 1);
+// a launch holds fewer than 2^32 threads, and the right-hand sides of a lock-step
+// group or the links of a large lattice are more numbers than that: each thread
+// takes every stride-th one
+__global__ void __launch_bounds__(256) k_all_finite(long n, const double* __restrict__ a, int* __restrict__ flag) {
+  const long stride = (long)gridDim.x * 256;
+  bool ok = true;
+#pragma unroll 4
+  for (long i = (long)blockIdx.x * 256 + threadIdx.x; i < n; i += stride) ok = ok && isfinite(a[i]);
+  if (!ok) atomicOr(flag, 1);
 }
 
 // ---------------------------------------------------------------------------
@@ -1906,7 +1912,8 @@ std::unique_ptr<MGBase> make_mg(Ctx& c) {
 // exported for the API file
 void check_finite(Ctx& c, const double* dev, long n) {
   HIP_CHECK(hipMemsetAsync(c.iflag.p, 0, sizeof(int), c.st));
-  hipLaunchKernelGGL(k_all_finite, dim3((n + 255) / 256), dim3(256), 0, c.st, n, dev, c.iflag.as<int>());
+  hipLaunchKernelGGL(k_all_finite, dim3((unsigned)std::min<long>((n + 1023) / 1024, 65536)), dim3(256), 0, c.st, n,
+                     dev, c.iflag.as<int>());
   int h = 0;
   HIP_CHECK(hipMemcpyAsync(&h, c.iflag.p, sizeof(int), hipMemcpyDeviceToHost, c.st));
   HIP_CHECK(hipStreamSynchronize(c.st));
